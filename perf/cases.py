@@ -1,0 +1,677 @@
+"""The calls that a user of this framework makes, with their inputs and their values in 64 bits.
+
+listed() names the calls that are followed, draw() gives more of the same ranges, prepare() makes what
+a program has in hand before the call, run() is the call through the package's public functions,
+work() the bytes and operations that it cannot do without and exact() its result in float64 by plain
+torch and numpy.
+
+Lengths are in h^-1 Mpc.  Particle states are those of a late node: a lattice displaced by a seeded
+random field with a spectrum like that of cold dark matter (each particle moved by a few mesh cells,
+many paths crossed), and positions with haloes where haloes are looked for.
+"""
+
+import math
+import os
+
+import numpy as np
+import torch
+
+import paper_1509_04685_amd as cola
+from paper_1509_04685_amd import learned
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+WEIGHTS = os.path.join(os.path.dirname(HERE), "paper_1509_04685_amd", "lc_weights_c16.json")
+COSMO = dict(omega_m=0.25, omega_b=0.044, h=0.7, n_s=0.95, sigma_8=0.8)
+Z_INIT, NODES, LATE = 19.0, 40, 30  # 40 nodes linear in a from z = 19; node 30 is z = 0.28
+CELL = 3.0                          # h^-1 Mpc between particles, as in the headline workload
+
+# mesh sides the transforms take: even, no prime factor but 2 and 3
+SMOOTH = sorted(2 ** a * 3 ** b for a in range(1, 11) for b in range(7) if 16 <= 2 ** a * 3 ** b <= 768)
+
+
+def listed():
+    return [
+        # a whole small run: initial conditions and 10 nodes of 32^3 particles on 96^3 cells; launches
+        # and latency count
+        dict(name="run_32", kind="run", n_part=32, pm=3, box=256.0, nodes=10),
+        # three nodes of a particle-mesh run of moderate size with the library's default kernel shapes,
+        # as the training and calibration scripts make them by the hundred
+        dict(name="step_128", kind="step", n_part=128, pm=3, frame="cola", tuned=False),
+        # the same at a mesh side that no table of plans was made for, two cells per particle and the
+        # plain leapfrog frame
+        dict(name="step_108_pm", kind="step", n_part=108, pm=2, frame="pm", tuned=False),
+        # the headline: 256^3 particles on 768^3 cells, kernel shapes tuned first as a long run does
+        dict(name="step_256", kind="step", n_part=256, pm=3, frame="cola", tuned=True),
+        # mocks: two shape classes of seeded realizations in one graph, tuned first
+        dict(name="ensemble", kind="ensemble", n_a=96, n_b=128, members=4, nodes=5, tuned=True),
+        # three nodes with the learned force correction on the coarse mesh
+        dict(name="learned_256", kind="learned", n_part=256),
+        # one training step of the correction network: forward, loss, backward
+        dict(name="train_128", kind="train", n=128, channels=16, force_input=False),
+        # friends-of-friends haloes of a large snapshot, with catalogue and mass function
+        dict(name="haloes_256", kind="haloes", n_part=256),
+        # spectra of a large snapshot: P(k), and multipoles in redshift space
+        dict(name="spectra_256", kind="spectra", n_part=256, n_pk=768),
+        # the fields of one training pair: coarse density, force meshes and accelerations, and the
+        # accelerations of the fine mesh
+        dict(name="fields_128", kind="fields", n_part=128, coarse=128, fine=384),
+        # a forward and an inverse transform of a field of a ragged size
+        dict(name="fft_324", kind="fft", n=324),
+        # cloud-in-cell density of an odd number of clustered points on a mesh that no power of two divides
+        dict(name="density_250", kind="density", particles=1000003, mesh=250),
+    ]
+
+
+def _smooth_between(rng, lo, hi, multiple=1):
+    """A mesh side of SMOOTH, spread over the logarithm of the range."""
+    want = math.exp(rng.uniform(math.log(lo), math.log(hi)))
+    sides = [n for n in SMOOTH if lo <= n <= hi and n % multiple == 0]
+    return min(sides, key=lambda n: abs(math.log(n / want)))
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    kind = rng.choice(["run", "step", "step", "ensemble", "learned", "train", "haloes", "spectra", "fields", "fft",
+                       "density"])
+    if kind == "run":
+        return dict(kind=kind, n_part=_smooth_between(rng, 16, 64), pm=rng.choice([1, 2, 3]),
+                    box=round(rng.uniform(64.0, 300.0), 1), nodes=rng.choice([5, 10]))
+    if kind == "step":
+        n = _smooth_between(rng, 32, 256)
+        return dict(kind=kind, n_part=n, pm=rng.choice([1, 2, 3]), frame=rng.choice(["cola", "cola", "pm"]),
+                    tuned=False)
+    if kind == "ensemble":
+        return dict(kind=kind, n_a=_smooth_between(rng, 32, 96), n_b=_smooth_between(rng, 32, 128),
+                    members=rng.randint(2, 5), nodes=rng.choice([3, 5]), tuned=False)
+    if kind == "learned":
+        return dict(kind=kind, n_part=_smooth_between(rng, 48, 256, 16))
+    if kind == "train":
+        return dict(kind=kind, n=16 * _log_int(rng, 3, 9), channels=rng.choice([16, 16, 32]),
+                    force_input=rng.choice([False, True]))
+    if kind == "haloes":
+        return dict(kind=kind, n_part=_log_int(rng, 40, 256))
+    if kind == "spectra":
+        return dict(kind=kind, n_part=_smooth_between(rng, 32, 256), n_pk=_smooth_between(rng, 64, 768))
+    if kind == "fields":
+        return dict(kind=kind, n_part=_log_int(rng, 32, 160), coarse=_smooth_between(rng, 32, 162),
+                    fine=_smooth_between(rng, 96, 486))
+    if kind == "fft":
+        return dict(kind=kind, n=_smooth_between(rng, 16, 768))
+    return dict(kind=kind, particles=_log_int(rng, 10_000, 10_000_000), mesh=_log_int(rng, 16, 512))
+
+
+# ---------------------------------------------------------------- seeded inputs
+
+
+def _gen(seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(int(seed))
+    return g
+
+
+def _modes(n, dtype):
+    m = torch.fft.fftfreq(n, 1.0 / n, device="cuda", dtype=dtype)
+    mz = torch.fft.rfftfreq(n, 1.0 / n, device="cuda", dtype=dtype)
+    return m[:, None, None], m[None, :, None], mz[None, None, :]
+
+
+def _displacements(n, box, rms, seed):
+    """(3, n^3) float32: a curl-free Gaussian field of the given rms per axis, |psi_k|^2 ~ P(k) / k^2 with
+    P ~ k at small k and ~ k^-2.4 at large."""
+    w = torch.fft.rfftn(torch.randn((n, n, n), generator=_gen(seed), device="cuda"))
+    mx, my, mz = _modes(n, torch.float32)
+    k2 = (mx * mx + my * my + mz * mz) * (2.0 * math.pi / box) ** 2
+    k2[0, 0, 0] = 1.0
+    k = k2.sqrt()
+    amp = k.sqrt() / (1.0 + k / 0.05) ** 1.7
+    amp[0, 0, 0] = 0.0
+    weight = torch.full((n // 2 + 1,), 2.0, device="cuda", dtype=torch.float64)
+    weight[0] = weight[-1] = 1.0
+    var = float(((amp.double() ** 2 / k2.double()).sum(dim=(0, 1)) * weight).sum()) / (3.0 * n ** 3)
+    w *= amp / k2 * (rms / math.sqrt(var))
+    out = torch.empty((3, n ** 3), device="cuda")
+    for d, m in enumerate((mx, my, mz)):
+        out[d] = torch.fft.irfftn(w * (1j * m * (2.0 * math.pi / box)), s=(n, n, n)).reshape(-1)
+    return out
+
+
+def _lattice(n, dtype):
+    i = torch.arange(n, device="cuda", dtype=dtype)
+    return torch.stack(torch.meshgrid(i, i, i, indexing="ij")).reshape(3, -1)
+
+
+def _wrap(pos, box):
+    """float32 positions in [0, box)."""
+    p = torch.remainder(pos, box).float().contiguous()
+    p[p >= box] = 0.0
+    return p
+
+
+def _late_positions(n, box, seed):
+    return _wrap((_lattice(n, torch.float64) + 0.5) * (box / n) + _displacements(n, box, 3.5, seed).double(), box)
+
+
+def _halo_positions(n, box, seed):
+    """Positions of n^3 particles in lattice order, half of the 8^3 blocks of the lattice with an inner cube of
+    3^3 to 8^3 particles fallen into a Plummer sphere, all carried along by a smooth displacement."""
+    h = box / n
+    g = _gen(seed + 7)
+    disp = _displacements(n, box, 3.5, seed).double().reshape(3, n, n, n)
+    idx = _lattice(n, torch.int64)
+    nb = (n + 7) // 8
+    block, local = idx // 8, idx % 8
+    b = (block[0] * nb + block[1]) * nb + block[2]
+    side = torch.randint(3, 9, (nb ** 3,), generator=g, device="cuda")
+    fallen = torch.rand(nb ** 3, generator=g, device="cuda") < 0.5
+    member = fallen[b] & (local < side[b]).all(dim=0)
+    first = torch.clamp(block * 8 + 3, max=n - 1)
+    centre = (first + 0.5) * h + disp[:, first[0], first[1], first[2]]
+    u = torch.rand(n ** 3, generator=g, device="cuda", dtype=torch.float64) * 0.95 + 0.02
+    v = torch.randn((3, n ** 3), generator=g, device="cuda", dtype=torch.float64)
+    scale = 0.06 * h * side[b].double()
+    r = torch.clamp(scale / torch.sqrt(u ** (-2.0 / 3.0) - 1.0), max=3.0 * h)
+    free = (idx + 0.5) * h + disp.reshape(3, -1) + 0.05 * h * v
+    return _wrap(torch.where(member, centre + v / v.norm(dim=0) * r, free), box)
+
+
+def _points(case, box, seed):
+    """Clustered points in no order: half of them uniform, half in Gaussian clumps."""
+    n, g = case["particles"], _gen(seed)
+    pos = torch.rand((3, n), generator=g, device="cuda", dtype=torch.float64) * box
+    k, clumps = n // 2, 64
+    centre = torch.rand((3, clumps), generator=g, device="cuda", dtype=torch.float64) * box
+    which = torch.randint(0, clumps, (k,), generator=g, device="cuda")
+    pos[:, :k] = centre[:, which] + torch.randn((3, k), generator=g, device="cuda", dtype=torch.float64) * (0.02 * box)
+    return _wrap(pos, box)
+
+
+def _state_arrays(n, box, d1, d2, seed):
+    """x, p, psi1, psi2 of a late node, (3, n^3) float32 each."""
+    psi1 = _displacements(n, box, 4.0, seed)
+    psi2 = _displacements(n, box, 1.0, seed + 1_000_003)
+    p = _displacements(n, box, 0.3, seed + 2_000_003)
+    return d1 * psi1 + d2 * psi2 + p, p, psi1, psi2
+
+
+def _net_inputs(case, seed):
+    """Network parameters and the fields of a training pair: density, coarse force, positions, accelerations."""
+    n, c, g = case["n"], case["channels"], _gen(seed)
+    box = CELL * n
+
+    def normal(count, std):
+        return torch.randn(count, generator=g, device="cuda") * std
+    params = torch.cat([normal(108 * c, math.sqrt(2.0 / 108)), normal(c, 0.02), normal(27 * c * c, math.sqrt(2.0 / (27 * c))),
+                        normal(c, 0.02), normal(3 * c, 0.3 / math.sqrt(c)), normal(3, 0.02)])
+    psi = _displacements(n, box, 3.5, seed + 5)
+    pos = _wrap((_lattice(n, torch.float64) + 0.5) * CELL + psi.double(), box)
+    delta = torch.randn((n, n, n), generator=g, device="cuda").exp_().sub_(1.6)
+    force = psi.reshape(3, n, n, n).contiguous()
+    acc = psi + 0.2 * torch.randn((3, n ** 3), generator=g, device="cuda")
+    target = acc + 0.3 * torch.randn((3, n ** 3), generator=g, device="cuda")
+    in_scale = (0.5,) + ((0.3, 0.3, 0.3) if case["force_input"] else (0.0, 0.0, 0.0))
+    return params, in_scale, 0.4, box, pos, delta, force, acc, target
+
+
+_TUNED = set()
+
+
+def _tune_once(key, f):
+    """Kernel shapes hold for the process: a program tunes each of its sizes once."""
+    if key not in _TUNED:
+        _TUNED.add(key)
+        f()
+
+
+def prepare(case, seed):
+    kind = case["kind"]
+    s = dict(case=case)
+    if kind == "run":
+        s["prob"] = cola.make_problem(case["box"], case["n_part"], case["pm"], Z_INIT, case["nodes"])
+        s["cosmo"] = cola.make_cosmology(**COSMO)
+        s["state"], s["ws"], s["seed"] = cola.ParticleState(s["prob"]), cola.Workspace(s["prob"]), int(seed)
+    elif kind in ("step", "learned", "spectra"):
+        n = case["n_part"]
+        box = CELL * n
+        pm = case.get("pm", 1)
+        s["cosmo"] = cola.make_cosmology(**COSMO)
+        s["prob"] = cola.make_problem(box, n, pm, Z_INIT, NODES, frame=case.get("frame", "cola"))
+        s["ws"] = cola.Workspace(s["prob"], n_pk=case.get("n_pk", 0))
+        s["state"] = cola.ParticleState(s["prob"])
+        a, d1, d2 = _node(LATE)
+        arrays = _state_arrays(n, box, d1, d2, seed)
+        for name, v in zip(("x", "p", "psi1", "psi2"), arrays):
+            getattr(s["state"], name).copy_(v)
+        s["state"].c.node = LATE
+        s["a"] = a
+        if kind != "spectra":
+            s["x0"], s["p0"] = arrays[0].contiguous(), arrays[1]
+        if case.get("tuned"):
+            _tune_once((n, pm), lambda: cola.autotune(s["prob"], s["ws"], state=s["state"]))
+        if kind == "learned":
+            s["net"], _ = learned.load_net(WEIGHTS)
+            s["lws"] = cola.lc_workspace(n, s["net"].channels)
+    elif kind == "ensemble":
+        s["cosmo"] = cola.make_cosmology(**COSMO)
+        classes = []
+        for k, n in enumerate((case["n_a"], case["n_b"])):
+            m = case["members"]
+            prob = cola.make_problem(3.125 * n, n, 3, Z_INIT, case["nodes"], n_real=m)
+            classes.append(dict(prob=prob, seeds=[int(seed) * 64 + 16 * k + r for r in range(m)], a_out=(), n_pk=0,
+                                n_bins=1))
+        s["ens"] = cola.Ensemble(classes, s["cosmo"])
+        if case.get("tuned"):
+            _tune_once((case["n_a"], case["n_b"], case["members"]), s["ens"].autotune)
+    elif kind == "train":
+        params, in_scale, out_scale, box, pos, delta, force, acc, target = _net_inputs(case, seed)
+        s["net"] = cola.LcNet(case["channels"], params=params.cpu().numpy(), in_scale=in_scale, out_scale=out_scale)
+        s["ws"] = cola.lc_workspace(case["n"], case["channels"], training=True)
+        s.update(box=box, pos=pos, delta=delta, force=force, acc=acc, target=target)
+    elif kind == "haloes":
+        n = case["n_part"]
+        s["box"] = CELL * n
+        s["pos"] = _halo_positions(n, s["box"], seed)
+        s["link"] = cola.linking_length(s["box"], n)
+        s["m_p"] = cola.particle_mass(cola.make_cosmology(**COSMO), s["box"], n)
+        s["edges"] = [math.log10(s["m_p"] * 50) + 0.2 * b for b in range(11)]
+        s["ws"] = cola.fof_workspace(n ** 3, s["box"], s["link"])
+    elif kind == "fields":
+        n = case["n_part"]
+        s["box"] = CELL * n
+        s["pos"] = _late_positions(n, s["box"], seed)
+        need = cola._lib.lib().cola_pm_fields_workspace_bytes(max(case["coarse"], case["fine"]))
+        s["ws"] = torch.empty(int(need), dtype=torch.uint8, device="cuda")
+    elif kind == "fft":
+        n = case["n"]
+        s["x"] = torch.randn((n, n, n), generator=_gen(seed), device="cuda")
+    elif kind == "density":
+        s["box"] = 500.0
+        s["pos"] = _points(case, s["box"], seed)
+        need = cola._lib.lib().cola_cic_workspace_bytes(case["particles"], case["mesh"])
+        s["ws"] = torch.empty(int(need), dtype=torch.uint8, device="cuda")
+    else:
+        raise ValueError(kind)
+    return s
+
+
+def run(s):
+    case = s["case"]
+    kind = case["kind"]
+    if kind == "run":
+        cola.ic_2lpt(s["prob"], s["cosmo"], [s["seed"]], s["state"], s["ws"])
+        cola.step(s["prob"], s["cosmo"], s["state"], case["nodes"] - 1, s["ws"])
+        return dict(x=s["state"].x, p=s["state"].p, psi1=s["state"].psi1, psi2=s["state"].psi2)
+    if kind in ("step", "learned"):
+        st = s["state"]
+        st.x.copy_(s["x0"])  # a run taken up again from a stored node
+        st.p.copy_(s["p0"])
+        st.c.node = LATE
+        st.invalidate_force()
+        if kind == "step":
+            cola.step(s["prob"], s["cosmo"], st, LATE + 3, s["ws"])
+        else:
+            cola.step_lc(s["prob"], s["cosmo"], st, LATE + 3, s["net"], s["lws"], s["ws"])
+        return dict(x=st.x, p=st.p)
+    if kind == "ensemble":
+        s["ens"].run()
+        return [dict(x=it["state"].x, p=it["state"].p) for it in s["ens"].items]
+    if kind == "train":
+        net = s["net"]
+        net.grads.zero_()
+        df = cola.lc_forward(net, s["delta"], s["force"], s["ws"], training=True)
+        stats, d_df = cola.lc_loss(s["pos"], s["box"], df, s["acc"], s["target"])
+        cola.lc_backward(net, d_df, s["ws"])
+        return dict(df=df, stats=stats, d_df=d_df, grads=net.grads)
+    if kind == "haloes":
+        group, size = cola.fof(s["pos"], s["box"], s["link"], s["ws"])
+        cat = cola.fof_catalogue(s["pos"], s["box"], group, size, 101, s["m_p"], s["ws"])
+        hist = cola.fof_mass_histogram(size, 20, s["m_p"], s["edges"])
+        # the catalogue goes into a table of fixed size, with room for every halo that there can be
+        room = size.numel() // 101 - cat["n"].numel()
+        return dict(group=group, size=size, hist=hist,
+                    **{k: torch.nn.functional.pad(v, (0, room)) for k, v in cat.items()})
+    if kind == "spectra":
+        n_pk = case["n_pk"]
+        pk = cola.power_spectrum(s["prob"], s["cosmo"], s["state"], s["a"], n_pk, n_pk // 2, s["ws"])
+        ell = cola.power_multipoles(s["prob"], s["cosmo"], s["state"], s["a"], n_pk, n_pk // 2, s["ws"])
+        return list(pk) + list(ell)
+    if kind == "fields":
+        out = cola.pm_fields(s["pos"], case["coarse"], s["box"], ws=s["ws"])
+        out["fine"] = cola.pm_fields(s["pos"], case["fine"], s["box"], delta=False, g=False, ws=s["ws"])["acc"]
+        return out
+    if kind == "fft":
+        xk = cola.fft_r2c(s["x"])
+        return dict(xk=xk, x=cola.fft_c2r(xk))
+    return cola.cic_density(s["pos"], case["mesh"], s["box"], ws=s["ws"])
+
+
+# ---------------------------------------------------------------- least work
+
+
+def _fft_flops(n):
+    return 2.5 * n ** 3 * math.log2(n ** 3)
+
+
+def work(case):
+    """Bytes: each input read and each output written once.  Operations: the transforms, the convolutions, and
+    some tens per particle."""
+    kind = case["kind"]
+    if kind == "run":
+        n, ng, nodes = case["n_part"], case["n_part"] * case["pm"], case["nodes"]
+        return dict(bytes=48.0 * n ** 3, flops=14 * _fft_flops(n) + nodes * (4 * _fft_flops(ng) + 150.0 * n ** 3))
+    if kind in ("step", "learned"):
+        n = case["n_part"]
+        f = 4 * (4 * _fft_flops(n * case.get("pm", 1)) + 150.0 * n ** 3)
+        if kind == "learned":
+            f += 4 * n ** 3 * 2.0 * (27 * 16 + 27 * 256 + 48)
+        return dict(bytes=72.0 * n ** 3, flops=f)
+    if kind == "ensemble":
+        b = f = 0.0
+        for n in (case["n_a"], case["n_b"]):
+            b += 24.0 * n ** 3 * case["members"]
+            f += case["members"] * (14 * _fft_flops(n) + case["nodes"] * (4 * _fft_flops(3 * n) + 150.0 * n ** 3))
+        return dict(bytes=b, flops=f)
+    if kind == "train":
+        v, c = case["n"] ** 3, case["channels"]
+        return dict(bytes=(4 + 12 + 12 + 12 + 12 + 12 + 12) * v, flops=2.0 * v * (2 * 27 * 4 * c + 3 * 27 * c * c + 6 * c) + 200.0 * v)
+    if kind == "haloes":
+        n = case["n_part"] ** 3
+        return dict(bytes=20.0 * n, flops=130.0 * n)
+    if kind == "spectra":
+        return dict(bytes=48.0 * case["n_part"] ** 3, flops=2 * _fft_flops(case["n_pk"]))
+    if kind == "fields":
+        n, c = case["n_part"] ** 3, case["coarse"] ** 3
+        return dict(bytes=36.0 * n + 16.0 * c, flops=4 * _fft_flops(case["coarse"]) + 4 * _fft_flops(case["fine"]) + 100.0 * n)
+    if kind == "fft":
+        n = case["n"]
+        return dict(bytes=4.0 * n ** 3 * 2 + 2 * 8.0 * n * n * (n // 2 + 1), flops=2 * _fft_flops(n))
+    return dict(bytes=12.0 * case["particles"] + 4.0 * case["mesh"] ** 3, flops=40.0 * case["particles"])
+
+
+# ---------------------------------------------------------------- the same in 64 bits
+
+_LEG = np.polynomial.legendre.leggauss(64)
+
+
+def _integral(f, lo, hi):
+    x, w = _LEG
+    return float(0.5 * (hi - lo) * np.sum(w * f(0.5 * (hi + lo) + 0.5 * (hi - lo) * x)))
+
+
+def _hubble(a):
+    return np.sqrt(COSMO["omega_m"] / a ** 3 + 1.0 - COSMO["omega_m"])
+
+
+def _growth(a):
+    """D1, D2 and their derivatives in a, by Runge-Kutta in ln a from matter domination, D1(1) = 1."""
+    om = COSMO["omega_m"]
+
+    def rhs(y, s):
+        e3 = om * math.exp(-3.0 * y)
+        e2 = e3 + 1.0 - om
+        c, d = 1.5 * e3 / e2, 2.0 - 1.5 * e3 / e2
+        return np.array([s[1], c * s[0] - d * s[1], s[3], c * (s[2] - s[0] ** 2) - d * s[3]])
+    got = []
+    y, s = math.log(1e-6), np.array([1e-6, 1e-6, -3.0 / 7.0 * 1e-12, -6.0 / 7.0 * 1e-12])
+    for end in sorted({math.log(a), 0.0}):
+        steps = max(1, int((end - y) * 400))
+        h = (end - y) / steps
+        for _ in range(steps if end > y else 0):
+            k1 = rhs(y, s)
+            k2 = rhs(y + h / 2, s + h / 2 * k1)
+            k3 = rhs(y + h / 2, s + h / 2 * k2)
+            k4 = rhs(y + h, s + h * k3)
+            s, y = s + h / 6 * (k1 + 2 * k2 + 2 * k3 + k4), y + h
+        y = end
+        got.append(s)
+    n, s = got[-1][0], got[0]
+    return s[0] / n, s[2] / n ** 2, s[1] / n / a, s[3] / n ** 2 / a
+
+
+_NODE = {}
+
+
+def _nodes(count):
+    a0 = 1.0 / (1.0 + Z_INIT)
+    return a0 + np.arange(count) * ((1.0 - a0) / (count - 1))
+
+
+def _node(j):
+    if j not in _NODE:
+        a = float(_nodes(NODES)[j])
+        _NODE[j] = (a,) + tuple(float(v) for v in _growth(a)[:2])
+    return _NODE[j]
+
+
+def _corners(u, n):
+    """The eight cells of each point of cell coordinates u (3, N), as flat indices, and their weights."""
+    m = torch.floor(u)
+    f = u - m
+    m = m.long()
+    for c in range(8):
+        o = (c >> 2 & 1, c >> 1 & 1, c & 1)
+        i = [torch.remainder(m[d] + o[d], n) for d in range(3)]
+        w = 1.0
+        for d in range(3):
+            w = w * (f[d] if o[d] else 1.0 - f[d])
+        yield (i[0] * n + i[1]) * n + i[2], w
+
+
+def _density64(u, n):
+    mesh = torch.zeros(n ** 3, device="cuda", dtype=torch.float64)
+    for i, w in _corners(u, n):
+        mesh.index_add_(0, i, w)
+    return (mesh * (n ** 3 / u.shape[1]) - 1.0).reshape(n, n, n)
+
+
+def _unit_modes(n):
+    """Integer modes with the Nyquist one zero (for odd powers), and k^2 with 1 at k = 0."""
+    m = _modes(n, torch.float64)
+    k2 = m[0] ** 2 + m[1] ** 2 + m[2] ** 2
+    k2[0, 0, 0] = 1.0
+    odd = [torch.where(v.abs() == n // 2, torch.zeros_like(v), v) for v in m]
+    return m, odd, k2
+
+
+def _force64(delta, box):
+    n = delta.shape[0]
+    _, odd, k2 = _unit_modes(n)
+    dk = torch.fft.rfftn(delta) / k2
+    dk[0, 0, 0] = 0.0
+    for v in odd:
+        yield torch.fft.irfftn(dk * (1j * v * (box / (2.0 * math.pi))), s=(n, n, n)).reshape(-1)
+
+
+def _acceleration64(u, n, box, delta=None):
+    delta = _density64(u, n) if delta is None else delta
+    out = torch.empty_like(u)
+    for d, g in enumerate(_force64(delta, box)):
+        out[d] = 0.0
+        for i, w in _corners(u, n):
+            out[d] += w * g[i]
+    return out
+
+
+def _steps64(n_part, pm, box, frame, nodes, j0, j1, x, p, psi1, psi2):
+    ng = n_part * pm
+    q = _lattice(n_part, torch.float64) * pm + 0.5
+    a = _nodes(nodes)
+    om = COSMO["omega_m"]
+    lpt = 0.0 if frame == "pm" else 1.0
+
+    def kick(j, lo, hi):
+        d1, d2 = _growth(float(a[j]))[:2]
+        k = 1.5 * om * _integral(lambda t: 1.0 / (t ** 2 * _hubble(t)), lo, hi)
+        return p + k * (g - lpt * d1 * psi1 - lpt * (d2 - d1 * d1) * psi2)
+    g = _acceleration64(q + x * (ng / box), ng, box)
+    for j in range(j0, j1):
+        mid = 0.5 * (a[j] + a[j + 1])
+        p = kick(j, a[j], mid)
+        (d1, d2), (e1, e2) = _growth(float(a[j]))[:2], _growth(float(a[j + 1]))[:2]
+        x = x + p * _integral(lambda t: 1.0 / (t ** 3 * _hubble(t)), a[j], a[j + 1])
+        x = x + lpt * (e1 - d1) * psi1 + lpt * (e2 - d2) * psi2
+        g = _acceleration64(q + x * (ng / box), ng, box)
+        p = kick(j + 1, mid, a[j + 1])
+    return x, p
+
+
+def _linear_power(k):
+    """P(k) at z = 0: n_s and the BBKS transfer with Sugiyama's shape, normalised to sigma_8."""
+    c = COSMO
+    gamma = c["omega_m"] * c["h"] * math.exp(-c["omega_b"] * (1.0 + math.sqrt(2.0 * c["h"]) / c["omega_m"]))
+
+    def shape(k, xp):
+        q = k / gamma
+        poly = 1.0 + 3.89 * q + (16.1 * q) ** 2 + (5.46 * q) ** 3 + (6.71 * q) ** 4
+        return k ** c["n_s"] * (xp.log1p(2.34 * q) / (2.34 * q)) ** 2 * poly ** -0.5
+
+    def integrand(y):
+        x = 8.0 * np.exp(y)
+        top = np.where(x < 0.05, 1.0 - x ** 2 / 10.0 + x ** 4 / 280.0, 3.0 * (np.sin(x) - x * np.cos(x)) / x ** 3)
+        return np.exp(3.0 * y) * shape(np.exp(y), np) * top ** 2 / (2.0 * math.pi ** 2)
+    edges = np.concatenate([np.linspace(math.log(1e-7), math.log(0.125), 24), np.log(np.arange(1.0, 1200.0, 3.0) / 8.0)[1:]])
+    var = sum(_integral(integrand, lo, hi) for lo, hi in zip(edges[:-1], edges[1:]))
+    return c["sigma_8"] ** 2 / var * shape(k, torch)
+
+
+def _ic64(n, box, seed):
+    """psi1, psi2 (3, n^3): second-order initial displacements of the seed's white noise."""
+    raw = np.random.Philox(key=np.array([seed, 0], dtype=np.uint64),
+                           counter=np.full(4, 2 ** 64 - 1, dtype=np.uint64)).random_raw(4 * n ** 3).reshape(-1, 4)
+    u1 = ((raw[:, 0] >> np.uint64(40)) + np.uint64(1)).astype(np.float64) * 2.0 ** -24
+    u2 = (raw[:, 1] >> np.uint64(40)).astype(np.float64) * 2.0 ** -24
+    noise = np.sqrt(-2.0 * np.log(u1)) * np.cos(2.0 * math.pi * u2)
+    w = torch.from_numpy(noise).cuda().reshape(n, n, n)
+    m, odd, k2 = _unit_modes(n)
+    kf = 2.0 * math.pi / box
+    dk = torch.fft.rfftn(w) * torch.sqrt(_linear_power(kf * k2.sqrt()) * (n ** 3 / box ** 3))
+    dk[0, 0, 0] = 0.0
+
+    def back(f):
+        return torch.fft.irfftn(f, s=(n, n, n))
+    diag = [back(dk * (v * v / k2)) for v in m]
+    src = diag[0] * diag[1] + diag[0] * diag[2] + diag[1] * diag[2]
+    for i, j in ((0, 1), (0, 2), (1, 2)):
+        src = src - back(dk * (odd[i] * odd[j] / k2)) ** 2
+    sk = torch.fft.rfftn(src)
+    psi1 = torch.stack([back(dk * (1j * v / (k2 * kf))).reshape(-1) for v in odd])
+    psi2 = torch.stack([back(sk * (-1j * v / (k2 * kf))).reshape(-1) for v in odd])
+    return psi1, psi2
+
+
+def _run64(n, pm, box, nodes, seed):
+    psi1, psi2 = _ic64(n, box, seed)
+    d1, d2 = _growth(1.0 / (1.0 + Z_INIT))[:2]
+    x, p = _steps64(n, pm, box, "cola", nodes, 0, nodes - 1, d1 * psi1 + d2 * psi2, torch.zeros_like(psi1), psi1, psi2)
+    return dict(x=x, p=p, psi1=psi1, psi2=psi2)
+
+
+def _spectra64(case, seed):
+    n, n_pk = case["n_part"], case["n_pk"]
+    box = CELL * n
+    a, d1, d2 = _node(LATE)
+    x, p, psi1, psi2 = (v.double() for v in _state_arrays(n, box, d1, d2, seed))
+    _, _, v1, v2 = _growth(a)
+    e = float(_hubble(a))
+    moved = x.clone()
+    moved[2] += p[2] / (a * a * e) + a * (v1 * psi1[2] + v2 * psi2[2])
+    q = (_lattice(n, torch.float64) + 0.5) * (n_pk / n)
+    # the lattice sits half a cell of the force mesh (one cell per particle here) off the nodes
+    m, _, _ = _unit_modes(n_pk)
+    m2 = (m[0] ** 2 + m[1] ** 2 + m[2] ** 2).reshape(-1)
+    bins = torch.floor(torch.sqrt(m2)).long()
+    bins -= (bins * bins > m2).long()
+    bins += ((bins + 1) ** 2 <= m2).long()
+    n_bins = n_pk // 2
+    weight = torch.full((1, 1, n_pk // 2 + 1), 2.0, device="cuda", dtype=torch.float64)
+    weight[..., 0] = weight[..., -1] = 1.0
+    weight = weight.expand(n_pk, n_pk, n_pk // 2 + 1).reshape(-1)
+    use = (bins < n_bins) & (m2 > 0)
+    win = ((torch.sinc(m[0] / n_pk) * torch.sinc(m[1] / n_pk)) * torch.sinc(m[2] / n_pk)).reshape(-1) ** 4
+    mu2 = (m[2] ** 2).expand(n_pk, n_pk, n_pk // 2 + 1).reshape(-1) / torch.clamp(m2, min=1.0)
+
+    def total(v):
+        return torch.bincount(bins[use], weights=(weight * v)[use], minlength=n_bins)[:n_bins]
+    count = total(torch.ones_like(m2))
+    safe = torch.clamp(count, min=1.0)
+    k_mean = total(m2.sqrt()) * (2.0 * math.pi / box) / safe
+    norm = box ** 3 / float(n_pk) ** 6
+
+    def powers(disp, ells):
+        pw = torch.fft.rfftn(_density64(q + disp * (n_pk / box), n_pk)).abs().square().reshape(-1) / win
+        leg = {0: torch.ones_like(mu2), 2: 1.5 * mu2 - 0.5, 4: (35.0 * mu2 ** 2 - 30.0 * mu2 + 3.0) / 8.0}
+        return [((2 * l + 1) * total(pw * leg[l]) / safe * norm)[None] for l in ells]
+    real = powers(x, (0,))
+    red = powers(moved, (0, 2, 4))
+    return [k_mean[None], real[0], count[None], k_mean[None]] + red + [count[None]]
+
+
+def _train64(case, seed):
+    params, in_scale, out_scale, box, pos, delta, force, acc, target = _net_inputs(case, seed)
+    n, c = case["n"], case["channels"]
+    flat = params.double().requires_grad_(True)
+    w1, b1, w2, b2, w3, b3 = torch.split(flat, [108 * c, c, 27 * c * c, c, 3 * c, 3])
+    x0 = torch.stack([delta.double()] + [f.double() for f in force], dim=-1) * torch.tensor(in_scale, device="cuda",
+                                                                                            dtype=torch.float64)
+
+    def conv(a, w, b):
+        out = b.expand(n, n, n, c)
+        for t in range(27):
+            d = (t // 9 - 1, t // 3 % 3 - 1, t % 3 - 1)
+            out = out + torch.roll(a, (-d[0], -d[1], -d[2]), (0, 1, 2)) @ w[:, :, t].T
+        return out
+    h = torch.nn.functional.silu(conv(x0, w1.reshape(c, 4, 27), b1))
+    h = torch.nn.functional.silu(conv(h, w2.reshape(c, c, 27), b2))
+    df = ((h @ w3.reshape(3, c).T + b3) * out_scale).permute(3, 0, 1, 2)
+    res = acc.double() - target.double()
+    denom = res.square().sum()
+    field = df.detach().reshape(3, -1).requires_grad_(True)
+    got = 0.0
+    for i, w in _corners(pos.double() * (n / box), n):
+        got = got + w * field[:, i]
+    loss = (res + got).square().sum() / denom
+    d_df, = torch.autograd.grad(loss, field)
+    grads, = torch.autograd.grad(df, flat, d_df.reshape(3, n, n, n))
+    return dict(df=df.detach().contiguous(), stats=torch.stack([loss.detach(), denom]), d_df=d_df.reshape(3, n, n, n),
+                grads=grads)
+
+
+def exact(case, seed):
+    kind = case["kind"]
+    if kind == "run":
+        return _run64(case["n_part"], case["pm"], case["box"], case["nodes"], int(seed))
+    if kind == "step":
+        n = case["n_part"]
+        _, d1, d2 = _node(LATE)
+        arrays = [v.double() for v in _state_arrays(n, CELL * n, d1, d2, seed)]
+        x, p = _steps64(n, case["pm"], CELL * n, case["frame"], NODES, LATE, LATE + 3, *arrays)
+        return dict(x=x, p=p)
+    if kind == "ensemble":
+        out = []
+        for k, n in enumerate((case["n_a"], case["n_b"])):
+            got = [_run64(n, 3, 3.125 * n, case["nodes"], int(seed) * 64 + 16 * k + r) for r in range(case["members"])]
+            out.append({v: torch.cat([g[v] for g in got], dim=1) for v in ("x", "p")})
+        return out
+    if kind == "train":
+        return _train64(case, seed)
+    if kind == "spectra":
+        return _spectra64(case, seed)
+    if kind == "fields":
+        n = case["n_part"]
+        box = CELL * n
+        pos = _late_positions(n, box, seed).double()
+        c, f = case["coarse"], case["fine"]
+        u = pos * (c / box)
+        delta = _density64(u, c)
+        return dict(delta=delta, g=torch.stack(list(_force64(delta, box))).reshape(3, c, c, c),
+                    acc=_acceleration64(u, c, box, delta), fine=_acceleration64(pos * (f / box), f, box))
+    if kind == "fft":
+        x = torch.randn((case["n"],) * 3, generator=_gen(seed), device="cuda").double()
+        return dict(xk=torch.fft.rfftn(x), x=x * float(case["n"]) ** 3)
+    if kind == "density":
+        return _density64(_points(case, 500.0, seed).double() * (case["mesh"] / 500.0), case["mesh"])
+    # haloes: whole numbers, and sums over the members they name; the corrected step: a network in
+    # 16 bits inside a whole call
+    return None
