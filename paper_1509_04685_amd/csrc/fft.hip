@@ -228,6 +228,9 @@ static size_t shape_lds(FftKind k, int n, const FftShape& sh) {
     return (size_t)sh.width * L * (sh.split ? sizeof(float) : sizeof(float2));
 }
 
+// Blocks of a z pass: W lines each, a plane's last block with the lines that are left.
+static long z_blocks(int n, int W) { return (long)n * ((n + W - 1) / W); }
+
 static int log2_exact(int w) {  // log2 of a power of two, -1 otherwise
     int l = 0;
     while ((1 << l) < w) ++l;
@@ -239,7 +242,7 @@ static bool shape_ok(FftKind k, int n, const FftShape& sh) {
     if (!plan_ok(L, sh.R) || sh.width < 1) return false;
     if (sh.split && (!sh.stat || !is_cols(k))) return false;
     // z passes: a power-of-two number of lines of one x plane per block
-    if (is_z(k) && (log2_exact(sh.width) < 0 || n % sh.width)) return false;
+    if (is_z(k) && log2_exact(sh.width) < 0) return false;
     long threads = shape_threads(k, n, sh);
     // 1024-thread blocks only for the kernels compiled for them: the static x-column plans with
     // split exchanges and z_c2r3
@@ -257,8 +260,8 @@ static FftShape default_shape(FftKind k, int n) {
         sh.width = std::max(1, 256 / pl.T);
         while ((long)sh.width * pl.T > 512) sh.width /= 2;
         if (is_z(k)) {
-            int w = 1;  // the largest power of two <= width that divides n
-            while (w * 2 <= sh.width && n % (w * 2) == 0) w *= 2;
+            int w = 1;  // the largest power of two <= width that divides n, up to 16 also one that does not
+            while (w * 2 <= sh.width && (n % (w * 2) == 0 || w < 16)) w *= 2;
             sh.width = w;
             while (sh.width > 1 && !shape_ok(k, n, sh)) sh.width /= 2;  // z_c2r3: three groups
         }
@@ -298,6 +301,7 @@ int set_fft_shape(int n, const char* kind, int R, int width, int stat) {
     if (stat < 0 || stat > 2) return COLA_ERR_INVALID_ARG;
     const FftShape sh{R, width, stat != 0, stat == 2};
     if (!shape_ok((FftKind)k, n, sh)) return COLA_ERR_INVALID_ARG;
+    if (is_z((FftKind)k) && n % width) return COLA_ERR_INVALID_ARG;  // a pinned z shape has no ragged block
     if (sh.stat && !static_available((FftKind)k, n, R, width, sh.split)) return COLA_ERR_INVALID_ARG;
     ShapeCache& c = shape_cache();
     std::lock_guard<std::mutex> g(c.mu);
@@ -411,7 +415,7 @@ static hipError_t run_z_r2c_shape(const float* in, long in_row, long in_bstride,
     L.op = OP_Z_R2C;
     const int lpb = sh.width;
     L.lds = shape_lds(FK_Z_R2C, g.n, sh);
-    L.grid = dim3((unsigned)((long)g.n * g.n / lpb), n_real);
+    L.grid = dim3((unsigned)z_blocks(g.n, lpb), n_real);
     L.block = dim3(lpb * (g.m / sh.R));
     L.st = st;
     L.rin = in;
@@ -442,7 +446,7 @@ static hipError_t run_z_c2r_shape(const float2* in, long in_bstride, float* out,
     L.op = OP_Z_C2R;
     const int lpb = sh.width;
     L.lds = shape_lds(FK_Z_C2R, g.n, sh);
-    L.grid = dim3((unsigned)((long)g.n * g.n / lpb), n_real);
+    L.grid = dim3((unsigned)z_blocks(g.n, lpb), n_real);
     L.block = dim3(lpb * (g.m / sh.R));
     L.st = st;
     L.cin = in;
@@ -466,18 +470,17 @@ static hipError_t run_z_c2r(const float2* in, long in_bstride, float* out, long 
                            st);
 }
 
-// The three force components into one interleaved mesh (k_fft_z_c2r3); `lines` rows (x, y) from
-// the first (all n^2 of them in the step; fewer when the autotuner times it on a scratch buffer).
+// The three force components into one interleaved mesh (k_fft_z_c2r3); the first `planes` x planes
+// (all n of them in the step; fewer when the autotuner times it on a scratch buffer).
 static hipError_t run_z_c2r3_shape(const float2* fx, const float2* fy, const float2* fz, long in_bstride, float* out,
                                    long out_row, long out_bstride, const Mesh3& g, const float2* tw, int n_real,
-                                   float kf, const FftShape& sh, hipStream_t st, long lines = -1) {
+                                   float kf, const FftShape& sh, hipStream_t st, int planes = -1) {
     if (out_row < 3L * (g.n + 2)) return hipErrorInvalidValue;
     FftLaunch L;
     L.op = OP_Z_C2R3;
     const int lpb = sh.width;
-    if (lines < 0) lines = (long)g.n * g.n;
     L.lds = shape_lds(FK_Z_C2R3, g.n, sh);
-    L.grid = dim3((unsigned)(lines / lpb), n_real);
+    L.grid = dim3((unsigned)(z_blocks(g.n, lpb) / g.n * (planes < 0 ? g.n : planes)), n_real);
     L.block = dim3((unsigned)shape_threads(FK_Z_C2R3, g.n, sh));
     L.st = st;
     L.cin = fx;
@@ -605,16 +608,15 @@ hipError_t autotune_fft(int n, float2* S, float2* A, float2* B, const float2* tw
     for (int k = 0; k < FK_NUM && status == hipSuccess; ++k) {
         FftKind kind = (FftKind)k;
         int L = line_len(kind, n);
-        // z_c2r3 is timed on as many rows as its interleaved output fits in one scratch buffer
-        auto z3_rows = [&](int w) {
-            return std::min((long)n * n, 2L * g.total_c() / force_row3(n)) / w * w;
-        };
+        // z_c2r3 is timed on as many x planes as its interleaved output fits in one scratch buffer
+        const int z3_planes = (int)std::min((long)n, 2L * g.total_c() / (force_row3(n) * n));
         std::vector<FftShape> cands;
         for (int R : valid_rs(L))
             for (int w : {1, 2, 4, 8, 16, 32, 64}) {
                 const long threads = (long)w * (L / R);
                 if (threads < 64 && w < 64) continue;
-                if (kind == FK_Z_C2R3 && z3_rows(w) < w) continue;
+                if (is_z(kind) && n % w && w > 16) continue;
+                if (kind == FK_Z_C2R3 && z3_planes < 1) continue;
                 const FftShape sp{R, w, true, true};
                 if (shape_ok(kind, n, sp) && static_available(kind, n, R, w, true)) cands.push_back(sp);
                 FftShape sh{R, w, false};
@@ -637,7 +639,7 @@ hipError_t autotune_fft(int n, float2* S, float2* A, float2* B, const float2* tw
                 case FK_X_MULT: return run_x_mult_shape(S, 0, A, 0, g, tw, 1, MUL_IK, 0, 0, kf, 1.0f, sh, st);
                 case FK_Z_C2R3:
                     return run_z_c2r3_shape(S, S, S, 0, reinterpret_cast<float*>(A), force_row3(n), 0, g, tw, 1, kf,
-                                            sh, st, z3_rows(sh.width));
+                                            sh, st, z3_planes);
                 default: return hipErrorInvalidValue;
             }
         };

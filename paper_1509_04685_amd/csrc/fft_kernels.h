@@ -132,10 +132,27 @@ __device__ __forceinline__ void store_col(float2* p, float2 v) {
 // does at W = 8 and 16 (4 instead of 8, 2 instead of 4).
 __device__ __forceinline__ constexpr int z_line_stride(int M) { return M + 2; }
 
+// The lines of block b: `count` lines from (x, y0).  A plane's last block holds the n mod W lines that
+// are left; its other line slots repeat the last line and store nothing.  With W a power of two that
+// divides n, as these passes had it, a side of 4 3^b moved 32-byte chunks per kz plane and block and
+// one of 2 3^b 16-byte chunks (486^3: 1392 us for the r2c pass; 324^3 r2c and c2r calls together
+// 1204 -> 1092 us with W = 8).
+struct ZBlock {
+    int x, y0, count;
+};
+__device__ __forceinline__ ZBlock z_block(int b, int n, int lw) {
+    const int tiles = (n + (1 << lw) - 1) >> lw;
+    ZBlock z;
+    z.x = b / tiles;
+    z.y0 = (b - z.x * tiles) << lw;
+    z.count = min(1 << lw, n - z.y0);
+    return z;
+}
+
 // Rows of n = 2M reals; output M+1 complex per row.  Z = FFT_M(x_even + i x_odd);
 // X_k = (Z_k + conj Z_{M-k})/2 - i W_n^k (Z_k - conj Z_{M-k})/2, k = 0..M.
-// Block: W = 2^lw lines (x, y0 .. y0 + W - 1) of one x plane (W divides n); output X_k of line j
-// at out[k plane + x n + y0 + j].
+// Block: W = 2^lw lines (x, y0 .. y0 + W - 1) of one x plane, fewer in the plane's last block where W
+// does not divide n (z_block); output X_k of line j at out[k plane + x n + y0 + j].
 template <class LE>
 __global__ void __launch_bounds__(512) k_fft_z_r2c(const float* in, long in_row, long in_bstride, float2* out,
                                                    long out_bstride, int n, long plane, int lw, LE eng,
@@ -146,15 +163,15 @@ __global__ void __launch_bounds__(512) k_fft_z_r2c(const float* in, long in_row,
     const int T = eng.T(), M = eng.n();
     const int W = 1 << lw;
     const int line = threadIdx.x / T, t = threadIdx.x % T;
-    const long first = (long)blockIdx.x * W;  // line index x n + y of the block's first line
-    const int x = (int)(first / n), y0 = (int)(first - (long)x * n);
+    const ZBlock zb = z_block(blockIdx.x, n, lw);
+    const long first = (long)zb.x * n + zb.y0;  // line index x n + y of the block's first line
     in += (long)blockIdx.y * in_bstride;
     out += (long)blockIdx.y * out_bstride;
     float2* const Lb = lds + TW;
     const int LS = z_line_stride(M);
     float2* L = Lb + line * LS;
     float2 v[R];
-    const float2* src = reinterpret_cast<const float2*>(in + (first + line) * in_row);
+    const float2* src = reinterpret_cast<const float2*>(in + (first + min(line, zb.count - 1)) * in_row);
     eng.first(t, [&](int q, int e) {
         float2 z = load_stream(src + e);
         v[q] = make_float2(fmaf(z.x, pa, pb), fmaf(z.y, pa, pb));
@@ -165,14 +182,15 @@ __global__ void __launch_bounds__(512) k_fft_z_r2c(const float* in, long in_row,
     eng.last(t, [&](int q, int e) { L[e] = v[q]; });
     __syncthreads();
     // split and transposed store: consecutive threads take consecutive lines of one k, so every
-    // kz plane receives W contiguous values; R outputs per thread plus the k = M column
-    float2* dst = out + (long)x * n + y0;
-    const int bd = blockDim.x;
+    // kz plane receives W contiguous values; R outputs per thread (line j, k = k0 + u T) plus the
+    // k = M column
+    float2* dst = out + first;
+    const int j = threadIdx.x & (W - 1), k0 = threadIdx.x >> lw;
+    if (j >= zb.count) return;
+    const float2* Lj = Lb + j * LS;
 #pragma unroll
     for (int u = 0; u < R; ++u) {
-        const int o = threadIdx.x + u * bd;
-        const int k = o >> lw, j = o & (W - 1);
-        const float2* Lj = Lb + j * LS;
+        const int k = k0 + u * T;
         const float2 zk = Lj[k];
         const float2 zc = cconj(Lj[k == 0 ? 0 : M - k]);
         const float2 e = cscale(cadd(zk, zc), 0.5f);
@@ -202,8 +220,8 @@ __global__ void __launch_bounds__(512) k_fft_z_c2r(const float2* in, long in_bst
     const int T = eng.T(), M = eng.n();
     const int W = 1 << lw;
     const int line = threadIdx.x / T, t = threadIdx.x % T;
-    const long first = (long)blockIdx.x * W;
-    const int x = (int)(first / n), y0 = (int)(first - (long)x * n);
+    const ZBlock zb = z_block(blockIdx.x, n, lw);
+    const long first = (long)zb.x * n + zb.y0;
     in += (long)blockIdx.y * in_bstride;
     out += (long)blockIdx.y * out_bstride;
     float2* const Lb = lds + TW;
@@ -211,23 +229,16 @@ __global__ void __launch_bounds__(512) k_fft_z_c2r(const float2* in, long in_bst
     const float2* twl = stage_twiddles<TW>(tw, lds);  // visible after the barrier below
     {
         // every load of this thread is issued before the first LDS store
-        const float2* src = in + (long)x * n + y0;
-        const int bd = blockDim.x;
+        const int j = threadIdx.x & (W - 1), k0 = threadIdx.x >> lw;  // this thread: line j, k = k0 + u T
+        const float2* src = in + first + min(j, zb.count - 1);
         float2 xv[R];
 #pragma unroll
-        for (int u = 0; u < R; ++u) {
-            const int o = threadIdx.x + u * bd;
-            xv[u] = load_stream(src + (long)(o >> lw) * plane + (o & (W - 1)));
-        }
-        const float2 xm = threadIdx.x < W ? load_stream(src + (long)M * plane + threadIdx.x) : make_float2(0.f, 0.f);
+        for (int u = 0; u < R; ++u) xv[u] = load_stream(src + (long)(k0 + u * T) * plane);
+        const float2 xm = threadIdx.x < W ? load_stream(src + (long)M * plane) : make_float2(0.f, 0.f);
 #pragma unroll
-        for (int u = 0; u < R; ++u) {
-            const int o = threadIdx.x + u * bd;
-            const int k = o >> lw, j = o & (W - 1);
-            Lb[j * LS + k] = cscale(xv[u], scale);
-        }
+        for (int u = 0; u < R; ++u) Lb[j * LS + k0 + u * T] = cscale(xv[u], scale);
         if (threadIdx.x < W)  // kz Nyquist plane
-            Lb[threadIdx.x * LS + M] = cscale(xm, scale);
+            Lb[j * LS + M] = cscale(xm, scale);
     }
     __syncthreads();
     float2* L = Lb + line * LS;
@@ -240,6 +251,7 @@ __global__ void __launch_bounds__(512) k_fft_z_c2r(const float2* in, long in_bst
     });
     __syncthreads();
     eng.template run<true>(v, L, t, twl, true);
+    if (line >= zb.count) return;
     float2* dst = reinterpret_cast<float2*>(out + (first + line) * out_row);
     eng.last(t, [&](int q, int e) {
         store_stream(dst + e, v[q]);
@@ -271,27 +283,25 @@ __global__ void __launch_bounds__(1024) k_fft_z_c2r3(const float2* in0, const fl
     const int line = lt / T, t = lt % T;
     // blocks of neighbouring lines meet in one XCD's L2: with W < 16 they share the 128-byte lines
     // of every kz plane
-    const long first = (long)xcd_block() * W;
-    const int x = (int)(first / n), y0 = (int)(first - (long)x * n);
+    const ZBlock zb = z_block(xcd_block(), n, lw);
+    const long first = (long)zb.x * n + zb.y0;
     float2* const Lb = lds + TW;
     const int LS = z_line_stride(M);  // this group's lines
     float2* const Lg = Lb + (long)comp * W * LS;
     const float2* twl = stage_twiddles<TW>(tw, lds);  // visible after the barrier below
     {
-        const float2* src = (comp == 0 ? in0 : (comp == 1 ? in1 : in2)) + (long)blockIdx.y * in_bstride +
-                            (long)x * n + y0;
+        const int j = lt & (W - 1), k0 = lt >> lw;  // this thread: line j, k = k0 + u T
+        const float2* src = (comp == 0 ? in0 : (comp == 1 ? in1 : in2)) + (long)blockIdx.y * in_bstride + first +
+                            min(j, zb.count - 1);
         const uint32_t pl = (uint32_t)plane;
         float2 xv[R];
 #pragma unroll
-        for (int u = 0; u < R; ++u) {  // k plane + j < (n/2 + 1) plane < 2^31
-            const uint32_t o = lt + u * gs;
-            xv[u] = load_stream(src + ((o >> lw) * pl + (o & (W - 1))));
-        }
-        const float2 xm = lt < W ? load_stream(src + (long)M * plane + lt) : make_float2(0.f, 0.f);
+        for (int u = 0; u < R; ++u)  // k plane < (n/2 + 1) plane < 2^31
+            xv[u] = load_stream(src + (uint32_t)(k0 + u * T) * pl);
+        const float2 xm = lt < W ? load_stream(src + (long)M * plane) : make_float2(0.f, 0.f);
 #pragma unroll
         for (int u = 0; u < R; ++u) {
-            const int o = lt + u * gs;
-            const int k = o >> lw, j = o & (W - 1);
+            const int k = k0 + u * T;
             float2 y = xv[u];
             if (comp == 2) {
                 const float kz = kf * (float)k;
@@ -300,7 +310,7 @@ __global__ void __launch_bounds__(1024) k_fft_z_c2r3(const float2* in0, const fl
             Lg[j * LS + k] = cscale(y, scale);
         }
         if (lt < W)  // kz Nyquist plane (0 for the i k_z component)
-            Lg[lt * LS + M] = comp == 2 ? make_float2(0.0f, 0.0f) : cscale(xm, scale);
+            Lg[j * LS + M] = comp == 2 ? make_float2(0.0f, 0.0f) : cscale(xm, scale);
     }
     __syncthreads();
     float2* L = Lg + line * LS;
@@ -328,7 +338,7 @@ __global__ void __launch_bounds__(1024) k_fft_z_c2r3(const float2* in0, const fl
     __syncthreads();
     float* dst = out + (long)blockIdx.y * out_bstride + first * out_row;
     const int half = rs / 2;  // float2 per staged row (rs is even)
-    for (int j = 0; j < W; ++j)
+    for (int j = 0; j < zb.count; ++j)
         for (int h = threadIdx.x; h < half; h += blockDim.x)
             store_stream(reinterpret_cast<float2*>(dst + j * out_row) + h, reinterpret_cast<const float2*>(S + j * rs)[h]);
 }
