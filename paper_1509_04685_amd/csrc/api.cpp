@@ -655,7 +655,7 @@ int power_spectrum_impl(const cola_problem* prob, const cola_cosmology* cosmo, c
     COLA_TRY(sorted_deposit(P, npr, p.n_real, dg, !on_node, fg, w.F, kd, L.tk, sb, reinterpret_cast<float*>(w.K),
                             (float)(cells / (double)npr), -1.0f, st));
     COLA_TRY(fft3d_r2c(reinterpret_cast<const float*>(w.K), 2L * gk.nzp, 2L * L.kstride, w.K2, L.kstride, gk, w.twk,
-                       p.n_real, 1.0f, 0.0f, st));
+                       p.n_real, 1.0f, 0.0f, st, true));
     const long nb = (long)n_bins * p.n_real;
     COLA_TRY(launch_fill_d(k_mean, nb, 0.0, st));
     COLA_TRY(launch_fill_d(pk, nb, 0.0, st));
@@ -743,7 +743,7 @@ int cola_power_multipoles(const cola_problem* prob, const cola_cosmology* cosmo,
     COLA_TRY(sorted_deposit(P, npr, p.n_real, dg, redshift_space != 0, fg, w.F, kd, L.tk, sb,
                             reinterpret_cast<float*>(w.K), (float)(cells / (double)npr), -1.0f, st));
     COLA_TRY(fft3d_r2c(reinterpret_cast<const float*>(w.K), 2L * gk.nzp, 2L * L.kstride, w.K2, L.kstride, gk, w.twk,
-                       p.n_real, 1.0f, 0.0f, st));
+                       p.n_real, 1.0f, 0.0f, st, true));
     const long nb = (long)n_bins * p.n_real;
     for (double* o : {k_mean, p0, p2, p4, n_modes}) COLA_TRY(launch_fill_d(o, nb, 0.0, st));
     COLA_TRY(pk_bin_multipoles(w.K2, L.kstride, gk, p.n_real, n_bins, los, k_mean, p0, p2, p4, n_modes,

@@ -104,9 +104,11 @@ hipError_t launch_twiddles(float2* tw, int len, hipStream_t st);
 
 // Forward 3D r2c: real rows at `in` (in_row floats apart, batch stride in_bstride floats) with
 // y = pa * x + pb applied on load -> transposed half spectrum `out` (batch stride out_bstride
-// float2), out of place (the z pass transposes).  z, then y, then x.
+// float2), out of place (the z pass transposes).  z, then y, then x.  same_digits: on the plan whose
+// rounding the spectra of earlier runs carry, where none was tuned.
 hipError_t fft3d_r2c(const float* in, long in_row, long in_bstride, float2* out, long out_bstride,
-                     const Mesh3& g, const float2* tw, int n_real, float pa, float pb, hipStream_t st);
+                     const Mesh3& g, const float2* tw, int n_real, float pa, float pb, hipStream_t st,
+                     bool same_digits = false);
 
 // Radial transfer of the Green's function (the learned form's filter): T(u) the cubic Hermite
 // interpolant of the n knots (u[j], t[j]) with slopes m[j] (green_slopes), u = |m| / (N/2) for the
@@ -152,7 +154,7 @@ hipError_t pm_force_interleaved(float2* P, float2* Q, float2* R, float* F, long 
 // z r2c + y forward only (first half of the PM force transform), out of place
 hipError_t fft_zy_forward(const float* in, long in_row, long in_bstride, float2* out, long out_bstride,
                           const Mesh3& g, const float2* tw, int n_real, float pa, float pb,
-                          hipStream_t st);
+                          hipStream_t st, bool same_digits = false);
 
 // Multiplier types for the inverse transforms of the initial conditions.
 enum MulType { MUL_SCALE = 0, MUL_IK = 1, MUL_KK = 2 };

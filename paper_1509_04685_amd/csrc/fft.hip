@@ -163,7 +163,7 @@ FftPlan make_plan_r(int n, int R, bool reverse) {
 
 static std::vector<int> valid_rs(int n) {
     std::vector<int> out;
-    for (int R : {2, 3, 4, 6, 8, 12, 16, 24})
+    for (int R : {2, 3, 4, 6, 8, 9, 12, 16, 18, 24})
         if (plan_ok(n, R)) out.push_back(R);
     return out;
 }
@@ -196,9 +196,17 @@ static hipError_t launch_static(const FftLaunch& L, int n) {
         case 384: return fft_static_384(L);
         case 288: return fft_static_288(L);
         case 256: return fft_static_256(L);
-        default: return hipErrorNotSupported;
+        default: break;
     }
+    for (auto f : {fft_static_sides_0, fft_static_sides_1, fft_static_sides_2, fft_static_sides_3}) {
+        const hipError_t e = f(L, n);
+        if (e != hipErrorNotSupported) return e;
+    }
+    return hipErrorNotSupported;
 }
+
+// Sides with several compile-time shapes per pass, which can be pinned (fft_static_<n>.hip).
+static bool static_pinnable(int n) { return n == 256 || n == 288 || n == 384 || n == 512 || n == 768 || n == 1536; }
 
 static bool is_cols(FftKind k) { return k == FK_COLS_X || k == FK_X_GREEN || k == FK_X_MULT; }
 
@@ -251,7 +259,9 @@ static bool shape_ok(FftKind k, int n, const FftShape& sh) {
     return shape_lds(k, n, sh) <= (k == FK_Z_C2R3 ? 150 : 128) * 1024;
 }
 
-static FftShape default_shape(FftKind k, int n) {
+// The run-time plan of any side, and the first compile-time plans of the pinnable ones: the values per
+// thread that a line's factors suggest.
+static FftShape plain_shape(FftKind k, int n) {
     int L = line_len(k, n);
     FftPlan pl = make_plan(L);
     FftShape sh;
@@ -268,8 +278,18 @@ static FftShape default_shape(FftKind k, int n) {
     } else {
         sh.width = pick_tk(n, pl.T);
     }
-    sh.stat = static_available(k, n, sh.R, sh.width);
+    sh.stat = static_pinnable(n) && static_available(k, n, sh.R, sh.width);
     return sh;
+}
+
+static FftShape default_shape(FftKind k, int n) {
+    const PassClass c = k == FK_Z_C2R3 ? PC_Z3 : (is_z(k) ? PC_Z : (is_rows(k) ? PC_ROWS : PC_COLS));
+    const PassShape d = default_pass(c, n);
+    if (d.R && static_available(k, n, d.R, d.width)) {
+        const FftShape sh{d.R, d.width, true};
+        if (shape_ok(k, n, sh)) return sh;
+    }
+    return plain_shape(k, n);
 }
 
 namespace {
@@ -283,12 +303,15 @@ ShapeCache& shape_cache() {
 }
 }  // namespace
 
-static FftShape shape_for(FftKind k, int n) {
+// same_digits: the transform of a power spectrum.  Its float64 sums carry the rounding of the plan (1e-8
+// between two plans of one side), and spectra are kept and compared between runs; so untuned spectra stay
+// on the plan that they always had, with the default lines per block where that plan has them.
+static FftShape shape_for(FftKind k, int n, bool same_digits = false) {
     ShapeCache& c = shape_cache();
     std::lock_guard<std::mutex> g(c.mu);
     auto it = c.tuned.find({(int)k, n});
     if (it != c.tuned.end()) return it->second;
-    return default_shape(k, n);
+    return same_digits ? plain_shape(k, n) : default_shape(k, n);
 }
 
 // Pins the shape of one pass kind at mesh size n (what the autotuner would otherwise choose).
@@ -302,7 +325,8 @@ int set_fft_shape(int n, const char* kind, int R, int width, int stat) {
     const FftShape sh{R, width, stat != 0, stat == 2};
     if (!shape_ok((FftKind)k, n, sh)) return COLA_ERR_INVALID_ARG;
     if (is_z((FftKind)k) && n % width) return COLA_ERR_INVALID_ARG;  // a pinned z shape has no ragged block
-    if (sh.stat && !static_available((FftKind)k, n, R, width, sh.split)) return COLA_ERR_INVALID_ARG;
+    if (sh.stat && (!static_pinnable(n) || !static_available((FftKind)k, n, R, width, sh.split)))
+        return COLA_ERR_INVALID_ARG;
     ShapeCache& c = shape_cache();
     std::lock_guard<std::mutex> g(c.mu);
     c.tuned[{k, n}] = sh;
@@ -387,9 +411,9 @@ static hipError_t run_rows_shape(FftOp op, float2* A, float2* S, long bstride, c
 }
 
 static hipError_t run_rows(FftOp op, float2* A, float2* S, long bstride, const Mesh3& g, const float2* tw, float kf,
-                           int n_real, hipStream_t st) {
+                           int n_real, hipStream_t st, bool same_digits = false) {
     return run_rows_shape(op, A, S, bstride, g, tw, kf, n_real,
-                          shape_for(op == OP_ROWS_SPLIT ? FK_Y_SPLIT : FK_ROWS_Y, g.n), st);
+                          shape_for(op == OP_ROWS_SPLIT ? FK_Y_SPLIT : FK_ROWS_Y, g.n, same_digits), st);
 }
 
 static hipError_t run_cols_shape(float2* data, long bstride, const Mesh3& g, const float2* tw, int n_real,
@@ -434,9 +458,10 @@ static hipError_t run_z_r2c_shape(const float* in, long in_row, long in_bstride,
 }
 
 static hipError_t run_z_r2c(const float* in, long in_row, long in_bstride, float2* out, long out_bstride,
-                            const Mesh3& g, const float2* tw, int n_real, float pa, float pb, hipStream_t st) {
+                            const Mesh3& g, const float2* tw, int n_real, float pa, float pb, hipStream_t st,
+                            bool same_digits = false) {
     return run_z_r2c_shape(in, in_row, in_bstride, out, out_bstride, g, tw, n_real, pa, pb,
-                           shape_for(FK_Z_R2C, g.n), st);
+                           shape_for(FK_Z_R2C, g.n, same_digits), st);
 }
 
 static hipError_t run_z_c2r_shape(const float2* in, long in_bstride, float* out, long out_row, long out_bstride,
@@ -548,17 +573,18 @@ static hipError_t run_x_mult_shape(const float2* spec, long spec_bstride, float2
 
 hipError_t fft_zy_forward(const float* in, long in_row, long in_bstride, float2* out, long out_bstride,
                           const Mesh3& g, const float2* tw, int n_real, float pa, float pb,
-                          hipStream_t st) {
-    hipError_t e = run_z_r2c(in, in_row, in_bstride, out, out_bstride, g, tw, n_real, pa, pb, st);
+                          hipStream_t st, bool same_digits) {
+    hipError_t e = run_z_r2c(in, in_row, in_bstride, out, out_bstride, g, tw, n_real, pa, pb, st, same_digits);
     if (e != hipSuccess) return e;
-    return run_rows(OP_ROWS_FWD, out, nullptr, out_bstride, g, tw, 0.0f, n_real, st);
+    return run_rows(OP_ROWS_FWD, out, nullptr, out_bstride, g, tw, 0.0f, n_real, st, same_digits);
 }
 
 hipError_t fft3d_r2c(const float* in, long in_row, long in_bstride, float2* out, long out_bstride,
-                     const Mesh3& g, const float2* tw, int n_real, float pa, float pb, hipStream_t st) {
-    hipError_t e = fft_zy_forward(in, in_row, in_bstride, out, out_bstride, g, tw, n_real, pa, pb, st);
+                     const Mesh3& g, const float2* tw, int n_real, float pa, float pb, hipStream_t st,
+                     bool same_digits) {
+    hipError_t e = fft_zy_forward(in, in_row, in_bstride, out, out_bstride, g, tw, n_real, pa, pb, st, same_digits);
     if (e != hipSuccess) return e;
-    return run_cols_shape(out, out_bstride, g, tw, n_real, shape_for(FK_COLS_X, g.n), st);
+    return run_cols_shape(out, out_bstride, g, tw, n_real, shape_for(FK_COLS_X, g.n, same_digits), st);
 }
 
 // x and y passes of the force: x_green (P -> P, Q), y split (P -> P: i k_y, R: plain), y inverse
@@ -621,7 +647,7 @@ hipError_t autotune_fft(int n, float2* S, float2* A, float2* B, const float2* tw
                 if (shape_ok(kind, n, sp) && static_available(kind, n, R, w, true)) cands.push_back(sp);
                 FftShape sh{R, w, false};
                 if (!shape_ok(kind, n, sh)) continue;
-                cands.push_back(sh);
+                if (R != 9 && R != 18) cands.push_back(sh);  // compile-time plans only
                 if (static_available(kind, n, R, w)) cands.push_back(FftShape{R, w, true});
             }
         if (cands.empty()) continue;

@@ -1,7 +1,7 @@
 // Register/LDS Stockham FFT engine for gfx950 (64-wide wavefronts).
 //
 // A line of n complex values (n = 2^a 3^b) is transformed by T = n / R threads, each owning
-// R values in registers.  Radix-r stages (r in {2,3,4,8}, and 6 and 12 in static plans; r | R)
+// R values in registers.  Radix-r stages (r in {2,3,4,8}, and 6, 9 and 12 in static plans; r | R)
 // follow the Stockham autosort recursion: with ns the product of the radices already applied,
 // butterfly j (0 <= j < n/r) reads elements j + i n/r (i < r), multiplies element i by W_{ns r}^{i (j mod ns)},
 // applies an r-point DFT and writes element i to (j / ns) ns r + (j mod ns) + i ns.  Thread t
@@ -122,6 +122,31 @@ __device__ __forceinline__ void dft8(float2* a) {
     a[6] = csub(e2, w2);
     a[3] = cadd(e3, w3);
     a[7] = csub(e3, w3);
+}
+
+// 9-point DFT as 3 x 3 with the twiddles W9^1, W9^2, W9^4 between.
+template <bool INV>
+__device__ __forceinline__ void dft9(float2* a) {
+    const float2 w1 = make_float2(0.76604444311897803520f, -0.64278760968653932632f);
+    const float2 w2 = make_float2(0.17364817766693034885f, -0.98480775301220805937f);
+    const float2 w4 = make_float2(-0.93969262078590838405f, -0.34202014332566873304f);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) dft3<INV>(a[i], a[i + 3], a[i + 6]);  // a[3 k + i]: k-th output of column i
+    a[4] = twiddle<INV>(a[4], w1);
+    a[7] = twiddle<INV>(a[7], w2);
+    a[5] = twiddle<INV>(a[5], w2);
+    a[8] = twiddle<INV>(a[8], w4);
+    float2 y[9];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        float2 u0 = a[3 * k], u1 = a[3 * k + 1], u2 = a[3 * k + 2];
+        dft3<INV>(u0, u1, u2);
+        y[k] = u0;
+        y[k + 3] = u1;
+        y[k + 6] = u2;
+    }
+#pragma unroll
+    for (int i = 0; i < 9; ++i) a[i] = y[i];
 }
 
 // k in [0, N1 N2) with k = k1 (mod N1) and k = k2 (mod N2) (N1, N2 coprime).
@@ -282,8 +307,8 @@ __device__ __forceinline__ void fft_line(float2 (&v)[R], const FftPlan& pl, floa
 // the host (any size), StatLine a plan fixed at compile time for one line length N, values per
 // thread R and LDS element stride LES.  With every stage's radix, product ns and LDS offset known
 // to the compiler, the static engine's index arithmetic folds into constants and LDS instruction
-// offsets; its radix order is 3s first (each merged with a 4 or a 2 into a radix-12 or -6
-// stage where R allows), then 8s, 4s, 2s; reversed for REV.
+// offsets; its radix order is 3s first (each merged with a 4 or a 2 into a radix-12 or -6 stage
+// where R allows, else two at a time into a radix-9 stage), then 8s, 4s, 2s; reversed for REV.
 
 template <int R>
 struct DynLine {
@@ -324,6 +349,9 @@ constexpr Radices static_radices(int n, int R, bool rev) {
         } else if (R % 6 == 0 && (m / 3) % 2 == 0) {
             s.r[k++] = 6;
             m /= 6;
+        } else if (R % 9 == 0 && m % 9 == 0) {
+            s.r[k++] = 9;
+            m /= 9;
         } else {
             s.r[k++] = 3;
             m /= 3;
@@ -425,6 +453,7 @@ struct StatLine {
                     if constexpr (r == 4) dft4<INV>(a[0], a[1], a[2], a[3]);
                     if constexpr (r == 6) dft_pfa3<2, INV>(a);
                     if constexpr (r == 8) dft8<INV>(a);
+                    if constexpr (r == 9) dft9<INV>(a);
                     if constexpr (r == 12) dft_pfa3<4, INV>(a);
                 }
             }

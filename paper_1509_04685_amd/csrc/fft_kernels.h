@@ -657,15 +657,17 @@ inline hipError_t go_x_mult(const FftLaunch& L, LE e) {
 
 // Static-plan launchers: x columns of line length N with R values per thread and TK columns per
 // tile, y rows of length N, z passes of line length M.
-template <int N, int R, int TK, bool SPL = false>
+template <int N, int R, int TK, bool SPL = false, bool FILT = true>
 inline hipError_t static_cols_ops(const FftLaunch& L) {
     using F = StatLine<N, R, TK, 1, false, SPL>;
     using I = StatLine<N, R, TK, 1, true, SPL>;
     if (L.probe) return hipSuccess;
+    if constexpr (!FILT)
+        if (L.op == OP_X_GREEN_FILT) return hipErrorNotSupported;
     switch (L.op) {
         case OP_COLS_FWD: return go_cols<F, TK>(L, F{});
         case OP_X_GREEN: return go_x_green<F, I, TK>(L, F{}, I{});
-        case OP_X_GREEN_FILT: return go_x_green<F, I, TK, true>(L, F{}, I{});
+        case OP_X_GREEN_FILT: return go_x_green<F, I, TK, FILT>(L, F{}, I{});
         case OP_X_MULT: return go_x_mult<F, TK>(L, F{});
         default: return hipErrorNotSupported;
     }
@@ -683,19 +685,118 @@ inline hipError_t static_rows_ops(const FftLaunch& L) {
     }
 }
 
-template <int M, int R>
-inline hipError_t static_z_ops(const FftLaunch& L) {
+template <int M, int R, FftOp OP>
+inline hipError_t static_z_op(const FftLaunch& L) {
     using E = StatLine<M, R, 1, 2, false>;
     if (L.probe) return hipSuccess;
+    if constexpr (OP == OP_Z_R2C) return go_z_r2c<E>(L, E{});
+    else if constexpr (OP == OP_Z_C2R) return go_z_c2r<E>(L, E{});
+    else return go_z_c2r3<E>(L, E{});
+}
+
+template <int M, int R>
+inline hipError_t static_z_ops(const FftLaunch& L) {
     switch (L.op) {
-        case OP_Z_R2C: return go_z_r2c<E>(L, E{});
-        case OP_Z_C2R: return go_z_c2r<E>(L, E{});
-        case OP_Z_C2R3: return go_z_c2r3<E>(L, E{});
+        case OP_Z_R2C: return static_z_op<M, R, OP_Z_R2C>(L);
+        case OP_Z_C2R: return static_z_op<M, R, OP_Z_C2R>(L);
+        case OP_Z_C2R3: return static_z_op<M, R, OP_Z_C2R3>(L);
         default: return hipErrorNotSupported;
     }
 }
 
-// Static kernels of the workload mesh sizes (fft_static_<n>.hip): hipErrorNotSupported when the
+// ------------------------------------------------------------------ default shapes
+//
+// Values per thread R and lines per block of each pass where nothing was pinned or tuned, for every
+// mesh side that has compile-time plans.  The rule follows a sweep of all plans and widths over 26 sides
+// from 16 to 768 (best of four, one realization; figures in us):
+//  * the plan with the fewest stages, i.e. LDS exchanges, and of those the one with the fewest values (more
+//    waves hide more latency): x_green 144^3 R = 12 [12,12] 9.6 against R = 6 [6,6,2,2] 12.0, 216^3 R = 6
+//    [6,6,6] 23.4 against R = 12 [12,6,3] 29.2.  R = 18 and 24 count as a stage more for their registers
+//    (x_green 768^3 R = 12 [12,4,4,4] 1268, R = 24 [12,8,8] 1404; y rows 324^3 R = 6 [6,6,3,3] 51.4, R = 18
+//    [6,6,9] 74); they serve the sides whose lines need too many threads otherwise (x_green 486^3 379).
+//  * y rows with more than one factor 3 take R = 6 also for one stage more (432^3 110 against 128).
+//  * z passes and y rows with fewer than 2^18 threads at that R, which leave the chip partly idle, take the
+//    smallest R: 144^3 z r2c R = 6 7.4 against R = 12 8.8, c2r 8.8 against 12.5.
+//  * z passes: 16 lines, so that a block moves whole 128-byte lines of each kz plane (768^3 z r2c 689,
+//    with 8 lines 987).  The fused z c2r3 pass, which holds three lines for each of those, takes 16 while
+//    its block fits twice in a CU (80 KB; 384^3 89 against 98), and 8 beyond (768^3, two thirds of the planes
+//    timed: 16 lines, 148 KB and one block per CU, 1089 against 705) and on small meshes (108^3 6.9
+//    against 8.2).  Of two plans of as many stages it takes R = 12 (432^3 138 against 155 with R = 6).
+//  * x columns: tiles of 8 (64-byte rows; the two tiles of a 128-byte line meet on one XCD).  From 384 on,
+//    sides that 128 divides take 16 while two such blocks fit a CU: row strides of a power of two fold on
+//    few memory channels, and whole lines halve the requests (384^3 x_green 146 against 179, 512^3 303
+//    against 409).  Not below, where the mesh sits in the cache (256^3 29.8 against 42.6), nor where rows
+//    straddle lines (486^3 708 against 379).
+//  * y rows: blocks of up to 256 threads, 512 from 576 on with R >= 12 (768^3 585 against 615), 128 on small
+//    meshes (96^3 3.8 against 4.3).
+//  * never less than a wave per block.
+// The run-time plans that most of these sides had before took, for x_green, 23.6 against 7.1 (96^3) and
+// 909 against 245 (432^3); for z c2r3 at 324^3 125 against 80.
+
+enum PassClass { PC_Z = 0, PC_Z3, PC_ROWS, PC_COLS };
+
+struct PassShape {
+    int R, width;
+};
+
+constexpr int plan_stages(int N, int R) { return static_plan_ok(N, R) ? static_radices(N, R, false).nst : 99; }
+
+constexpr PassShape default_pass(PassClass c, int n) {
+    const bool z = c == PC_Z || c == PC_Z3;
+    const int N = z ? n / 2 : n;
+    const int cand[10] = {3, 4, 6, 8, 9, 12, 16, 18, 24, 0};
+    // threads per line's T: 16 lines (z), three times 8 (z c2r3), 8 columns, 1 row
+    const int unit = c == PC_Z ? 16 : (c == PC_Z3 ? 24 : (c == PC_COLS ? 8 : 1));
+    const int limit = c == PC_Z3 ? 1024 : 512;
+    const long lines = z ? (long)n * n : (long)(n / 2 + 1) * n;
+    int R = 0, least = 0, score = 99;
+    for (int i = 0; cand[i]; ++i) {
+        const int r = cand[i];
+        if (r < (N % 3 ? 4 : (N % 2 ? 3 : 6)) || !static_plan_ok(N, r) || (long)unit * (N / r) > limit) continue;
+        if (!least) least = r;
+        const int sc = plan_stages(N, r) + (r >= 18 ? 1 : 0);
+        if (sc < score || (sc == score && c == PC_Z3 && r == 12)) {
+            R = r;
+            score = sc;
+        }
+    }
+    if (!R) return {0, 0};
+    const bool idle = lines * (N / R) < (1L << 18);
+    if (c == PC_ROWS && N % 9 == 0 && plan_stages(N, 6) <= score + 1) R = 6;
+    if (c != PC_COLS && idle) R = least;
+    int w = 16;
+    if (c == PC_Z3 && (idle || 3L * w * (N / R) > limit || 3L * w * (N + 2) * 8 > 80 * 1024)) w = 8;
+    if (c == PC_COLS) {
+        w = n >= 384 && n % 128 == 0 && 16L * n * 8 <= 64 * 1024 ? 16 : 8;
+        while (w == 16 && 16 * (N / R) > limit) R *= 2;
+        if (8L * n * 8 > 80 * 1024) w = 4;
+    }
+    if (c == PC_ROWS)
+        for (w = 64; w > 1 && w * (N / R) > (idle ? 128 : (n >= 576 && R >= 12 ? 512 : 256));) w /= 2;
+    while (w < 32 && w * (N / R) * (c == PC_Z3 ? 3 : 1) < 64) w *= 2;
+    return {R, w};
+}
+
+// The compile-time kernels of the default shapes of mesh side n (the x pass with a Green's-function
+// filter only for the sides that the learned correction takes, multiples of 16).
+template <int n>
+inline hipError_t static_default(const FftLaunch& L) {
+    constexpr PassShape z = default_pass(PC_Z, n), z3 = default_pass(PC_Z3, n), r = default_pass(PC_ROWS, n),
+                        c = default_pass(PC_COLS, n);
+    static_assert(z.R && z3.R && r.R && c.R, "a side without a compile-time plan");
+    if (L.split) return hipErrorNotSupported;
+    if (L.op == OP_Z_C2R3) return L.R == z3.R ? static_z_op<n / 2, z3.R, OP_Z_C2R3>(L) : hipErrorNotSupported;
+    if (is_z_op(L.op)) {
+        if (L.R != z.R) return hipErrorNotSupported;
+        return L.op == OP_Z_R2C ? static_z_op<n / 2, z.R, OP_Z_R2C>(L) : static_z_op<n / 2, z.R, OP_Z_C2R>(L);
+    }
+    if (is_rows_op(L.op)) return L.R == r.R ? static_rows_ops<n, r.R>(L) : hipErrorNotSupported;
+    return L.R == c.R && L.width == c.width ? static_cols_ops<n, c.R, c.width, false, n % 16 == 0>(L)
+                                            : hipErrorNotSupported;
+}
+
+// Static kernels (fft_static_<n>.hip: the sides of the workloads, several shapes each;
+// fft_static_sides_<i>.hip: the default shapes of the other sides): hipErrorNotSupported when the
 // file has no kernel of the launch's op, size and shape; with L.probe set nothing is launched.
 hipError_t fft_static_1536(const FftLaunch& L);
 hipError_t fft_static_768(const FftLaunch& L);
@@ -703,5 +804,9 @@ hipError_t fft_static_512(const FftLaunch& L);
 hipError_t fft_static_384(const FftLaunch& L);
 hipError_t fft_static_288(const FftLaunch& L);
 hipError_t fft_static_256(const FftLaunch& L);
+hipError_t fft_static_sides_0(const FftLaunch& L, int n);
+hipError_t fft_static_sides_1(const FftLaunch& L, int n);
+hipError_t fft_static_sides_2(const FftLaunch& L, int n);
+hipError_t fft_static_sides_3(const FftLaunch& L, int n);
 
 }  // namespace cola
