@@ -219,7 +219,7 @@ struct TileGeom {
     int n = 0;             // mesh cells per side
     int tx = 1, ty = 1, tz = 1;
     int ntx = 1, nty = 1, ntz = 1;
-    int lx = 0, ly = 0, lz = 0;  // log2 of the tile sides (all powers of two)
+    int lx = 0, ly = 0, lz = 0;  // log2 of the tile sides (all powers of two; the last tile of a side may be narrower)
     long ntiles = 0;
     long nkeys = 0;        // ntiles * 8 categories
 };

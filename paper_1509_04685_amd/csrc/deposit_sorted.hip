@@ -21,24 +21,32 @@
 
 namespace cola {
 
-// Tiles of tx x tx x tz cells: tx = 8 and tz = 64 where they divide n, with tz lowered (down to 16)
-// while a tile would hold more than about 1024 particles on average -- on a mesh with a particle
-// per cell (PM_grid 1) the 4096-particle tiles of 8 x 8 x 64 made the tile pass and the sort
-// counters (many waves on one key) slower: 0.19 + 0.25 ms against 0.13 + 0.16 ms for 8 x 8 x 16.
+// Tiles of 8 x 8 x tz cells; a mesh side that a tile side does not divide ends in a narrower tile.  tz is
+// the largest of 64, 32, 16 that pads the side by at most an eighth and holds no more than about 1024
+// particles on average -- on a mesh with a particle per cell (PM_grid 1) the 4096-particle tiles of
+// 8 x 8 x 64 made the tile pass and the sort counters (many waves on one key) slower: 0.19 + 0.25 ms
+// against 0.13 + 0.16 ms for 8 x 8 x 16.  Meshes of several particles per cell take smaller tiles, until
+// one holds about 4096 particles, so that there are keys and blocks enough (uniform points in no
+// order, 2.1e6 on 28^3: 485 -> 354 us, 1.7e6 on 64^3: 487 -> 285 us).
+// Tiles that divide the side, as before, fell to 2 x 2 x 2 and to single cells for sides of 2 b and odd
+// sides: 1e6 points on 250^3 took 2389 us, and past 256^3 single-cell tiles are more blocks than a
+// grid holds.
 TileGeom make_tiles(int n, long n_particles) {
     TileGeom t;
     t.n = n;
-    t.tx = 1;
-    for (int c : {8, 4, 2})
-        if (n % c == 0) { t.tx = c; break; }
-    t.ty = t.tx;
     const double per_cell = (double)n_particles / ((double)n * n * n);
-    t.tz = 1;
-    for (int c : {64, 32, 16, 8, 4, 2})
-        if (n % c == 0 && (c <= 16 || (double)t.tx * t.ty * c * per_cell <= 1024.0)) { t.tz = c; break; }
-    t.ntx = n / t.tx;
-    t.nty = n / t.ty;
-    t.ntz = n / t.tz;
+    t.tx = 8;
+    t.tz = 16;
+    for (int c : {64, 32})
+        if ((n + c - 1) / c * c - n <= n / 8 && (double)t.tx * t.tx * c * per_cell <= 1024.0) { t.tz = c; break; }
+    while ((double)t.tx * t.tx * t.tz * per_cell > 4096.0 && t.tx * t.tz > 8) {
+        if (t.tx > 4 || t.tz <= 4) t.tx /= 2;
+        else t.tz /= 2;
+    }
+    t.ty = t.tx;
+    t.ntx = (n + t.tx - 1) / t.tx;
+    t.nty = (n + t.ty - 1) / t.ty;
+    t.ntz = (n + t.tz - 1) / t.tz;
     t.ntiles = (long)t.ntx * t.nty * t.ntz;
     t.nkeys = t.ntiles * 8;
     auto lg = [](int v) { int l = 0; while ((1 << l) < v) ++l; return l; };
@@ -94,6 +102,17 @@ __device__ __forceinline__ float4 load_rec_stream(const float4* p) {
     v.z = __builtin_nontemporal_load(&p->z);
     v.w = __builtin_nontemporal_load(&p->w);
     return v;
+}
+
+// Key and tile-local cell of the cell (mx, my, mz).  Tile sides are powers of two; the upper face of a
+// tile is its last layer, which in the last tile of a side is the mesh's last layer.
+__device__ __forceinline__ uint32_t tile_key(const TileGeom& tg, int mx, int my, int mz, int& local) {
+    const int lx = mx & (tg.tx - 1), ly = my & (tg.ty - 1), lz = mz & (tg.tz - 1), last = tg.n - 1;
+    const uint32_t tile = ((uint32_t)(mx >> tg.lx) * tg.nty + (my >> tg.ly)) * tg.ntz + (mz >> tg.lz);
+    const uint32_t cat = ((lx == tg.tx - 1 || mx == last) ? 4 : 0) | ((ly == tg.ty - 1 || my == last) ? 2 : 0) |
+                         ((lz == tg.tz - 1 || mz == last) ? 1 : 0);
+    local = (((lx << tg.ly) + ly) << tg.lz) + lz;
+    return tile * 8 + cat;
 }
 
 // Binning of the particles onto the mesh of dg (key and cell record per particle, counts per
@@ -154,11 +173,8 @@ __global__ void __launch_bounds__(256) k_dep_bin(ParticlePtrs P, long npr, Latti
         CellC c[3];
 #pragma unroll
         for (int d = 0; d < 3; ++d) c[d] = cell_c(idx[d], x[d], dg.n_part, dg.n_mesh, dg.inv_h, dg.qoff);
-        const int lx = c[0].m % tg.tx, ly = c[1].m % tg.ty, lz = c[2].m % tg.tz;
-        const long tile = ((long)(c[0].m / tg.tx) * tg.nty + c[1].m / tg.ty) * tg.ntz + c[2].m / tg.tz;
-        const int cat = ((lx == tg.tx - 1) ? 4 : 0) | ((ly == tg.ty - 1) ? 2 : 0) | ((lz == tg.tz - 1) ? 1 : 0);
-        key = (uint32_t)(tile * 8 + cat);
-        const int local = (((lx << tg.ly) + ly) << tg.lz) + lz;
+        int local;
+        key = tile_key(tg, c[0].m, c[1].m, c[2].m, local);
         rec = make_float4(__int_as_float(local), c[0].f, c[1].f, c[2].f);
         __builtin_nontemporal_store(key, sb.keys + gid);
         store_rec_stream(sb.recs + gid, rec);
@@ -179,20 +195,18 @@ __global__ void k_dep_bin_abs(const float* px, const float* py, const float* pz,
         CellC c[3];
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-            // rounded product: contracted into u - floor(u) as one fused multiply-add, the
-            // fraction of a coordinate that rounds up to a node would come out negative
-            const float u = __fmul_rn(__builtin_nontemporal_load(ps[d] + p), inv_h);
-            const float fl = floorf(u);
-            c[d].f = u - fl;
+            // the cell of the rounded product, the fraction of the exact one (a fused multiply-add):
+            // where the product rounds up to a node the fraction is about -1e-7 of it, a weight that
+            // the tile pass clamps at 0
+            const float v = __builtin_nontemporal_load(ps[d] + p);
+            const float fl = floorf(v * inv_h);
+            c[d].f = fmaf(v, inv_h, -fl);
             int m = (int)fl % n_mesh;
             m = m < 0 ? m + n_mesh : m;
             c[d].m = min(max(m, 0), n_mesh - 1);
         }
-        const int lx = c[0].m % tg.tx, ly = c[1].m % tg.ty, lz = c[2].m % tg.tz;
-        const long tile = ((long)(c[0].m / tg.tx) * tg.nty + c[1].m / tg.ty) * tg.ntz + c[2].m / tg.tz;
-        const int cat = ((lx == tg.tx - 1) ? 4 : 0) | ((ly == tg.ty - 1) ? 2 : 0) | ((lz == tg.tz - 1) ? 1 : 0);
-        key = (uint32_t)(tile * 8 + cat);
-        const int local = (((lx << tg.ly) + ly) << tg.lz) + lz;
+        int local;
+        key = tile_key(tg, c[0].m, c[1].m, c[2].m, local);
         __builtin_nontemporal_store(key, sb.keys + p);
         store_rec_stream(sb.recs + p, make_float4(__int_as_float(local), c[0].f, c[1].f, c[2].f));
     }
@@ -319,6 +333,9 @@ __global__ void __launch_bounds__(256) k_dep_tile(TileGeom tg, SortBufs sb, long
     const int tzi = (int)(tile % tg.ntz);
     const int tyi = (int)((tile / tg.ntz) % tg.nty);
     const int txi = (int)(tile / ((long)tg.ntz * tg.nty));
+    // cells of this tile along each axis (the last tile of a side may be narrower)
+    const int ncx = min(tg.tx, tg.n - txi * tg.tx), ncy = min(tg.ty, tg.n - tyi * tg.ty),
+              ncz = min(tg.tz, tg.n - tzi * tg.tz);
     const uint32_t* start = sb.start + (long)r * sb.kstride;
     const float4* recs = sb.sorted + (long)r * npr;
     // The 14 range bounds are requested first, so that their latency overlaps the LDS clear.
@@ -369,20 +386,21 @@ __global__ void __launch_bounds__(256) k_dep_tile(TileGeom tg, SortBufs sb, long
         const float4 rec = recs[rb[q] + (i - rlen[q])];
         const int local = __float_as_int(rec.x);
         const int lz = local & (tg.tz - 1), ly = (local >> tg.lz) & (tg.ty - 1), lx = local >> (tg.lz + tg.ly);
-        const int hx = lx - dx * tg.tx, hy = ly - dy * tg.ty, hz = lz - dz * tg.tz;
+        // a record of the tile below sits on that tile's upper face
+        const int hx = dx ? -1 : lx, hy = dy ? -1 : ly, hz = dz ? -1 : lz;
         const float wx[2] = {1.0f - rec.y, rec.y}, wy[2] = {1.0f - rec.z, rec.z}, wz[2] = {1.0f - rec.w, rec.w};
 #pragma unroll
         for (int cx = 0; cx < 2; ++cx) {
             const int ux = hx + cx;
-            if (ux < 0 || ux >= tg.tx) continue;
+            if (ux < 0 || ux >= ncx) continue;
 #pragma unroll
             for (int cy = 0; cy < 2; ++cy) {
                 const int uy = hy + cy;
-                if (uy < 0 || uy >= tg.ty) continue;
+                if (uy < 0 || uy >= ncy) continue;
 #pragma unroll
                 for (int cz = 0; cz < 2; ++cz) {
                     const int uz = hz + cz;
-                    if (uz < 0 || uz >= tg.tz) continue;
+                    if (uz < 0 || uz >= ncz) continue;
                     // clamped at 0: the conversion of a negative weight would wrap to ~2^32
                     atomicAdd(&acc[(((ux << tg.ly) + uy) << tg.lz) + uz],
                               __float2ull_rn(fmaxf(wx[cx] * wy[cy] * wz[cz] * 4294967296.0f, 0.0f)));
@@ -394,10 +412,11 @@ __global__ void __launch_bounds__(256) k_dep_tile(TileGeom tg, SortBufs sb, long
     float* out = mesh + (long)r * mesh_bstride;
     const double unit = 2.3283064365386962890625e-10;  // 2^-32
     auto cell = [&](int i) { return fmaf((float)((double)acc[i] * unit), scale, offset); };
-    if ((tg.tz & 3) == 0) {  // rows of the tile are whole float4s
+    if (((tg.tz | tg.n | (int)row) & 3) == 0) {  // rows of the tile are whole, aligned float4s
         for (int i4 = threadIdx.x; i4 < (ncell >> 2); i4 += blockDim.x) {
             const int i = i4 << 2;
             const int uz = i & (tg.tz - 1), uy = (i >> tg.lz) & (tg.ty - 1), ux = i >> (tg.lz + tg.ly);
+            if (ux >= ncx || uy >= ncy || uz >= ncz) continue;
             const long gx = (long)txi * tg.tx + ux, gy = (long)tyi * tg.ty + uy, gz = (long)tzi * tg.tz + uz;
             const float4 a = make_float4(cell(i), cell(i + 1), cell(i + 2), cell(i + 3));
             store_rec_stream(reinterpret_cast<float4*>(out + (gx * tg.n + gy) * row + gz), a);
@@ -405,6 +424,7 @@ __global__ void __launch_bounds__(256) k_dep_tile(TileGeom tg, SortBufs sb, long
     } else {
         for (int i = threadIdx.x; i < ncell; i += blockDim.x) {
             const int uz = i & (tg.tz - 1), uy = (i >> tg.lz) & (tg.ty - 1), ux = i >> (tg.lz + tg.ly);
+            if (ux >= ncx || uy >= ncy || uz >= ncz) continue;
             const long gx = (long)txi * tg.tx + ux, gy = (long)tyi * tg.ty + uy, gz = (long)tzi * tg.tz + uz;
             out[(gx * tg.n + gy) * row + gz] = cell(i);
         }
