@@ -772,11 +772,10 @@ int cola_cic_density(const float* pos[3], int64_t n, int32_t n_mesh, double box,
     if (ws_bytes < need) return COLA_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const TileGeom tg = make_tiles(n_mesh, (long)n);
-    const SortBufs sb = carve_sort(ws, (long)n, tg, 1);
     const double cells = (double)n_mesh * n_mesh * n_mesh;
     ws_forget(ws);
     (void)hipGetLastError();
-    COLA_TRY(sorted_deposit_absolute(pos, (long)n, n_mesh, (float)(n_mesh / box), tg, sb, delta, n_mesh,
+    COLA_TRY(sorted_deposit_absolute(pos, (long)n, n_mesh, (float)(n_mesh / box), tg, ws, delta, n_mesh,
                                      (float)(cells / (double)n), -1.0f, st));
     return COLA_OK;
 }

@@ -258,10 +258,11 @@ hipError_t sorted_deposit_binned(long npr, int n_real, const LatticeGeom& dg, co
 hipError_t mesh_ghosts(float* F, long row, int n, long bstride, int n_real, hipStream_t st);
 
 // The same deposit for absolute positions pos[3] (n floats each, wrapped into the mesh), one
-// realization, onto a mesh of n_mesh cells per side with rows of `row` floats.
+// realization, onto a mesh of n_mesh cells per side with rows of `row` floats.  scratch: at least
+// abs_sort_bytes, which no mesh with tiles tg needs more of than sort_bytes.
+size_t abs_sort_bytes(long n, const TileGeom& tg);
 hipError_t sorted_deposit_absolute(const float* const pos[3], long n, int n_mesh, float inv_h, const TileGeom& tg,
-                                   const SortBufs& sb, float* mesh, long row, float scale, float offset,
-                                   hipStream_t st);
+                                   void* scratch, float* mesh, long row, float scale, float offset, hipStream_t st);
 
 // ------------------------------------------------------------------ launchers (ic_kernels.hip)
 hipError_t ic_noise(float* w, int n_part, const uint64_t* seeds_host, int n_real, long bstride,

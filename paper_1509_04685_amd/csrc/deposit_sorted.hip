@@ -182,35 +182,60 @@ __global__ void __launch_bounds__(256) k_dep_bin(ParticlePtrs P, long npr, Latti
     (void)wave_increment(sb.count + (long)r * sb.kstride, key, valid);
 }
 
-// Binning of absolute positions (the component entry point): the cell of a coordinate is
-// floor(pos / H) modulo the mesh, the fraction pos / H minus that floor.  Everything after the
-// binning is the step's deposit.
-__global__ void k_dep_bin_abs(const float* px, const float* py, const float* pz, long n, int n_mesh, float inv_h,
-                              TileGeom tg, SortBufs sb) {
+// Absolute positions (the component entry points): the cell of a coordinate is floor(pos n / L) modulo
+// the mesh.  Two passes over the positions: the first counts per key and keeps each point's rank in its
+// key (the counter's old value), the second forms the cell record again and stores it at its key's start
+// plus that rank.  Both are bound by the counters' atomics where the points come in no order (about 20 per
+// nanosecond on the whole chip, against one per run of equal keys in lattice order), so the second pass
+// has none, and no key and record arrays pass through HBM between the two:
+// ABS_MEASURED.
+struct AbsCells {
+    CellC c[3];
+};
+__device__ __forceinline__ AbsCells abs_cells(const float* px, const float* py, const float* pz, long p, int n_mesh,
+                                              float inv_h) {
+    const float* ps[3] = {px, py, pz};
+    AbsCells a;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        // the cell of the rounded product, the fraction of the exact one (a fused multiply-add):
+        // where the product rounds up to a node the fraction is about -1e-7 of it, a weight that
+        // the tile pass clamps at 0
+        const float v = __builtin_nontemporal_load(ps[d] + p);
+        const float fl = floorf(v * inv_h);
+        a.c[d].f = fmaf(v, inv_h, -fl);
+        int m = (int)fl % n_mesh;
+        m = m < 0 ? m + n_mesh : m;
+        a.c[d].m = min(max(m, 0), n_mesh - 1);
+    }
+    return a;
+}
+
+__global__ void __launch_bounds__(256) k_abs_count(const float* px, const float* py, const float* pz, long n,
+                                                   int n_mesh, float inv_h, TileGeom tg, uint32_t* count,
+                                                   uint32_t* rank) {
     const long p = (long)blockIdx.x * blockDim.x + threadIdx.x;
     const bool valid = p < n;
     uint32_t key = 0;
     if (valid) {
-        const float* ps[3] = {px, py, pz};
-        CellC c[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            // the cell of the rounded product, the fraction of the exact one (a fused multiply-add):
-            // where the product rounds up to a node the fraction is about -1e-7 of it, a weight that
-            // the tile pass clamps at 0
-            const float v = __builtin_nontemporal_load(ps[d] + p);
-            const float fl = floorf(v * inv_h);
-            c[d].f = fmaf(v, inv_h, -fl);
-            int m = (int)fl % n_mesh;
-            m = m < 0 ? m + n_mesh : m;
-            c[d].m = min(max(m, 0), n_mesh - 1);
-        }
+        const AbsCells a = abs_cells(px, py, pz, p, n_mesh, inv_h);
         int local;
-        key = tile_key(tg, c[0].m, c[1].m, c[2].m, local);
-        __builtin_nontemporal_store(key, sb.keys + p);
-        store_rec_stream(sb.recs + p, make_float4(__int_as_float(local), c[0].f, c[1].f, c[2].f));
+        key = tile_key(tg, a.c[0].m, a.c[1].m, a.c[2].m, local);
     }
-    (void)wave_increment(sb.count, key, valid);
+    const uint32_t r = wave_increment(count, key, valid);
+    if (valid) __builtin_nontemporal_store(r, rank + p);
+}
+
+__global__ void __launch_bounds__(256) k_abs_scatter(const float* px, const float* py, const float* pz, long n,
+                                                     int n_mesh, float inv_h, TileGeom tg, const uint32_t* start,
+                                                     const uint32_t* rank, float4* sorted) {
+    const long p = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= n) return;
+    const uint32_t r = __builtin_nontemporal_load(rank + p);
+    const AbsCells a = abs_cells(px, py, pz, p, n_mesh, inv_h);
+    int local;
+    const uint32_t key = tile_key(tg, a.c[0].m, a.c[1].m, a.c[2].m, local);
+    sorted[start[key] + r] = make_float4(__int_as_float(local), a.c[0].f, a.c[1].f, a.c[2].f);
 }
 
 // Exclusive scan, phase 1: each block scans 1024 counts (4 per thread) and stores its total.
@@ -469,45 +494,80 @@ SortBufs carve_sort(void* base, long npr, const TileGeom& tg, int n_real) {
 }
 
 namespace {
+// Exclusive scan of the key counts of every realization; cursor = start.
+void scan_keys(int n_real, const TileGeom& tg, const SortBufs& sb, long npr, hipStream_t st) {
+    hipLaunchKernelGGL(k_scan_blocks, dim3(sb.nblocks, n_real), dim3(256), 0, st, sb.count, sb.start, sb.block_sums,
+                       tg.nkeys, sb.kstride, sb.nblocks);
+    hipLaunchKernelGGL(k_scan_totals, dim3(1, n_real), dim3(1024), 0, st, sb.block_sums, sb.nblocks);
+    hipLaunchKernelGGL(k_scan_finish, dim3((unsigned)((tg.nkeys + 1 + 255) / 256), n_real), dim3(256), 0, st,
+                       sb.start, sb.cursor, sb.block_sums, tg.nkeys, sb.kstride, sb.nblocks, (uint32_t)npr);
+}
+
+// Tile accumulation of the sorted records.
+hipError_t run_tiles(long npr, int n_real, const TileGeom& tg, const SortBufs& sb, float* mesh, long row,
+                     long mesh_bstride, float scale, float offset, hipStream_t st) {
+    ProfScope ps(PROF_DEP_TILE, st);
+    size_t lds = (size_t)tg.tx * tg.ty * tg.tz * sizeof(unsigned long long);
+    hipLaunchKernelGGL(k_dep_tile, dim3((unsigned)tg.ntiles, n_real), dim3(256), lds, st, tg, sb, npr, mesh, row,
+                       mesh_bstride, scale, offset);
+    return hipGetLastError();
+}
+
 // Scan of the key counts, scatter of the records into key order, tile accumulation: the passes
-// after the binning, shared by the step's deposit and the deposit of absolute positions.
+// after the binning of the step's deposit.
 hipError_t sort_and_tile(long npr, int n_real, const TileGeom& tg, const SortBufs& sb, float* mesh, long row,
                          long mesh_bstride, float scale, float offset, hipStream_t st) {
-    const dim3 pgrid((unsigned)((npr + 255) / 256), n_real);
     {
         ProfScope ps(PROF_DEP_SORT, st);
-        hipLaunchKernelGGL(k_scan_blocks, dim3(sb.nblocks, n_real), dim3(256), 0, st, sb.count, sb.start,
-                           sb.block_sums, tg.nkeys, sb.kstride, sb.nblocks);
-        hipLaunchKernelGGL(k_scan_totals, dim3(1, n_real), dim3(1024), 0, st, sb.block_sums, sb.nblocks);
-        hipLaunchKernelGGL(k_scan_finish, dim3((unsigned)((tg.nkeys + 1 + 255) / 256), n_real), dim3(256), 0, st,
-                           sb.start, sb.cursor, sb.block_sums, tg.nkeys, sb.kstride, sb.nblocks,
-                           (uint32_t)npr);
-        hipLaunchKernelGGL(k_dep_scatter, pgrid, dim3(256), 0, st, npr, sb);
+        scan_keys(n_real, tg, sb, npr, st);
+        hipLaunchKernelGGL(k_dep_scatter, dim3((unsigned)((npr + 255) / 256), n_real), dim3(256), 0, st, npr, sb);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    {
-        ProfScope ps(PROF_DEP_TILE, st);
-        size_t lds = (size_t)tg.tx * tg.ty * tg.tz * sizeof(unsigned long long);
-        hipLaunchKernelGGL(k_dep_tile, dim3((unsigned)tg.ntiles, n_real), dim3(256), lds, st, tg, sb, npr, mesh, row,
-                           mesh_bstride, scale, offset);
-    }
-    return hipGetLastError();
+    return run_tiles(npr, n_real, tg, sb, mesh, row, mesh_bstride, scale, offset, st);
 }
 }  // namespace
 
+size_t abs_sort_bytes(long n, const TileGeom& tg) {
+    const size_t nblocks = (size_t)((tg.nkeys + 1023) / 1024);
+    return (size_t)n * (4 + 16) + ((size_t)tg.nkeys + 1) * 4 * 3 + nblocks * 4 + 256 * 6;
+}
+
 hipError_t sorted_deposit_absolute(const float* const pos[3], long n, int n_mesh, float inv_h, const TileGeom& tg,
-                                   const SortBufs& sb, float* mesh, long row, float scale, float offset,
-                                   hipStream_t st) {
+                                   void* scratch, float* mesh, long row, float scale, float offset, hipStream_t st) {
+    auto al = [](size_t x) { return (x + 255) / 256 * 256; };
+    char* b = static_cast<char*>(scratch);
+    SortBufs sb;
+    sb.kstride = tg.nkeys + 1;
+    sb.nblocks = (int)((tg.nkeys + 1023) / 1024);
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        char* p = b + off;
+        off = al(off + bytes);
+        return p;
+    };
+    sb.sorted = reinterpret_cast<float4*>(take((size_t)n * 16));
+    uint32_t* rank = reinterpret_cast<uint32_t*>(take((size_t)n * 4));
+    sb.count = reinterpret_cast<uint32_t*>(take((size_t)sb.kstride * 4));
+    sb.start = reinterpret_cast<uint32_t*>(take((size_t)sb.kstride * 4));
+    sb.cursor = reinterpret_cast<uint32_t*>(take((size_t)sb.kstride * 4));
+    sb.block_sums = reinterpret_cast<uint32_t*>(take((size_t)sb.nblocks * 4));
     hipError_t e = launch_fill(reinterpret_cast<float*>(sb.count), sb.kstride, 0.0f, st);
     if (e != hipSuccess) return e;
+    const dim3 grid((unsigned)((n + 255) / 256));
     {
         ProfScope ps(PROF_DEPOSIT, st);
-        hipLaunchKernelGGL(k_dep_bin_abs, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, pos[0], pos[1], pos[2],
-                           n, n_mesh, inv_h, tg, sb);
+        hipLaunchKernelGGL(k_abs_count, grid, dim3(256), 0, st, pos[0], pos[1], pos[2], n, n_mesh, inv_h, tg, sb.count,
+                           rank);
+    }
+    {
+        ProfScope ps(PROF_DEP_SORT, st);
+        scan_keys(1, tg, sb, n, st);
+        hipLaunchKernelGGL(k_abs_scatter, grid, dim3(256), 0, st, pos[0], pos[1], pos[2], n, n_mesh, inv_h, tg,
+                           sb.start, rank, sb.sorted);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    return sort_and_tile(n, 1, tg, sb, mesh, row, 0, scale, offset, st);
+    return run_tiles(n, 1, tg, sb, mesh, row, 0, scale, offset, st);
 }
 
 hipError_t sorted_deposit(const ParticlePtrs& P, long npr, int n_real, const LatticeGeom& dg, bool drift,

@@ -249,9 +249,20 @@ int cola_pm_fields(int32_t n_mesh, double box, const float* pos[3], int64_t n, f
     ws_forget(ws);
     (void)hipGetLastError();
     LC_TRY(launch_twiddles(w.tw, n_mesh, st));
-    LC_TRY(launch_fill(s_real, 2L * gm.total_c(), 0.0f, st));
-    LC_TRY(cic_deposit_absolute(pos, n, n_mesh, (float)(n_mesh / box), row, s_real, st));
-    LC_TRY(density_finish(s_real, row, n_mesh, (float)(cells / (double)n), -1.0f, st));
+    // The tiled deposit sorts its records in A, B and F, which the force fills only afterwards: 20 to 23
+    // bytes per cell, room for about a particle per cell.  More particles than that are added to the
+    // mesh with float atomics (2.1e6 lattice particles, with fill and conversion: 684 us on 128^3 and on 384^3;
+    // tiled: 110 and 150 us).
+    const TileGeom tg = make_tiles(n_mesh, n);
+    const size_t room = 2 * lc_align(gm.bytes()) + fields_f_bytes(n_mesh);
+    if (n <= (int64_t)INT32_MAX - 1 && abs_sort_bytes(n, tg) <= room) {
+        LC_TRY(sorted_deposit_absolute(pos, n, n_mesh, (float)(n_mesh / box), tg, w.A, s_real, row,
+                                       (float)(cells / (double)n), -1.0f, st));
+    } else {
+        LC_TRY(launch_fill(s_real, 2L * gm.total_c(), 0.0f, st));
+        LC_TRY(cic_deposit_absolute(pos, n, n_mesh, (float)(n_mesh / box), row, s_real, st));
+        LC_TRY(density_finish(s_real, row, n_mesh, (float)(cells / (double)n), -1.0f, st));
+    }
     if (delta) LC_TRY(mesh_unpad(s_real, row, n_mesh, delta, st));
     LC_TRY(fft_zy_forward(s_real, row, 0, w.A, 0, gm, w.tw, 1, 1.0f, 0.0f, st));
     LC_TRY(pm_force_interleaved(w.A, w.B, w.S, w.F, w.frow, 0, 0, gm, w.tw, (float)(2.0 * M_PI / box), 1, st));

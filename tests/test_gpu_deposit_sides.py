@@ -64,3 +64,19 @@ def test_density_of_ragged_sides(cola, n, count):
     # bitwise repeatable
     again = cola.cic_density(torch.as_tensor(pos, device="cuda"), n, box).cpu().numpy()
     assert np.array_equal(again.astype(np.float64), got)
+
+
+@pytest.mark.parametrize("n,count,same", [(16, 3000, True), (36, 46656, True), (16, 60000, False)])
+def test_fields_density(cola, n, count, same):
+    """The density of pm_fields: the tiled deposit while its records fit the workspace (about a particle
+    per cell), the same to the bit; float atomics beyond, where a sum of c weights below 1 in any order is
+    off by at most c 2^-24 of its value, c < 200 here."""
+    print(f"pm_fields density {count} points on {n}^3", file=sys.stderr, flush=True)
+    rng = np.random.default_rng(n + count)
+    pos = torch.as_tensor(rng.uniform(0.0, 10.0, size=(3, count)).astype(np.float32), device="cuda").clamp_(max=9.9999)
+    want = cola.cic_density(pos, n, 10.0)
+    got = cola.pm_fields(pos, n, 10.0, g=False, acc=False)["delta"]
+    if same:
+        assert torch.equal(got, want)
+    else:
+        assert float((got - want).abs().max()) < 200 * 6e-8 * float(want.max() + 1.0)
