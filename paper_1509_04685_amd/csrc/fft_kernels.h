@@ -729,6 +729,8 @@ inline hipError_t static_z_ops(const FftLaunch& L) {
 //    straddle lines (486^3 708 against 379).
 //  * y rows: blocks of up to 256 threads, 512 from 576 on with R >= 12 (768^3 585 against 615), 128 on small
 //    meshes (96^3 3.8 against 4.3).
+//  * powers of two take R >= 8, whose stages are those of the run-time plans with 16 values, so that their
+//    digits stay (R = 4 would gain 3 % on the z passes of 64^3 and 128^3).
 //  * never less than a wave per block.
 // The run-time plans that most of these sides had before took, for x_green, 23.6 against 7.1 (96^3) and
 // 909 against 245 (432^3); for z c2r3 at 324^3 125 against 80.
@@ -752,7 +754,7 @@ constexpr PassShape default_pass(PassClass c, int n) {
     int R = 0, least = 0, score = 99;
     for (int i = 0; cand[i]; ++i) {
         const int r = cand[i];
-        if (r < (N % 3 ? 4 : (N % 2 ? 3 : 6)) || !static_plan_ok(N, r) || (long)unit * (N / r) > limit) continue;
+        if (r < (N % 3 ? 8 : (N % 2 ? 3 : 6)) || !static_plan_ok(N, r) || (long)unit * (N / r) > limit) continue;
         if (!least) least = r;
         const int sc = plan_stages(N, r) + (r >= 18 ? 1 : 0);
         if (sc < score || (sc == score && c == PC_Z3 && r == 12)) {
