@@ -270,6 +270,14 @@ int cola_lc_backward(const cola_lc_net* net, int32_t n_mesh, const float* d_df, 
 int cola_lc_loss(int32_t n_mesh, double box, const float* pos[3], int64_t n, const float* df[3],
                  const float* g1[3], const float* g3[3], double* stats, float* d_df, void* stream);
 
+/* cola_lc_loss with a workspace of cola_lc_loss_workspace_bytes (n at most 2^31 - 2), in which the particles
+ * are sorted so that d_df is formed tile by tile instead of with atomics to memory; without one (ws NULL)
+ * it is cola_lc_loss.  cola_lc_loss_workspace_bytes returns 0 for sizes that it does not take. */
+size_t cola_lc_loss_workspace_bytes(int32_t n_mesh, int64_t n);
+int cola_lc_loss_ws(int32_t n_mesh, double box, const float* pos[3], int64_t n, const float* df[3],
+                    const float* g1[3], const float* g3[3], double* stats, float* d_df, void* ws,
+                    size_t ws_bytes, void* stream);
+
 /* One Adam step (Kingma & Ba 2015) at step number t >= 1 on net->params with net->grads, then
  * clears net->grads and repacks the BF16 weights. */
 int cola_lc_adam(const cola_lc_net* net, int32_t t, float lr, float beta1, float beta2, float eps,

@@ -516,8 +516,12 @@ def lc_loss(pos, box, df, g1, g3, stats=None, d_df=None):
         stats = torch.empty(2, dtype=torch.float64, device=df.device)
     if d_df is None:
         d_df = torch.empty((3, n, n, n), dtype=torch.float32, device=df.device)
-    _lib.check(_lib.lib().cola_lc_loss(n, float(box), _ptrs3(pos), pos.shape[1], _ptrs3(df), _ptrs3(g1),
-                                       _ptrs3(g3), _ptr(stats), _ptr(d_df), _stream()), "cola_lc_loss")
+    count = int(pos.shape[1])
+    nb = int(_lib.lib().cola_lc_loss_workspace_bytes(n, count))
+    ws = torch.empty(nb, dtype=torch.uint8, device=df.device) if nb else None
+    _lib.check(_lib.lib().cola_lc_loss_ws(n, float(box), _ptrs3(pos), count, _ptrs3(df), _ptrs3(g1), _ptrs3(g3),
+                                          _ptr(stats), _ptr(d_df), _ptr(ws) if nb else None, nb, _stream()),
+               "cola_lc_loss")
     return stats, d_df
 
 

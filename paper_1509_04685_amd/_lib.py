@@ -24,7 +24,8 @@ EXPORTS = ("cola_workspace_bytes", "cola_ic_2lpt", "cola_pm_force", "cola_step",
            "cola_profiler_num_kinds", "cola_profiler_kind_name", "cola_profiler_read", "cola_copy",
            "cola_last_error", "cola_autotune", "cola_ensemble_run", "cola_ensemble_release",
            "cola_lc_param_count", "cola_lc_packed_bytes", "cola_lc_workspace_bytes", "cola_lc_pack",
-           "cola_lc_forward", "cola_lc_backward", "cola_lc_loss", "cola_lc_adam", "cola_step_lc",
+           "cola_lc_forward", "cola_lc_backward", "cola_lc_loss", "cola_lc_loss_ws",
+           "cola_lc_loss_workspace_bytes", "cola_lc_adam", "cola_step_lc",
            "cola_pm_fields_workspace_bytes", "cola_pm_fields", "cola_positions", "cola_mfma_selftest",
            "cola_profiler_read_groups", "cola_fof_workspace_bytes", "cola_fof", "cola_fof_catalogue",
            "cola_fof_mass_histogram", "cola_particle_mass", "cola_power_multipoles", "cola_pm_force_lc",
@@ -123,6 +124,9 @@ def _load():
         "cola_lc_backward": (ctypes.c_int, [N, i32, vp, vp, sz, vp]),
         "cola_lc_loss": (ctypes.c_int, [i32, dbl, ctypes.POINTER(vp), i64, ctypes.POINTER(vp), ctypes.POINTER(vp),
                                         ctypes.POINTER(vp), vp, vp, vp]),
+        "cola_lc_loss_workspace_bytes": (sz, [i32, i64]),
+        "cola_lc_loss_ws": (ctypes.c_int, [i32, dbl, ctypes.POINTER(vp), i64, ctypes.POINTER(vp), ctypes.POINTER(vp),
+                                           ctypes.POINTER(vp), vp, vp, vp, sz, vp]),
         "cola_lc_adam": (ctypes.c_int, [N, i32, ctypes.c_float, ctypes.c_float, ctypes.c_float, ctypes.c_float, vp]),
         "cola_step_lc": (ctypes.c_int, [P, C, i32, i32, PP, N, vp, sz, vp, sz, vp]),
         "cola_pm_fields_workspace_bytes": (sz, [i32]),

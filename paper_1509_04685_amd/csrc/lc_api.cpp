@@ -183,11 +183,30 @@ int cola_lc_backward(const cola_lc_net* net, int32_t n_mesh, const float* d_df, 
 
 int cola_lc_loss(int32_t n_mesh, double box, const float* pos[3], int64_t n, const float* df[3], const float* g1[3],
                  const float* g3[3], double* stats, float* d_df, void* stream) {
+    return cola_lc_loss_ws(n_mesh, box, pos, n, df, g1, g3, stats, d_df, nullptr, 0, stream);
+}
+
+size_t cola_lc_loss_workspace_bytes(int32_t n_mesh, int64_t n) {
+    if (n_mesh < 2 || n_mesh > kMaxLcMesh || n < 1 || n > (int64_t)INT32_MAX - 1) return 0;
+    return lc_loss_bytes(n_mesh, (long)n);
+}
+
+int cola_lc_loss_ws(int32_t n_mesh, double box, const float* pos[3], int64_t n, const float* df[3], const float* g1[3],
+                    const float* g3[3], double* stats, float* d_df, void* ws, size_t ws_bytes, void* stream) {
     if (!std::isfinite(box)) return COLA_ERR_NONFINITE;
     if (n_mesh < 2 || n_mesh > kMaxLcMesh || !(box > 0.0) || n < 1) return COLA_ERR_INVALID_ARG;
     if (!ptrs3(pos) || !ptrs3(df) || !ptrs3(g1) || !ptrs3(g3) || !stats || !d_df) return COLA_ERR_INVALID_ARG;
+    hipStream_t st = static_cast<hipStream_t>(stream);
     (void)hipGetLastError();
-    LC_TRY(lc_loss(pos, n, n_mesh, box, df, g1, g3, stats, d_df, static_cast<hipStream_t>(stream)));
+    if (!ws) {
+        LC_TRY(lc_loss(pos, n, n_mesh, box, df, g1, g3, stats, d_df, st));
+        return COLA_OK;
+    }
+    const size_t need = cola_lc_loss_workspace_bytes(n_mesh, n);
+    if (need == 0) return COLA_ERR_UNSUPPORTED_SIZE;
+    if (ws_bytes < need) return COLA_ERR_WORKSPACE_TOO_SMALL;
+    ws_forget(ws);
+    LC_TRY(lc_loss_tiled(pos, (long)n, n_mesh, box, df, g1, g3, stats, d_df, ws, st));
     return COLA_OK;
 }
 

@@ -85,6 +85,14 @@ hipError_t lc_band(const float* T, int n, float beta, float* const out[3], long 
 hipError_t lc_loss(const float* const pos[3], long np, int n, double box, const float* const df[3],
                    const float* const g1[3], const float* const g3[3], double* stats, float* ddf,
                    hipStream_t st);
+// The same with d_df formed by tiles; scratch: lc_loss_bytes (0: too many tiles for 32-bit keys).
+size_t lc_loss_bytes(int n, long np);
+hipError_t lc_loss_tiled(const float* const pos[3], long np, int n, double box, const float* const df[3],
+                         const float* const g1[3], const float* const g3[3], double* stats, float* ddf, void* scratch,
+                         hipStream_t st);
+// stats = (0, sum_p |g3 - g1|^2).
+hipError_t lc_loss_denominator(const float* const g1[3], const float* const g3[3], long np, double* stats,
+                               hipStream_t st);
 hipError_t lc_adam(float* p, float* g, float* m, float* v, long np, float lr, float b1, float b2, float eps, int t,
                    hipStream_t st);
 // Absolute positions q + x wrapped into [0, box) (lattice as in the step).

@@ -22,6 +22,7 @@
 #include "cola_internal.h"
 #include "lc_internal.h"
 #include "force_gather.h"
+#include "lc_cic.h"
 
 namespace cola {
 
@@ -771,17 +772,6 @@ __global__ void __launch_bounds__(256) k_lc_out_back(const float* ddf, const uin
 
 // ------------------------------------------------------------------ particle loss
 
-__device__ __forceinline__ void cic_abs(float pos, float inv_h, int n, int& i0, int& i1, float& f) {
-    const float u = pos * inv_h;
-    const float fl = floorf(u);
-    f = u - fl;
-    int m = (int)fl % n;
-    m = m < 0 ? m + n : m;
-    m = min(max(m, 0), n - 1);  // a non-finite position still maps inside the mesh
-    i0 = m;
-    i1 = m + 1 == n ? 0 : m + 1;
-}
-
 // stats[1] += sum_p |g3 - g1|^2  (float64)
 __global__ void k_lc_denom(const float* g1x, const float* g1y, const float* g1z, const float* g3x,
                            const float* g3y, const float* g3z, long np, double* stats) {
@@ -801,7 +791,8 @@ __global__ void k_lc_denom(const float* g1x, const float* g1y, const float* g1z,
 }
 
 // r_p = g1 + G[dF]_p - g3;  stats[0] += |r|^2 / denom;  d_dF += G^T (2 r / denom)  (G = CIC gather
-// at absolute positions on the dense n^3 mesh).
+// at absolute positions on the dense n^3 mesh), with float atomics: for callers that have no scratch
+// (lc_loss.hip has the tiled form).
 __global__ void k_lc_loss(const float* px, const float* py, const float* pz, long np, int n, float inv_h,
                           const float* dfx, const float* dfy, const float* dfz, const float* g1x, const float* g1y,
                           const float* g1z, const float* g3x, const float* g3y, const float* g3z, double* stats,
@@ -810,39 +801,24 @@ __global__ void k_lc_loss(const float* px, const float* py, const float* pz, lon
     const long p = (long)blockIdx.x * blockDim.x + threadIdx.x;
     double l2 = 0.0;
     if (p < np) {
-        int ix0, ix1, iy0, iy1, iz0, iz1;
-        float fx, fy, fz;
-        cic_abs(px[p], inv_h, n, ix0, ix1, fx);
-        cic_abs(py[p], inv_h, n, iy0, iy1, fy);
-        cic_abs(pz[p], inv_h, n, iz0, iz1, fz);
-        const int ix[2] = {ix0, ix1}, iy[2] = {iy0, iy1}, iz[2] = {iz0, iz1};
-        const float wx[2] = {1.0f - fx, fx}, wy[2] = {1.0f - fy, fy}, wz[2] = {1.0f - fz, fz};
-        float g0 = 0.f, g1 = 0.f, g2 = 0.f;
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const long v = ((long)ix[a] * n + iy[b]) * n + iz[c];
-                    const float w = wx[a] * wy[b] * wz[c];
-                    g0 += w * dfx[v];
-                    g1 += w * dfy[v];
-                    g2 += w * dfz[v];
-                }
-        const float r0 = g1x[p] + g0 - g3x[p], r1 = g1y[p] + g1 - g3y[p], r2 = g1z[p] + g2 - g3z[p];
+        LossCell c;
+        loss_cell(px[p], py[p], pz[p], inv_h, n, c);
+        const float *df[3] = {dfx, dfy, dfz}, *g1[3] = {g1x, g1y, g1z}, *g3[3] = {g3x, g3y, g3z};
+        float r0, r1, r2;
+        loss_resid(c, n, df, g1, g3, p, r0, r1, r2);
         const double inv = 1.0 / stats[1];
         l2 = ((double)r0 * r0 + (double)r1 * r1 + (double)r2 * r2) * inv;
         const float s = (float)(2.0 * inv);
+        const float wx[2] = {1.0f - c.f[0], c.f[0]}, wy[2] = {1.0f - c.f[1], c.f[1]}, wz[2] = {1.0f - c.f[2], c.f[2]};
         const long V = (long)n * n * n;
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
             for (int b = 0; b < 2; ++b)
 #pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const long v = ((long)ix[a] * n + iy[b]) * n + iz[c];
-                    const float w = wx[a] * wy[b] * wz[c] * s;
+                for (int d = 0; d < 2; ++d) {
+                    const long v = ((long)c.i[0][a] * n + c.i[1][b]) * n + c.i[2][d];
+                    const float w = wx[a] * wy[b] * wz[d] * s;
                     atomicAdd(&ddf[v], w * r0);
                     atomicAdd(&ddf[V + v], w * r1);
                     atomicAdd(&ddf[2 * V + v], w * r2);
@@ -1056,15 +1032,23 @@ hipError_t lc_backward(const LcParams& P, const LcActs& A, LcGrads& G, int n, fl
     return hipErrorInvalidValue;
 }
 
-hipError_t lc_loss(const float* const pos[3], long np, int n, double box, const float* const df[3],
-                   const float* const g1[3], const float* const g3[3], double* stats, float* ddf,
-                   hipStream_t st) {
+hipError_t lc_loss_denominator(const float* const g1[3], const float* const g3[3], long np, double* stats,
+                               hipStream_t st) {
     hipError_t e = launch_fill_d(stats, 2, 0.0, st);
     if (e != hipSuccess) return e;
-    if ((e = launch_fill(ddf, 3L * n * n * n, 0.0f, st)) != hipSuccess) return e;
     ProfScope ps(PROF_LC_MISC, st);
     hipLaunchKernelGGL(k_lc_denom, dim3((unsigned)std::min<long>(blocks_for(np, 256), 1024)), dim3(256), 0, st,
                        g1[0], g1[1], g1[2], g3[0], g3[1], g3[2], np, stats);
+    return hipGetLastError();
+}
+
+hipError_t lc_loss(const float* const pos[3], long np, int n, double box, const float* const df[3],
+                   const float* const g1[3], const float* const g3[3], double* stats, float* ddf,
+                   hipStream_t st) {
+    hipError_t e = lc_loss_denominator(g1, g3, np, stats, st);
+    if (e != hipSuccess) return e;
+    if ((e = launch_fill(ddf, 3L * n * n * n, 0.0f, st)) != hipSuccess) return e;
+    ProfScope ps(PROF_LC_MISC, st);
     hipLaunchKernelGGL(k_lc_loss, dim3(blocks_for(np, 256)), dim3(256), 0, st, pos[0], pos[1], pos[2], np, n,
                        (float)(n / box), df[0], df[1], df[2], g1[0], g1[1], g1[2], g3[0], g3[1], g3[2], stats, ddf);
     return hipGetLastError();
