@@ -528,134 +528,237 @@ hipError_t lc_band(const float* T, int n, float beta, float* const out[3], long 
 
 // ------------------------------------------------------------------ weight gradient
 
-constexpr int SDZ = TV + 8;       // padded channel row of the staged upstream gradient
-constexpr int SXP = HVOX + 8;     // padded channel row of the staged input halo
+// dW[co][ci][tap] = sum_v dZ[v][co] X[v + d_tap][ci], db[co] = sum_v dZ[v][co], over tiles of 4x4x16 voxels:
+// MFMA with M = output channels, N = input channels, K = 32 voxels (two 16-voxel z rows).  Both operands
+// index K along z, so dZ and the halo of X go to LDS channel-major (two z neighbours of a channel per
+// 32-bit write), rows of the halo 24 values apart so that a fragment of 8 voxels is one aligned
+// 16-byte read.  That read and the next 4 bytes hold the fragments of all three dz of a (dx, dy):
+// the words as they are (dz = -1), shifted by one value (v_alignbit, 0) and by one word (+1).
+//
+// FIRST (layer 1): 4 input channels fill a quarter of the N = 16 columns, so each MFMA takes four (dx, dy)
+// side by side (column m: pair 4 j + m / 4, channel m % 4).
+// The four waves split the 8 K steps of a tile (KS = 4), or with 32 x 32 channels, whose sums need all
+// registers of a wave for a third of the taps, the (dx, dy) pairs.  The bias is one more product, with ones.
+//
+// A block sums its tiles in registers and writes its sums once, as its row of `part`; k_wgrad_reduce adds
+// the rows.  Flushing with float atomics from 1024 blocks, 7e6 atomics on 6912 addresses, and fragments
+// gathered by eight 16-bit reads each, took 574 us (16 x 16 channels) and 501 us (layer 1) on 128^3;
+// so 72 and 39 us, and 5 each for the rows.
+constexpr int SDZ = TV + 8;         // channel row of the staged upstream gradient
+constexpr int HZP = 24;             // z row of the staged halo (HZ used)
+constexpr int SXP = HX * HY * HZP + 8;  // channel row: an odd multiple of 16 bytes
+constexpr int HPAIRS = HX * HY * (HZ / 2);
 
-// dW[co][ci][tap] += sum_v dZ[v][co] X[v + d_tap][ci] and db[co] += sum_v dZ[v][co] over the
-// tiles of this block: MFMA with M = output channels, N = input channels, K = 32 voxels (two
-// 16-voxel z rows); wave w owns the taps w, w + 4, ...; one atomic flush per block.
-template <int CINP, int MB>
-__global__ void __launch_bounds__(256) k_conv3_wgrad(const uint16_t* __restrict__ dz, const uint16_t* __restrict__ x,
-                                                     float* dw, float* db, int n, int cin, int tiles) {
-    constexpr int COP = 16 * MB;
-    constexpr int NBN = (CINP + 15) / 16;
-    constexpr int TPW = 7;
+template <int C, bool FIRST>
+struct WgradShape {
+    static constexpr int CIN = FIRST ? 4 : C;
+    static constexpr int MB = C / 16, NBN = FIRST ? 1 : C / 16;
+    static constexpr int KS = (FIRST || C == 16) ? 4 : 1, TS = 4 / KS;
+    static constexpr int NJ = FIRST ? 3 : (9 + TS - 1) / TS;
+    static constexpr int NP = C * CIN * 27 + C;  // values of one row of partial sums: dW, then db
+    static constexpr size_t kTileBytes = (size_t)C * SDZ * 2 + (size_t)CIN * SXP * 2;
+    static constexpr size_t kLds = KS == 4 && (size_t)NP * 4 > kTileBytes ? (size_t)NP * 4 : kTileBytes;
+};
+
+template <int C, bool FIRST>
+__global__ void __launch_bounds__(256, 2) k_conv3_wgrad(const uint16_t* __restrict__ dz, const uint16_t* __restrict__ x,
+                                                        float* part, int n, int tiles) {
+    using S = WgradShape<C, FIRST>;
+    constexpr int MB = S::MB, NBN = S::NBN, KS = S::KS, TS = S::TS, NJ = S::NJ;
+    constexpr int C8 = C / 8, X8 = FIRST ? 1 : C8;
+    constexpr int NDZ = TV / 2 * C8, NX = HPAIRS * X8;  // staged items: a pair of z neighbours, 8 channels (FIRST: 4)
+    constexpr int KDZ = (NDZ + 255) / 256, KX = (NX + 255) / 256;
     extern __shared__ uint4 smem[];
-    uint16_t* sdz = reinterpret_cast<uint16_t*>(smem);  // [COP][SDZ], channel-major
-    uint16_t* sx = sdz + COP * SDZ;                      // [CINP][SXP], channel-major
+    uint16_t* sdz = reinterpret_cast<uint16_t*>(smem);  // [C][SDZ]
+    uint16_t* sx = sdz + C * SDZ;                        // [CIN][SXP]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int m = lane & 15, kb = lane >> 4;
+    const int ksel = KS == 4 ? wave : 0, tsel = TS == 4 ? wave : 0;
     const int nty = n / TY, ntz = n / TZ;
     const uint4* dzg = reinterpret_cast<const uint4*>(dz);
     const uint4* xg = reinterpret_cast<const uint4*>(x);
-    f32x4 acc[TPW][MB][NBN];
+    Frag8 ones;
+    ones.u = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+    f32x4 acc[NJ][3][MB][NBN], accb[MB];
 #pragma unroll
-    for (int a = 0; a < TPW; ++a)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
-        for (int i = 0; i < MB; ++i)
+        for (int t = 0; t < 3; ++t)
 #pragma unroll
-            for (int j = 0; j < NBN; ++j) acc[a][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float bacc = 0.0f;
-    for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+            for (int i = 0; i < MB; ++i)
+#pragma unroll
+                for (int jn = 0; jn < NBN; ++jn) acc[j][t][i][jn] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < MB; ++i) accb[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // The next tile is loaded during the products, except where the sums leave no registers for it.
+    constexpr bool PREFETCH = FIRST || C == 16;
+    u32x4 rdz[KDZ][2], rx[KX][2];
+    auto load_tile = [&](int tile) {
         const int tz = tile % ntz, ty = (tile / ntz) % nty, tx = tile / (ntz * nty);
         const int x0 = tx * TX, y0 = ty * TY, z0 = tz * TZ;
-        __syncthreads();
-        for (int i = tid; i < TV * (COP / 8); i += 256) {
-            const int c8 = i % (COP / 8), tv = i / (COP / 8);
-            const int lz = tv % TZ, ly = (tv / TZ) % TY, lx = tv / (TZ * TY);
-            const long v = ((long)(x0 + lx) * n + (y0 + ly)) * n + (z0 + lz);
-            Frag8 f;
-            f.u = dzg[v * (COP / 8) + c8];
 #pragma unroll
-            for (int h = 0; h < 8; ++h) sdz[(c8 * 8 + h) * SDZ + tv] = f.h[h];
+        for (int k = 0; k < KDZ; ++k) {
+            const int i = tid + k * 256;
+            if (i < NDZ) {
+                const int c8 = i % C8, tv = 2 * (i / C8);
+                const int lz = tv % TZ, ly = (tv / TZ) % TY, lx = tv / (TZ * TY);
+                const long v = ((long)(x0 + lx) * n + (y0 + ly)) * n + (z0 + lz);
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    rdz[k][q] = *reinterpret_cast<const u32x4*>(dzg + (v + q) * C8 + c8);
+            }
         }
 #pragma unroll
-        for (int k = 0; k < (HVOX + 255) / 256; ++k) {
-            const int hv = tid + k * 256;
-            if (hv < HVOX) {
-                const int hz = hv % HZ, hy = (hv / HZ) % HY, hx = hv / (HZ * HY);
+        for (int k = 0; k < KX; ++k) {
+            const int i = tid + k * 256;
+            if (i < NX) {
+                const int c8 = i % X8, pr = i / X8;
+                const int hz = 2 * (pr % (HZ / 2)), hr = pr / (HZ / 2), hy = hr % HY, hx = hr / HY;
                 const int gx = wrap_halo(x0 + hx - 1, n), gy = wrap_halo(y0 + hy - 1, n);
-                const int gz = wrap_halo(z0 + hz - 1, n);
-                const uint4* src = xg + (((long)gx * n + gy) * n + gz) * (CINP / 8);
+                const long row = ((long)gx * n + gy) * n;
 #pragma unroll
-                for (int c8 = 0; c8 < CINP / 8; ++c8) {
-                    Frag8 f;
-                    f.u = src[c8];
+                for (int q = 0; q < 2; ++q)
+                    rx[k][q] = *reinterpret_cast<const u32x4*>(xg + (row + wrap_halo(z0 + hz + q - 1, n)) * X8 + c8);
+            }
+        }
+    };
+    // two voxels of 8 (or 4) channels to channel-major LDS: one 32-bit write per channel
+    auto put_pair = [&](uint16_t* dst, int stride, const u32x4& a, const u32x4& b, int channels) {
 #pragma unroll
-                    for (int h = 0; h < 8; ++h) sx[(c8 * 8 + h) * SXP + hv] = f.h[h];
-                }
+        for (int h = 0; h < channels; h += 2) {
+            const uint32_t lo = a[h / 2], hi = b[h / 2];
+            *reinterpret_cast<uint32_t*>(dst + h * stride) = (lo & 0xffffu) | (hi << 16);
+            *reinterpret_cast<uint32_t*>(dst + (h + 1) * stride) = (lo >> 16) | (hi & 0xffff0000u);
+        }
+    };
+    if (PREFETCH && (int)blockIdx.x < tiles) load_tile(blockIdx.x);
+    for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        if (!PREFETCH) load_tile(tile);
+        __syncthreads();  // the previous tile's readers are done
+#pragma unroll
+        for (int k = 0; k < KDZ; ++k) {
+            const int i = tid + k * 256;
+            if (i < NDZ) put_pair(sdz + (i % C8) * 8 * SDZ + 2 * (i / C8), SDZ, rdz[k][0], rdz[k][1], 8);
+        }
+#pragma unroll
+        for (int k = 0; k < KX; ++k) {
+            const int i = tid + k * 256;
+            if (i < NX) {
+                const int pr = i / X8;
+                put_pair(sx + (i % X8) * 8 * SXP + (pr / (HZ / 2)) * HZP + 2 * (pr % (HZ / 2)), SXP, rx[k][0], rx[k][1],
+                         FIRST ? 4 : 8);
             }
         }
         __syncthreads();
-        if (tid < COP) {
-            float s = 0.0f;
-            for (int tv = 0; tv < TV; ++tv) s += bf2f(sdz[tid * SDZ + tv]);
-            bacc += s;
-        }
-        for (int ksv = 0; ksv < TV / 32; ++ksv) {
-            const int row = ksv * 2 + (kb >> 1), zh = (kb & 1) * 8;  // voxels z = zh .. zh + 7 of row
+        if (PREFETCH && tile + (int)gridDim.x < tiles) load_tile(tile + gridDim.x);
+#pragma unroll
+        for (int ks0 = 0; ks0 < TV / 32; ks0 += KS) {
+            const int row = (ks0 + ksel) * 2 + (kb >> 1), zh = (kb & 1) * 8;  // voxels z = zh .. zh + 7 of row
             const int lx = row / TY, ly = row % TY;
             Frag8 af[MB];
 #pragma unroll
-            for (int i = 0; i < MB; ++i)
+            for (int i = 0; i < MB; ++i) {
                 af[i].u = *reinterpret_cast<const uint4*>(sdz + (i * 16 + m) * SDZ + row * TZ + zh);
+                if (tsel == 0) accb[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i].v, ones.v, accb[i], 0, 0, 0);
+            }
 #pragma unroll
-            for (int a = 0; a < TPW; ++a) {
-                const int tap = wave + 4 * a;
-                if (tap < 27) {
-                    const int dx = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dzz = tap % 3 - 1;
-                    const int hv0 = ((lx + 1 + dx) * HY + (ly + 1 + dy)) * HZ + (zh + 1 + dzz);
+            for (int j = 0; j < NJ; ++j) {
+                const int pair = FIRST ? min(4 * j + (m >> 2), 8) : tsel + TS * j;
+                if (!FIRST && pair >= 9) break;
+                const int hrow = (lx + pair / 3) * HY + ly + pair % 3;
 #pragma unroll
-                    for (int j = 0; j < NBN; ++j) {
-                        const int ci = j * 16 + m;
-                        Frag8 bfr;
-                        if (ci < CINP) {
-                            const uint16_t* p = sx + ci * SXP + hv0;
-                            uint32_t t8[8];
+                for (int jn = 0; jn < NBN; ++jn) {
+                    const int ci = FIRST ? (m & 3) : jn * 16 + m;
+                    const uint16_t* p = sx + ci * SXP + hrow * HZP + zh;
+                    const uint4 w = *reinterpret_cast<const uint4*>(p);
+                    const uint32_t w4 = *reinterpret_cast<const uint32_t*>(p + 8);
+                    Frag8 f[3];
+                    f[0].u = w;
+                    f[1].u = make_uint4(__builtin_amdgcn_alignbit(w.y, w.x, 16), __builtin_amdgcn_alignbit(w.z, w.y, 16),
+                                        __builtin_amdgcn_alignbit(w.w, w.z, 16), __builtin_amdgcn_alignbit(w4, w.w, 16));
+                    f[2].u = make_uint4(w.y, w.z, w.w, w4);
 #pragma unroll
-                            for (int q = 0; q < 8; ++q) t8[q] = p[q];
-                            bfr.u = pack8(t8);
-                        } else {
-                            bfr.u = make_uint4(0, 0, 0, 0);
-                        }
+                    for (int t = 0; t < 3; ++t)
 #pragma unroll
                         for (int i = 0; i < MB; ++i)
-                            acc[a][i][j] =
-                                __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i].v, bfr.v, acc[a][i][j], 0, 0, 0);
-                    }
+                            acc[j][t][i][jn] =
+                                __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i].v, f[t].v, acc[j][t][i][jn], 0, 0, 0);
                 }
             }
         }
     }
-    // flush: lane holds rows co = 16 i + 4 kb + q, column ci = 16 j + m
+    // lane holds rows co = 16 i + 4 kb + q, column m of each product
+    float* const row = part + (long)blockIdx.x * S::NP;
+    float* const red = reinterpret_cast<float*>(smem);
+    auto emit = [&](auto&& put) {
 #pragma unroll
-    for (int a = 0; a < TPW; ++a) {
-        const int tap = wave + 4 * a;
-        if (tap < 27) {
+        for (int j = 0; j < NJ; ++j) {
+            const int pair = FIRST ? 4 * j + (m >> 2) : tsel + TS * j;
+            if (pair >= 9) continue;
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+#pragma unroll
+                for (int i = 0; i < MB; ++i)
+#pragma unroll
+                    for (int jn = 0; jn < NBN; ++jn)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const int co = i * 16 + 4 * kb + q, ci = FIRST ? (m & 3) : jn * 16 + m;
+                            put((co * S::CIN + ci) * 27 + pair * 3 + t, acc[j][t][i][jn][q]);
+                        }
+        }
+        if (tsel == 0 && m == 0)
 #pragma unroll
             for (int i = 0; i < MB; ++i)
 #pragma unroll
-                for (int j = 0; j < NBN; ++j)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int co = i * 16 + 4 * kb + q, ci = j * 16 + m;
-                        if (ci < cin) atomicAdd(&dw[((long)co * cin + ci) * 27 + tap], acc[a][i][j][q]);
-                    }
+                for (int q = 0; q < 4; ++q) put(C * S::CIN * 27 + i * 16 + 4 * kb + q, accb[i][q]);
+    };
+    if constexpr (KS == 4) {  // the waves hold parts of the same sums
+        for (int w = 0; w < 4; ++w) {
+            __syncthreads();
+            if (wave == w) emit([&](int i, float v) { red[i] = w == 0 ? v : red[i] + v; });
         }
+        __syncthreads();
+        for (int i = tid; i < S::NP; i += 256) row[i] = red[i];
+    } else {
+        emit([&](int i, float v) { row[i] = v; });
     }
-    if (tid < COP) atomicAdd(&db[tid], bacc);
 }
 
-template <int CINP, int MB>
-static hipError_t run_wgrad(const uint16_t* dz, const uint16_t* x, float* dw, float* db, int n, int cin,
+// dw[i] += sum over rows of part[row][i], the bias after the weights; 64 values by 16 groups of rows per block.
+__global__ void __launch_bounds__(1024) k_wgrad_reduce(const float* part, int rows, int np, int nw, float* dw, float* db) {
+    __shared__ float red[16][64];
+    const int c = threadIdx.x & 63, g = threadIdx.x >> 6;
+    const int i = blockIdx.x * 64 + c;
+    float s = 0.0f;
+    if (i < np) {
+#pragma unroll 8
+        for (int r = g; r < rows; r += 16) s += part[(long)r * np + i];
+    }
+    red[g][c] = s;
+    __syncthreads();
+    if (g == 0 && i < np) {
+#pragma unroll
+        for (int k = 1; k < 16; ++k) s += red[k][c];
+        if (i < nw) dw[i] += s;
+        else db[i - nw] += s;
+    }
+}
+
+// part: room for `room` floats of partial sums (at least one row).
+template <int C, bool FIRST>
+static hipError_t run_wgrad(const uint16_t* dz, const uint16_t* x, float* dw, float* db, int n, float* part, long room,
                             hipStream_t st) {
+    using S = WgradShape<C, FIRST>;
     const long tiles = conv_tiles(n);
-    const size_t lds = (size_t)16 * MB * SDZ * 2 + (size_t)CINP * SXP * 2;
-    auto kern = k_conv3_wgrad<CINP, MB>;
-    if (hipError_t e = allow_lds_lc(kern, lds); e != hipSuccess) return e;
+    const int blocks = (int)std::min(std::min(tiles, 512L), room / S::NP);  // two blocks per CU
+    auto kern = k_conv3_wgrad<C, FIRST>;
+    if (hipError_t e = allow_lds_lc(kern, S::kLds); e != hipSuccess) return e;
     ProfScope ps(PROF_LC_WGRAD, st);
-    hipLaunchKernelGGL(kern, dim3((unsigned)std::min<long>(tiles, 1024)), dim3(256), lds, st, dz, x, dw, db, n, cin,
-                       (int)tiles);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), S::kLds, st, dz, x, part, n, (int)tiles);
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3((S::NP + 63) / 64), dim3(1024), 0, st, part, blocks, S::NP, S::NP - C, dw,
+                       db);
     return hipGetLastError();
 }
 
@@ -1019,10 +1122,13 @@ static hipError_t backward_c(const LcParams& P, const LcActs& A, LcGrads& G, int
                            st, ddf, A.z2, P.w3, out_scale, n, A.dz2, G.w3, G.b3);
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
-    if (hipError_t e = run_wgrad<C, NB>(A.dz2, A.a1, G.w2, G.b2, n, C, st); e != hipSuccess) return e;
+    // A2 is not read by the backward pass: its space takes the partial sums of the weight gradients
+    float* const part = reinterpret_cast<float*>(A.a2);
+    const long room = V * C / 2;
+    if (hipError_t e = run_wgrad<C, false>(A.dz2, A.a1, G.w2, G.b2, n, part, room, st); e != hipSuccess) return e;
     if (hipError_t e = run_conv<C, NB, EPI_DSILU>(A.dz2, P.wt2, nullptr, A.dz1, nullptr, A.z1, n, st); e != hipSuccess)
         return e;
-    return run_wgrad<8, NB>(A.dz1, A.x0, G.w1, G.b1, n, 4, st);
+    return run_wgrad<C, true>(A.dz1, A.x0, G.w1, G.b1, n, part, room, st);
 }
 
 hipError_t lc_backward(const LcParams& P, const LcActs& A, LcGrads& G, int n, float out_scale, float band,
