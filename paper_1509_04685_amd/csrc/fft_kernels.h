@@ -14,6 +14,7 @@
 #pragma once
 
 #include "cola_internal.h"
+#include "wave_ops.h"
 
 namespace cola {
 
@@ -27,15 +28,6 @@ struct ColGeom {
     int tk;           // columns per tile
     int tiles;        // tiles per plane
 };
-
-// Block b runs on XCD b % 8 (round-robin dispatch); hand each XCD a contiguous run of tiles so
-// that neighbouring tiles, which share 128-byte lines when a tile row is narrower than a line,
-// meet in the same L2.
-__device__ __forceinline__ int xcd_block() {
-    const int nb = gridDim.x, b = blockIdx.x;
-    const int q = nb >> 3, r = nb & 7, x = b & 7, i = b >> 3;
-    return (x < r) ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
-}
 
 // TK > 0: columns per tile fixed at compile time (cg.tk is then equal to it).  c: the column (y),
 // plane: the kz plane of the block's tile.

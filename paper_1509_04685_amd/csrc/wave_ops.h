@@ -1,5 +1,4 @@
-// Wave-level helpers shared by the kernels that count particles into bins (deposit sort,
-// friends-of-friends cells).
+// Block order and wave-level helpers shared by the kernels (FFT passes, deposit sort, friends-of-friends).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -7,6 +6,15 @@
 #include <cstdint>
 
 namespace cola {
+
+// Block b runs on XCD b % 8 (round-robin dispatch); hand each XCD a contiguous run of the grid's blocks
+// (along x), so that neighbouring blocks, which share cache lines -- the 128-byte lines of narrow FFT tiles, the
+// cells and mesh lines around neighbouring particles -- meet in the same L2.
+__device__ __forceinline__ int xcd_block() {
+    const int nb = gridDim.x, b = blockIdx.x;
+    const int q = nb >> 3, r = nb & 7, x = b & 7, i = b >> 3;
+    return (x < r) ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
+}
 
 // Wave-aggregated atomic increment by runs: consecutive lanes with equal keys share one atomic,
 // and every run of the wave issues its atomic at once (one memory round trip per wave; particles
