@@ -207,6 +207,7 @@ LatticeGeom force_geom(const cola_problem& p, const Layout& L) {
     g.qoff = 0.5f;
     g.row = L.frow;
     g.mesh_bstride = L.fstride;
+    g.set_lattice();
     return g;
 }
 LatticeGeom dens_geom(const cola_problem& p, const Layout& L) {
@@ -650,6 +651,7 @@ int power_spectrum_impl(const cola_problem* prob, const cola_cosmology* cosmo, c
     dg.qoff = (float)(0.5 * (double)n_pk / (double)L.g.n);
     dg.row = 2L * gk.nzp;
     dg.mesh_bstride = 2L * L.kstride;
+    dg.set_lattice();
     double cells = (double)n_pk * n_pk * n_pk;
     SortBufs sb = carve_sort(w.sort, npr, L.tk, p.n_real);
     COLA_TRY(sorted_deposit(P, npr, p.n_real, dg, !on_node, fg, w.F, kd, L.tk, sb, reinterpret_cast<float*>(w.K),
@@ -738,6 +740,7 @@ int cola_power_multipoles(const cola_problem* prob, const cola_cosmology* cosmo,
     dg.qoff = (float)(0.5 * (double)n_pk / (double)L.g.n);
     dg.row = 2L * gk.nzp;
     dg.mesh_bstride = 2L * L.kstride;
+    dg.set_lattice();
     double cells = (double)n_pk * n_pk * n_pk;
     SortBufs sb = carve_sort(w.sort, npr, L.tk, p.n_real);
     COLA_TRY(sorted_deposit(P, npr, p.n_real, dg, redshift_space != 0, fg, w.F, kd, L.tk, sb,

@@ -185,6 +185,12 @@ struct LatticeGeom {
     float qoff;     // lattice offset in this mesh's cells (0.5 * n_mesh / N_g)
     long row;       // floats per mesh row (force meshes: per row of interleaved (x, y, z) cells)
     long mesh_bstride;  // floats between realizations
+    int pm = 0;         // cells per particle spacing where that is whole, else 0 (set_lattice)
+    float inv_np = 0.0f;  // 1 / N_p
+    void set_lattice() {
+        pm = n_mesh % n_part == 0 ? n_mesh / n_part : 0;
+        inv_np = 1.0f / (float)n_part;
+    }
 };
 
 struct KickDrift {

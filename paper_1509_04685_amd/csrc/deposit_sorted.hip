@@ -17,6 +17,7 @@
 
 #include "cola_internal.h"
 #include "force_gather.h"
+#include "lattice.h"
 #include "tile_pull.h"
 #include "wave_ops.h"
 
@@ -59,33 +60,6 @@ TileGeom make_tiles(int n, long n_particles) {
 
 namespace {
 
-struct CellC {
-    int m;
-    float f;
-};
-
-// 32-bit index arithmetic: i * n_mesh < 1536^2 and a lattice index < 1536^3 < 2^32.
-__device__ __forceinline__ CellC cell_c(int i, float x, int n_part, int n_mesh, float inv_h, float qoff) {
-    const uint32_t a = (uint32_t)i * (uint32_t)n_mesh;
-    const int q = (int)(a / (uint32_t)n_part);
-    const int rem = (int)(a - (uint32_t)q * (uint32_t)n_part);
-    float w = (float)rem / (float)n_part + qoff + x * inv_h;
-    float fl = floorf(w);
-    CellC c;
-    c.f = w - fl;
-    int m = (q + (int)fl) % n_mesh;
-    m = m < 0 ? m + n_mesh : m;
-    c.m = min(max(m, 0), n_mesh - 1);
-    return c;
-}
-
-__device__ __forceinline__ void lagr_idx(uint32_t p, int n_part, int& i, int& j, int& l) {
-    const uint32_t np = (uint32_t)n_part, np2 = np * np;
-    const uint32_t ii = p / np2, r = p - ii * np2, jj = r / np;
-    i = (int)ii;
-    j = (int)jj;
-    l = (int)(r - jj * np);
-}
 
 // The per-particle key and record arrays are written once and read once, in particle order:
 // non-temporal, so that they do not evict mesh and count lines from L2 (the tile pass also
@@ -114,15 +88,13 @@ template <int MODE>
 __global__ void __launch_bounds__(256) k_dep_bin(ParticlePtrs P, long npr, LatticeGeom dg, TileGeom tg,
                                                  LatticeGeom fg, const float* F, KickDrift kd, SortBufs sb) {
     constexpr bool DRIFT = MODE != 0;
-    const long p = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    const int r = blockIdx.y;
-    const bool valid = p < npr;
-    const long gid = (long)r * npr + p;
+    const LatticeSite site = lattice_site(dg);
+    const int r = blockIdx.z;
+    const bool valid = site.valid;
+    const long gid = (long)r * npr + site.p;
     uint32_t key = 0;
     float4 rec = make_float4(0.f, 0.f, 0.f, 0.f);
     if (valid) {
-        int idx[3];
-        lagr_idx((uint32_t)p, dg.n_part, idx[0], idx[1], idx[2]);
         float x[3];
 #pragma unroll
         for (int d = 0; d < 3; ++d) x[d] = __builtin_nontemporal_load(P.x[d] + gid);
@@ -143,9 +115,9 @@ __global__ void __launch_bounds__(256) k_dep_bin(ParticlePtrs P, long npr, Latti
             }
             float g[3] = {0.0f, 0.0f, 0.0f};
             if (kd.kick != 0.0f) {  // no force mesh is read for a pure drift (redshift-space mapping)
-                CellC c[3];
+                LatticeCell c[3];
 #pragma unroll
-                for (int d = 0; d < 3; ++d) c[d] = cell_c(idx[d], x[d], fg.n_part, fg.n_mesh, fg.inv_h, fg.qoff);
+                for (int d = 0; d < 3; ++d) c[d] = lattice_cell(fg, site.i[d], x[d]);
                 gather_interleaved(F + (long)r * fg.mesh_bstride, fg.row, fg.n_mesh, c[0].m, c[1].m, c[2].m, c[0].f,
                                    c[1].f, c[2].f, g);
             }
@@ -160,9 +132,9 @@ __global__ void __launch_bounds__(256) k_dep_bin(ParticlePtrs P, long npr, Latti
                 }
             }
         }
-        CellC c[3];
+        LatticeCell c[3];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) c[d] = cell_c(idx[d], x[d], dg.n_part, dg.n_mesh, dg.inv_h, dg.qoff);
+        for (int d = 0; d < 3; ++d) c[d] = lattice_cell(dg, site.i[d], x[d]);
         int local;
         key = tile_key(tg, c[0].m, c[1].m, c[2].m, local);
         rec = make_float4(__int_as_float(local), c[0].f, c[1].f, c[2].f);
@@ -181,7 +153,7 @@ __global__ void __launch_bounds__(256) k_dep_bin(ParticlePtrs P, long npr, Latti
 // 250^3 cells, 89 + 83 us with atomics in both and records in between, 74 + 25 us so; 1e7 uniform ones on
 // 200^3 1162 -> 864 us for the whole deposit.
 struct AbsCells {
-    CellC c[3];
+    LatticeCell c[3];
 };
 __device__ __forceinline__ AbsCells abs_cells(const float* px, const float* py, const float* pz, long p, int n_mesh,
                                               float inv_h) {
@@ -316,9 +288,29 @@ __global__ void k_dep_scatter(long npr, SortBufs sb) {
     if (valid) sb.sorted[(long)r * npr + slot] = rec;
 }
 
+// A CIC weight w in [0, 1] in 32.32 fixed point (rounded; a negative one, see above, is 0).
+__device__ __forceinline__ unsigned long long fixed_weight(float w) {
+    const float t = __builtin_rintf(fmaxf(w, 0.0f) * 4294967296.0f);
+    const bool whole = t >= 4294967296.0f;
+    return (unsigned long long)(whole ? 1u : 0u) << 32 | (whole ? 0u : (uint32_t)t);
+}
+
+// A 32.32 fixed-point sum as float, rounded once: its 32 leading bits, the last of them also set for any
+// bit below (round to nearest even of the conversion then sees them).
+__device__ __forceinline__ float mass_of(unsigned long long v) {
+    const uint32_t hi = (uint32_t)(v >> 32);
+    const int s = hi ? __clz((int)hi) : 32;
+    const unsigned long long t = v << s;
+    return ldexpf((float)((uint32_t)(t >> 32) | min((uint32_t)t, 1u)), -s);
+}
+
 // One block per tile: pull the records whose corners reach into the tile, accumulate in LDS,
 // write every cell of the tile once as delta = rho * scale + offset.  The 14 record ranges are
-// fetched in parallel first, then all threads sweep their concatenation.
+// fetched in parallel first, then all threads sweep their concatenation, the next record in flight
+// while one is added.  The pass is bound by the vector ALU as much as by its stores (1135
+// instructions per wave, 121 of 130 us, with 64-bit conversions of every weight and cell and 64-bit
+// addresses, on 256^3 cells and particles), hence 32-bit arithmetic for both: 121 us there; 653 -> 636 us for
+// 256^3 particles on 768^3 cells, where the chain of loads of a tile is longer than its arithmetic.
 __global__ void __launch_bounds__(256) k_dep_tile(TileGeom tg, SortBufs sb, long npr, float* mesh, long row,
                                                   long mesh_bstride, float scale, float offset) {
     // Cell masses accumulate as 32.32 fixed point in 64-bit integers: LDS integer atomics run at
@@ -334,7 +326,8 @@ __global__ void __launch_bounds__(256) k_dep_tile(TileGeom tg, SortBufs sb, long
     // The range bounds are requested first, so that their latency overlaps the LDS clear.
     uint32_t b, e;
     request_pulls(tg, tb, sb.start + (long)r * sb.kstride, b, e);
-    for (int i = threadIdx.x; i < ncell; i += blockDim.x) acc[i] = 0ull;
+    // 8 bytes per lane and store: with 16 the whole pass took 767 instead of 636 us on 768^3
+    for (int i = threadIdx.x; i < ncell; i += 256) acc[i] = 0ull;
     finish_pulls(pr, b, e);
     __syncthreads();
     const uint32_t total = pr.len[14];
@@ -346,50 +339,48 @@ __global__ void __launch_bounds__(256) k_dep_tile(TileGeom tg, SortBufs sb, long
     const uint32_t chunk = (total + blockDim.x - 1) / blockDim.x;
     const uint32_t i0 = threadIdx.x * chunk;
     const uint32_t i1 = min(total, i0 + chunk);
+    int dx = 0, dy = 0, dz = 0;
+    float4 next = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (i0 < i1) next = recs[pulled_record(pr, ps, i0, dx, dy, dz)];
     for (uint32_t i = i0; i < i1; ++i) {
-        int dx, dy, dz;
-        const float4 rec = recs[pulled_record(pr, ps, i, dx, dy, dz)];
+        const float4 rec = next;
         int hx, hy, hz;
         pulled_cell(tg, __float_as_int(rec.x), dx, dy, dz, hx, hy, hz);
+        if (i + 1 < i1) next = recs[pulled_record(pr, ps, i + 1, dx, dy, dz)];
         const float wx[2] = {1.0f - rec.y, rec.y}, wy[2] = {1.0f - rec.z, rec.z}, wz[2] = {1.0f - rec.w, rec.w};
+        const bool okx[2] = {hx >= 0, hx + 1 < tb.nx}, oky[2] = {hy >= 0, hy + 1 < tb.ny}, okz[2] = {hz >= 0, hz + 1 < tb.nz};
+        const int cell0 = ((hx << tg.ly) + hy) * (1 << tg.lz) + hz;  // of the lower corner (an index, not yet a cell)
 #pragma unroll
-        for (int cx = 0; cx < 2; ++cx) {
-            const int ux = hx + cx;
-            if (ux < 0 || ux >= tb.nx) continue;
+        for (int cx = 0; cx < 2; ++cx)
 #pragma unroll
             for (int cy = 0; cy < 2; ++cy) {
-                const int uy = hy + cy;
-                if (uy < 0 || uy >= tb.ny) continue;
-#pragma unroll
-                for (int cz = 0; cz < 2; ++cz) {
-                    const int uz = hz + cz;
-                    if (uz < 0 || uz >= tb.nz) continue;
-                    // clamped at 0: the conversion of a negative weight would wrap to ~2^32
-                    atomicAdd(&acc[(((ux << tg.ly) + uy) << tg.lz) + uz],
-                              __float2ull_rn(fmaxf(wx[cx] * wy[cy] * wz[cz] * 4294967296.0f, 0.0f)));
-                }
+                if (!(okx[cx] && oky[cy])) continue;
+                const float wxy = wx[cx] * wy[cy];
+                const int c = cell0 + (((cx << tg.ly) + cy) << tg.lz);
+                if (okz[0]) atomicAdd(&acc[c], fixed_weight(wxy * wz[0]));
+                if (okz[1]) atomicAdd(&acc[c + 1], fixed_weight(wxy * wz[1]));
             }
-        }
     }
     __syncthreads();
-    float* out = mesh + (long)r * mesh_bstride;
-    const double unit = 2.3283064365386962890625e-10;  // 2^-32
-    auto cell = [&](int i) { return fmaf((float)((double)acc[i] * unit), scale, offset); };
+    float* out = mesh + (long)r * mesh_bstride + ((long)tb.x0 * tg.n + tb.y0) * row + tb.z0;
+    const uint32_t row32 = (uint32_t)row;  // offsets within a tile: below 8 1536 rows of 1568 floats
     if (((tg.tz | tg.n | (int)row) & 3) == 0) {  // rows of the tile are whole, aligned float4s
-        for (int i4 = threadIdx.x; i4 < (ncell >> 2); i4 += blockDim.x) {
+        for (int i4 = threadIdx.x; i4 < (ncell >> 2); i4 += 256) {
             const int i = i4 << 2;
             const int uz = i & (tg.tz - 1), uy = (i >> tg.lz) & (tg.ty - 1), ux = i >> (tg.lz + tg.ly);
             if (ux >= tb.nx || uy >= tb.ny || uz >= tb.nz) continue;
-            const long gx = (long)tb.x0 + ux, gy = (long)tb.y0 + uy, gz = (long)tb.z0 + uz;
-            const float4 a = make_float4(cell(i), cell(i + 1), cell(i + 2), cell(i + 3));
-            store_rec_stream(reinterpret_cast<float4*>(out + (gx * tg.n + gy) * row + gz), a);
+            const ulonglong2 u = reinterpret_cast<const ulonglong2*>(acc)[i >> 1],
+                             v = reinterpret_cast<const ulonglong2*>(acc)[(i >> 1) + 1];
+            const float4 a = make_float4(fmaf(mass_of(u.x), scale, offset), fmaf(mass_of(u.y), scale, offset),
+                                         fmaf(mass_of(v.x), scale, offset), fmaf(mass_of(v.y), scale, offset));
+            const uint32_t o = __umul24(__umul24(ux, tg.n) + uy, row32) + uz;
+            store_rec_stream(reinterpret_cast<float4*>(out + o), a);
         }
     } else {
-        for (int i = threadIdx.x; i < ncell; i += blockDim.x) {
+        for (int i = threadIdx.x; i < ncell; i += 256) {
             const int uz = i & (tg.tz - 1), uy = (i >> tg.lz) & (tg.ty - 1), ux = i >> (tg.lz + tg.ly);
             if (ux >= tb.nx || uy >= tb.ny || uz >= tb.nz) continue;
-            const long gx = (long)tb.x0 + ux, gy = (long)tb.y0 + uy, gz = (long)tb.z0 + uz;
-            out[(gx * tg.n + gy) * row + gz] = cell(i);
+            out[__umul24(__umul24(ux, tg.n) + uy, row32) + uz] = fmaf(mass_of(acc[i]), scale, offset);
         }
     }
 }
@@ -511,7 +502,7 @@ hipError_t sorted_deposit_absolute(const float* const pos[3], long n, int n_mesh
 hipError_t sorted_deposit(const ParticlePtrs& P, long npr, int n_real, const LatticeGeom& dg, bool drift,
                           const LatticeGeom& fg, const float* F, const KickDrift& kd, const TileGeom& tg,
                           const SortBufs& sb, float* mesh, float scale, float offset, hipStream_t st) {
-    const dim3 pgrid((unsigned)((npr + 255) / 256), n_real);
+    const dim3 pgrid = lattice_grid(dg.n_part, n_real);
     hipError_t e = launch_fill(reinterpret_cast<float*>(sb.count), sb.kstride * n_real, 0.0f, st);
     if (e != hipSuccess) return e;
     {
@@ -534,8 +525,7 @@ hipError_t gather_kick_drift_bin(const ParticlePtrs& P, long npr, int n_real, co
     KickDrift k = kd;
     k.los = -1;
     ProfScope ps(PROF_GKD, st);
-    hipLaunchKernelGGL(k_dep_bin<2>, dim3((unsigned)((npr + 255) / 256), n_real), dim3(256), 0, st, P, npr, dg, tg,
-                       fg, F, k, sb);
+    hipLaunchKernelGGL(k_dep_bin<2>, lattice_grid(dg.n_part, n_real), dim3(256), 0, st, P, npr, dg, tg, fg, F, k, sb);
     return hipGetLastError();
 }
 

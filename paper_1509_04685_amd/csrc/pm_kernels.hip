@@ -11,42 +11,14 @@
 
 #include "cola_internal.h"
 #include "force_gather.h"
+#include "lattice.h"
 
 namespace cola {
 
-struct Cell {
-    int m;    // lower node, wrapped into [0, n)
-    float f;  // fraction towards m + 1
-};
-
-// 32-bit index arithmetic throughout: i * n_mesh < 1536^2 and a lattice index < 1536^3 < 2^32
-// (64-bit divisions are long instruction sequences on this hardware).
-__device__ __forceinline__ Cell cell_of(int i, float x, int n_part, int n_mesh, float inv_h, float qoff) {
-    const uint32_t a = (uint32_t)i * (uint32_t)n_mesh;
-    const int q = (int)(a / (uint32_t)n_part);
-    const int rem = (int)(a - (uint32_t)q * (uint32_t)n_part);
-    float w = (float)rem / (float)n_part + qoff + x * inv_h;
-    float fl = floorf(w);
-    Cell c;
-    c.f = w - fl;
-    int m = (q + (int)fl) % n_mesh;
-    m = m < 0 ? m + n_mesh : m;
-    c.m = min(max(m, 0), n_mesh - 1);  // a non-finite position still maps inside the mesh
-    return c;
-}
-
 __device__ __forceinline__ int wrap1(int m, int n) { return m + 1 == n ? 0 : m + 1; }
 
-__device__ __forceinline__ void lagr_index(uint32_t p, int n_part, int& i, int& j, int& l) {
-    const uint32_t np = (uint32_t)n_part, np2 = np * np;
-    const uint32_t ii = p / np2, r = p - ii * np2, jj = r / np;
-    i = (int)ii;
-    j = (int)jj;
-    l = (int)(r - jj * np);
-}
-
-__device__ __forceinline__ void deposit8(float* mesh, long row, int n, const Cell& cx, const Cell& cy,
-                                         const Cell& cz) {
+__device__ __forceinline__ void deposit8(float* mesh, long row, int n, const LatticeCell& cx, const LatticeCell& cy,
+                                         const LatticeCell& cz) {
     const int xs[2] = {cx.m, wrap1(cx.m, n)}, ys[2] = {cy.m, wrap1(cy.m, n)}, zs[2] = {cz.m, wrap1(cz.m, n)};
     const float wx[2] = {1.0f - cx.f, cx.f}, wy[2] = {1.0f - cy.f, cy.f}, wz[2] = {1.0f - cz.f, cz.f};
 #pragma unroll
@@ -116,7 +88,7 @@ __global__ void k_deposit_abs(const float* px, const float* py, const float* pz,
                               float inv_h, long row, float* mesh) {
     long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (gid >= n) return;
-    Cell c[3];
+    LatticeCell c[3];
     const float* ps[3] = {px, py, pz};
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
@@ -184,12 +156,12 @@ __device__ __forceinline__ float bracket(float g, float d1, float d2m, float s1,
 // particle set could alias as far as the compiler knows, which would otherwise order them).  The
 // particle streams are non-temporal, leaving L2 to the force-mesh lines that neighbouring
 // particles share.
-__global__ void __launch_bounds__(256) k_gather_kick_drift(ParticlePtrs P, uint32_t npr, LatticeGeom fg,
+__global__ void __launch_bounds__(256) k_gather_kick_drift(ParticlePtrs P, long npr, LatticeGeom fg,
                                                            const float* F, KickDrift kd) {
-    const uint32_t p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= npr) return;
-    const int r = blockIdx.y;
-    const long gid = (long)r * npr + p;
+    const LatticeSite site = lattice_site(fg);
+    if (!site.valid) return;
+    const int r = blockIdx.z;
+    const long gid = (long)r * npr + site.p;
     float x[3], pv[3], s1[3], s2[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) x[d] = __builtin_nontemporal_load(P.x[d] + gid);
@@ -202,11 +174,9 @@ __global__ void __launch_bounds__(256) k_gather_kick_drift(ParticlePtrs P, uint3
         s1[d] = __builtin_nontemporal_load(P.psi1[d] + gid);
         s2[d] = __builtin_nontemporal_load(P.psi2[d] + gid);
     }
-    int idx[3];
-    lagr_index((uint32_t)p, fg.n_part, idx[0], idx[1], idx[2]);
-    Cell c[3];
+    LatticeCell c[3];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) c[d] = cell_of(idx[d], x[d], fg.n_part, fg.n_mesh, fg.inv_h, fg.qoff);
+    for (int d = 0; d < 3; ++d) c[d] = lattice_cell(fg, site.i[d], x[d]);
     float g[3];
     gather_interleaved(F + r * fg.mesh_bstride, fg.row, fg.n_mesh, c[0].m, c[1].m, c[2].m, c[0].f, c[1].f, c[2].f,
                        g);
@@ -222,21 +192,19 @@ __global__ void __launch_bounds__(256) k_gather_kick_drift(ParticlePtrs P, uint3
 hipError_t gather_kick_drift(const ParticlePtrs& P, long npr, int n_real, const LatticeGeom& fg, const float* F,
                              const KickDrift& kd, hipStream_t st) {
     ProfScope ps((kd.drift != 0.0f || kd.dd1 != 0.0f) ? PROF_GKD : PROF_KICK, st);
-    hipLaunchKernelGGL(k_gather_kick_drift, dim3((unsigned)((npr + 255) / 256), n_real), dim3(256), 0, st, P,
-                       (uint32_t)npr, fg, F, kd);
+    hipLaunchKernelGGL(k_gather_kick_drift, lattice_grid(fg.n_part, n_real), dim3(256), 0, st, P, npr, fg, F, kd);
     return hipGetLastError();
 }
 
-__global__ void k_gather_force(ParticlePtrs P, long npr, int n_real, LatticeGeom fg, const float* F, float* ax,
-                               float* ay, float* az) {
-    long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= npr * n_real) return;
-    long r = gid / npr, p = gid - r * npr;
-    int idx[3];
-    lagr_index((uint32_t)p, fg.n_part, idx[0], idx[1], idx[2]);
-    Cell c[3];
+__global__ void __launch_bounds__(256) k_gather_force(ParticlePtrs P, long npr, LatticeGeom fg, const float* F, float* ax,
+                                                      float* ay, float* az) {
+    const LatticeSite site = lattice_site(fg);
+    if (!site.valid) return;
+    const int r = blockIdx.z;
+    const long gid = (long)r * npr + site.p;
+    LatticeCell c[3];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) c[d] = cell_of(idx[d], P.x[d][gid], fg.n_part, fg.n_mesh, fg.inv_h, fg.qoff);
+    for (int d = 0; d < 3; ++d) c[d] = lattice_cell(fg, site.i[d], P.x[d][gid]);
     float g[3];
     gather_interleaved(F + r * fg.mesh_bstride, fg.row, fg.n_mesh, c[0].m, c[1].m, c[2].m, c[0].f, c[1].f, c[2].f,
                        g);
@@ -247,10 +215,9 @@ __global__ void k_gather_force(ParticlePtrs P, long npr, int n_real, LatticeGeom
 
 hipError_t gather_force(const ParticlePtrs& P, long npr, int n_real, const LatticeGeom& fg, const float* F,
                         float* const acc[3], hipStream_t st) {
-    long n = npr * n_real;
     ProfScope ps(PROF_GATHER, st);
-    hipLaunchKernelGGL(k_gather_force, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, P, npr, n_real,
-                       fg, F, acc[0], acc[1], acc[2]);
+    hipLaunchKernelGGL(k_gather_force, lattice_grid(fg.n_part, n_real), dim3(256), 0, st, P, npr, fg, F, acc[0], acc[1],
+                       acc[2]);
     return hipGetLastError();
 }
 
