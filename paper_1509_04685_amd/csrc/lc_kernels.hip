@@ -93,6 +93,14 @@ constexpr int TV = TX * TY * TZ;
 
 __device__ __forceinline__ int wrap_halo(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
+// Vectors per row of the staged weights: the K steps' 8-channel groups, made odd so that the 16 rows
+// that a fragment reads start in different banks.
+constexpr int conv_weight_row(int cinp) { return ((27 * cinp + 31) / 32 * 4) | 1; }
+// Up to 16 channels in and out a lane's weights (one vector per K step) stay in its registers.
+constexpr bool conv_weights_in_registers(int cinp, int nb) { return nb == 1 && cinp <= 16; }
+// A tap's place in the halo, relative to tap 0 of the same voxel.
+constexpr int tap_place(int tap) { return ((tap / 9) * HY + (tap / 3) % 3) * HZ + tap % 3; }
+
 enum { EPI_ZA = 0, EPI_A = 1, EPI_DSILU = 2, EPI_OUT = 3, EPI_OUT_STORE = 4 };
 
 // Inputs of the first layer taken straight from the step's fields (instead of a packed X0):
@@ -116,26 +124,29 @@ struct OutDst {
     int zs = 1;
 };
 
-// The halo of tile `tile` (one voxel, all its C8 vectors of channels, per thread and k) into
-// registers, for the tile after the one being computed.
+constexpr int HK = (HVOX + 255) / 256;  // halo voxels of a thread: tid + 256 k
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));  // a register quad (uint4 is a struct)
-template <int HK, int C8>
-__device__ __forceinline__ void load_halo_regs(u32x4 (&h)[HK][C8], const uint4* __restrict__ ing, int tile, int n,
-                                               int nty, int ntz, int tid) {
-    const int tz = tile % ntz, ty = (tile / ntz) % nty, tx = tile / (ntz * nty);
+
+// Where this thread's halo voxels lie relative to a tile's first voxel, and where a tile lies; `voxel` is the
+// index of halo voxel k of the tile at (x0, y0, z0) in the periodic mesh.
+struct HaloPlace {
+    int hx[HK], hy[HK], hz[HK];
+    int n, nty, ntz;
+    int x0, y0, z0;
+    __device__ __forceinline__ HaloPlace(int n_, int tid) : n(n_), nty(n_ / TY), ntz(n_ / TZ), x0(0), y0(0), z0(0) {
 #pragma unroll
-    for (int k = 0; k < HK; ++k) {
-        const int hv = tid + k * 256;
-        if (hv < HVOX) {
-            const int hz = hv % HZ, hy = (hv / HZ) % HY, hx = hv / (HZ * HY);
-            const int gx = wrap_halo(tx * TX + hx - 1, n), gy = wrap_halo(ty * TY + hy - 1, n);
-            const int gz = wrap_halo(tz * TZ + hz - 1, n);
-            const uint4* src = ing + (((long)gx * n + gy) * n + gz) * C8;
-#pragma unroll
-            for (int c8 = 0; c8 < C8; ++c8) h[k][c8] = *reinterpret_cast<const u32x4*>(src + c8);
+        for (int k = 0; k < HK; ++k) {
+            const int hv = tid + k * 256;
+            hz[k] = hv % HZ - 1, hy[k] = (hv / HZ) % HY - 1, hx[k] = hv / (HZ * HY) - 1;
         }
     }
-}
+    __device__ __forceinline__ void go(int tile) {
+        const int row = tile / ntz;
+        z0 = (tile - row * ntz) * TZ, y0 = (row % nty) * TY, x0 = (row / nty) * TX;
+    }
+    __device__ __forceinline__ int row(int k) const { return wrap_halo(x0 + hx[k], n) * n + wrap_halo(y0 + hy[k], n); }
+    __device__ __forceinline__ long voxel(int k) const { return (long)row(k) * n + wrap_halo(z0 + hz[k], n); }
+};
 
 // out[v][co] = sum_tap sum_ci W[co][tap][ci] in[v + d_tap][ci] + bias[co], then
 //   EPI_ZA: out = Z, out2 = silu(Z);  EPI_A: out = silu(Z);  EPI_DSILU: out = Z * silu'(prev[v][co]).
@@ -144,76 +155,109 @@ __device__ __forceinline__ void load_halo_regs(u32x4 (&h)[HK][C8], const uint4* 
 //   EPI_OUT: the output layer, dF = (W3 silu(Z) + b3) * scale, added to the meshes of `od`;
 //   EPI_OUT_STORE: the same, stored instead of added.
 // FIELDS (first layer only, CINP = 8): the halo is built from `fs` instead of `in`.
-// At least three waves per SIMD, i.e. three blocks per CU (at most 168 VGPRs): with two, the
-// 16-channel layers left the matrix cores
-// and LDS idle through each tile's barriers (0.50 -> 0.41 ms per launch on 256^3); four would
-// spill the 16-channel output layer.
+// Bound by vector instructions, matrix instructions and LDS reads about equally (1370, 900 and 2200 cycles of the
+// 3550 that a tile takes a CU; more blocks, another tile order or longer operand pipelines change
+// nothing).  16 -> 16 channels with the output layer on 256^3: 509 us with operand addresses formed
+// per read, 422 with constant ones, 379 with the weights in registers, the weights as the
+// left operand (a lane then holds four channels of one voxel: one store, or one LDS vector, instead
+// of four), W3 through scalar loads and the halo's places formed once per block.  At least three waves
+// per SIMD (at most 168 VGPRs): with two, 0.50 instead of 0.41 ms.
 template <int CINP, int NB, int EPI, bool FIELDS = false>
 __global__ void __launch_bounds__(256, 3) k_conv3_mfma(const uint16_t* __restrict__ in, const uint16_t* __restrict__ w,
                                                     const float* __restrict__ bias, uint16_t* out, uint16_t* out2,
-                                                    const uint16_t* __restrict__ prev, int n, int tiles, FieldSrc fs,
-                                                    OutDst od) {
+                                                    const uint16_t* __restrict__ prev, int n, int tiles,
+                                                    const float* __restrict__ w3, const float* __restrict__ b3,
+                                                    FieldSrc fs, OutDst od) {
     constexpr int COP = 16 * NB;
     constexpr int KTOT = 27 * CINP;
     constexpr int KSTEPS = (KTOT + 31) / 32;
-    constexpr int KUNROLL = NB == 1 ? 2 : KSTEPS;
     constexpr int C8 = CINP / 8;
+    constexpr int WS = conv_weight_row(CINP);
+    constexpr bool WREG = conv_weights_in_registers(CINP, NB);
     extern __shared__ uint4 smem[];
-    uint4* sw = smem;                      // weights, COP * 27 * C8 vectors
-    uint4* sh = smem + COP * 27 * C8;      // halo, HVOX * C8 vectors
+    uint4* sw = smem;                            // weights, COP rows of WS vectors (none with WREG)
+    uint4* sh = smem + (WREG ? 0 : COP * WS);    // halo, HVOX * C8 vectors
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint4* wg = reinterpret_cast<const uint4*>(w);
-    for (int i = tid; i < COP * 27 * C8; i += 256) sw[i] = wg[i];
-    const int nty = n / TY, ntz = n / TZ;
     const int m = lane & 15, kb = lane >> 4;
+    const uint4* wg = reinterpret_cast<const uint4*>(w);
+    Frag8 wreg[WREG ? KSTEPS : 1];
+    if constexpr (WREG) {
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks)
+            wreg[ks].u = ks * 4 + kb < 27 * C8 ? wg[m * 27 * C8 + ks * 4 + kb] : make_uint4(0, 0, 0, 0);
+    } else {
+        for (int i = tid; i < COP * WS; i += 256) {
+            const int co = i / WS, v = i - co * WS;
+            sw[i] = v < 27 * C8 ? wg[co * 27 * C8 + v] : make_uint4(0, 0, 0, 0);
+        }
+    }
+    const uint4* const aw = sw + m * WS + kb;
+    // K step ks of lane (m, kb) holds channels (32 ks + 8 kb) % CINP .. + 7 of tap t = (32 ks + 8 kb) / CINP.  The taps'
+    // places in the halo are constants, so a read is a lane's base plus an immediate: with 16
+    // channels the lanes of the upper half (kb >= 2) take tap 2 ks + 1, which lies at one of three
+    // distances from tap 2 ks (the next z, row or plane), each with its base; with 8 the four taps
+    // of a step have their places in toff.  Formed anew for each step and row, these addresses were
+    // most of the pass's vector instructions.  Taps past the last read their lane's own last place and
+    // meet zeros on both sides.
+    const uint4* const corner = sh + ((wave * HY) * HZ + m) * C8 + kb % C8;
+    const uint4* const base_z = corner + (kb >= C8 ? tap_place(1) * C8 : 0);
+    const uint4* const base_y = corner + (kb >= C8 ? (tap_place(3) - tap_place(2)) * C8 : 0);
+    const uint4* const base_x = corner + (kb >= C8 ? (tap_place(9) - tap_place(8)) * C8 : 0);
+    int toff[C8 == 1 ? KSTEPS : 1];
+    if constexpr (C8 == 1)
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) toff[ks] = tap_place(min(ks * 4 + kb, 26));
+    const bool past = (KSTEPS - 1) * 32 + kb * 8 >= KTOT;  // this lane's last step is past the last tap
     const uint4* ing = reinterpret_cast<const uint4*>(in);
     // Up to 16 input channels the next tile's halo is requested into registers while the current
     // tile is computed (one halo voxel, all its channels, per thread and k), so a tile's loads no
     // longer stand between its barrier and its matrix-core loop.
-    constexpr int HK = (HVOX + 255) / 256;
     constexpr bool PREFETCH = !FIELDS && C8 <= 2;
     constexpr int PK = PREFETCH ? HK : 1, PC = PREFETCH ? C8 : 1;
     u32x4 hreg[PK][PC];
-    if constexpr (PREFETCH)
-        if ((int)blockIdx.x < tiles) load_halo_regs<PK, PC>(hreg, ing, blockIdx.x, n, nty, ntz, tid);
+    HaloPlace at(n, tid);
+    auto request = [&] {
+#pragma unroll
+        for (int k = 0; k < PK; ++k)
+            if (tid + k * 256 < HVOX) {
+                const uint4* src = ing + at.voxel(k) * C8;
+#pragma unroll
+                for (int c8 = 0; c8 < PC; ++c8) hreg[k][c8] = *reinterpret_cast<const u32x4*>(src + c8);
+            }
+    };
+    if ((int)blockIdx.x < tiles) at.go(blockIdx.x);
+    if constexpr (PREFETCH) request();
     for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-        const int tz = tile % ntz, ty = (tile / ntz) % nty, tx = tile / (ntz * nty);
-        const int x0 = tx * TX, y0 = ty * TY, z0 = tz * TZ;
+        const int x0 = at.x0, y0 = at.y0, z0 = at.z0;
         const int y0v = y0;
         __syncthreads();  // the previous tile's readers are done with the halo
-        if constexpr (PREFETCH) {
-#pragma unroll
-            for (int k = 0; k < PK; ++k) {
-                const int hv = tid + k * 256;
-                if (hv < HVOX)
-#pragma unroll
-                    for (int c8 = 0; c8 < PC; ++c8) *reinterpret_cast<u32x4*>(sh + hv * C8 + c8) = hreg[k][c8];
-            }
-        } else
 #pragma unroll
         for (int k = 0; k < HK; ++k) {  // one halo voxel (all its channels) per thread
             const int hv = tid + k * 256;
             if (hv < HVOX) {
-                const int hz = hv % HZ, hy = (hv / HZ) % HY, hx = hv / (HZ * HY);
-                const int gx = wrap_halo(x0 + hx - 1, n), gy = wrap_halo(y0 + hy - 1, n);
-                const int gz = wrap_halo(z0 + hz - 1, n);
-                if constexpr (FIELDS) {
+                if constexpr (PREFETCH) {
+#pragma unroll
+                    for (int c8 = 0; c8 < PC; ++c8) *reinterpret_cast<u32x4*>(sh + hv * C8 + c8) = hreg[k][c8];
+                } else if constexpr (FIELDS) {
                     static_assert(C8 == 1, "field input has 4 channels (padded to 8)");
-                    const long v = ((long)gx * n + gy) * n + gz;
-                    const long o = ((long)gx * n + gy) * fs.row + (long)gz * fs.zs;
+                    const int gz = wrap_halo(at.z0 + at.hz[k], n);
+                    const long v = at.voxel(k);
+                    const long o = at.row(k) * fs.row + (long)gz * fs.zs;
                     // a channel with a zero input scale is not read (a density-only network)
                     const float g0 = fs.s[0] != 0.0f ? fs.g[0][o] * fs.s[0] : 0.0f;
                     const float g1 = fs.s[1] != 0.0f ? fs.g[1][o] * fs.s[1] : 0.0f;
                     const float g2 = fs.s[2] != 0.0f ? fs.g[2][o] * fs.s[2] : 0.0f;
                     sh[hv] = make_uint4(fs.d0[v] | (f2bf(g0) << 16), f2bf(g1) | (f2bf(g2) << 16), 0u, 0u);
                 } else {
-                    const uint4* src = ing + (((long)gx * n + gy) * n + gz) * C8;
+                    const uint4* src = ing + at.voxel(k) * C8;
 #pragma unroll
                     for (int c8 = 0; c8 < C8; ++c8) sh[hv * C8 + c8] = src[c8];
                 }
             }
         }
         __syncthreads();
+        const bool more = tile + (int)gridDim.x < tiles;
+        if (more) at.go(tile + gridDim.x);
         // the output layer's force-mesh values are requested first, the next halo after them (loads
         // complete in order, so the epilogue does not wait for the halo)
         constexpr bool FO_EARLY = EPI == EPI_OUT && NB == 1;  // 32 channels: no registers to spare
@@ -226,45 +270,42 @@ __global__ void __launch_bounds__(256, 3) k_conv3_mfma(const uint16_t* __restric
             for (int c = 0; c < 3; ++c) fo[c] = od.f[c][fo_off];
         }
         if constexpr (PREFETCH)
-            if (tile + (int)gridDim.x < tiles) load_halo_regs<PK, PC>(hreg, ing, tile + gridDim.x, n, nty, ntz, tid);
+            if (more) request();
         f32x4 acc[4][NB];
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
             for (int b = 0; b < NB; ++b) acc[r][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-        // 16-channel layers: unrolled by two, which leaves the registers for the prefetched halo
-        // (fully unrolled they needed 150-168)
-#pragma unroll KUNROLL
+#pragma unroll
         for (int ks = 0; ks < KSTEPS; ++ks) {
-            const int k = ks * 32 + kb * 8;
-            const int tap = k / CINP, c0 = k % CINP;
             Frag8 bf[NB], af[4];
-            if (tap < 27) {
-                const int dx = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dz = tap % 3 - 1;
+            const bool zero = ks == KSTEPS - 1 && KTOT % 32 != 0 && past;
+            const int tap = ks * 4 / C8;  // of the lanes kb < C8
+            const uint4* av;
+            if (C8 == 1) av = corner + toff[C8 == 1 ? ks : 0];
+            else if (C8 == 4 || tap == 26) av = corner + tap_place(tap) * C8;
+            else av = (tap % 9 == 8 ? base_x : tap % 3 == 2 ? base_y : base_z) + tap_place(tap) * C8;
 #pragma unroll
-                for (int b = 0; b < NB; ++b) bf[b].u = sw[((b * 16 + m) * 27 + tap) * C8 + c0 / 8];
+            for (int b = 0; b < NB; ++b) bf[b].u = WREG ? wreg[WREG ? ks : 0].u : aw[b * 16 * WS + ks * 4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int hv = ((wave + 1 + dx) * HY + (r + 1 + dy)) * HZ + (m + 1 + dz);
-                    af[r].u = sh[hv * C8 + c0 / 8];
-                }
-            } else {
-#pragma unroll
-                for (int b = 0; b < NB; ++b) bf[b].u = make_uint4(0, 0, 0, 0);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) af[r].u = make_uint4(0, 0, 0, 0);
+            for (int r = 0; r < 4; ++r) {
+                af[r].u = av[r * HZ * C8];
+                if (zero) af[r].u = make_uint4(0, 0, 0, 0);
             }
 #pragma unroll
             for (int r = 0; r < 4; ++r)
 #pragma unroll
                 for (int b = 0; b < NB; ++b)
-                    acc[r][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[r].v, bf[b].v, acc[r][b], 0, 0, 0);
+                    acc[r][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[b].v, af[r].v, acc[r][b], 0, 0, 0);
+            // two steps' operands in flight at a time: more would take the registers of a third wave per SIMD
+            if (ks & 1) __builtin_amdgcn_sched_barrier(0);
         }
-        // lane holds voxels z0 + 4 kb + q of the row, output channel co = 16 b + m
+        // lane holds output channels 16 b + 4 kb + q of voxel z0 + m of the row (the weights are the left
+        // operand): four neighbouring channels, so they leave in one store
         if constexpr (EPI == EPI_OUT || EPI == EPI_OUT_STORE) {
-            // A2 (rounded to BF16 as in the stored-activation path) goes to LDS as [voxel][COP + 1]
+            // A2 (rounded to BF16 as in the stored-activation path) goes to LDS as [voxel][COP + 4]
             // floats in the halo's space; then one thread per voxel forms the three outputs
-            constexpr int SP = COP + 1;
+            constexpr int SP = COP + 4;
             static_assert(TV * SP * 4 <= HVOX * CINP * 2, "staging must fit in the halo space");
             float* stage = reinterpret_cast<float*>(sh);
             __syncthreads();  // every wave is done reading the halo
@@ -272,20 +313,23 @@ __global__ void __launch_bounds__(256, 3) k_conv3_mfma(const uint16_t* __restric
             for (int r = 0; r < 4; ++r)
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
-                    const float bb = bias[b * 16 + m];
+                    f32x4 a;
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
-                        stage[((wave * 4 + r) * 16 + 4 * kb + q) * SP + b * 16 + m] =
-                            bf2f(f2bf(silu_f(acc[r][b][q] + bb)));
+                        a[q] = bf2f(f2bf(silu_f(acc[r][b][q] + bias[b * 16 + 4 * kb + q])));
+                    *reinterpret_cast<f32x4*>(stage + ((wave * 4 + r) * 16 + m) * SP + b * 16 + 4 * kb) = a;
                 }
             __syncthreads();
-            float y0 = od.b3[0], y1 = od.b3[1], y2 = od.b3[2];
+            float y0 = b3[0], y1 = b3[1], y2 = b3[2];
 #pragma unroll
-            for (int co = 0; co < COP; ++co) {
-                const float a = stage[tid * SP + co];
-                y0 += od.w3[co] * a;
-                y1 += od.w3[COP + co] * a;
-                y2 += od.w3[2 * COP + co] * a;
+            for (int c4 = 0; c4 < COP; c4 += 4) {
+                const f32x4 a = *reinterpret_cast<const f32x4*>(stage + tid * SP + c4);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    y0 += w3[c4 + q] * a[q];
+                    y1 += w3[COP + c4 + q] * a[q];
+                    y2 += w3[2 * COP + c4 + q] * a[q];
+                }
             }
             if constexpr (EPI == EPI_OUT_STORE) {
                 const int lx = tid >> 6, ly = (tid >> 4) & 3, lz = tid & 15;  // voxel tid of the tile
@@ -308,24 +352,28 @@ __global__ void __launch_bounds__(256, 3) k_conv3_mfma(const uint16_t* __restric
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const long vrow = ((long)(x0 + wave) * n + (y0 + r)) * n + z0 + 4 * kb;
+            const long o0 = (((long)(x0 + wave) * n + (y0 + r)) * n + z0 + m) * COP + 4 * kb;
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                const int co = b * 16 + m;
-                const float bb = bias ? bias[co] : 0.0f;
+                const long o = o0 + b * 16;
+                uint2 pv = make_uint2(0, 0);
+                if (EPI == EPI_DSILU) pv = *reinterpret_cast<const uint2*>(prev + o);
+                uint32_t t[4], t2[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const long o = (vrow + q) * COP + co;
-                    const float z = acc[r][b][q] + bb;
+                    const float z = acc[r][b][q] + (bias ? bias[b * 16 + 4 * kb + q] : 0.0f);
                     if (EPI == EPI_ZA) {
-                        out[o] = (uint16_t)f2bf(z);
-                        out2[o] = (uint16_t)f2bf(silu_f(z));
+                        t[q] = f2bf(z);
+                        t2[q] = f2bf(silu_f(z));
                     } else if (EPI == EPI_A) {
-                        out[o] = (uint16_t)f2bf(silu_f(z));
+                        t[q] = f2bf(silu_f(z));
                     } else {
-                        out[o] = (uint16_t)f2bf(z * silu_g(bf2f(prev[o])));
+                        t[q] = f2bf(z * silu_g(bf2f((q < 2 ? pv.x : pv.y) >> (q & 1 ? 16 : 0))));
                     }
                 }
+                *reinterpret_cast<uint2*>(out + o) = make_uint2(t[0] | (t[1] << 16), t[2] | (t[3] << 16));
+                if (EPI == EPI_ZA)
+                    *reinterpret_cast<uint2*>(out2 + o) = make_uint2(t2[0] | (t2[1] << 16), t2[2] | (t2[3] << 16));
             }
         }
     }
@@ -334,7 +382,9 @@ __global__ void __launch_bounds__(256, 3) k_conv3_mfma(const uint16_t* __restric
 // The first layer of a density-only network (the force channels' input scales are zero): the
 // only input channel is the BF16 density d0 [V], so K = 27 taps (padded to 32) instead of 27 taps
 // x 8 channels -- one MFMA K step per output block instead of seven, six of which would multiply
-// zeros.  Lane (m, kb) takes taps 8 kb .. 8 kb + 7 of voxel m's row; the weights are channel 0 of
+// zeros.  Bound by vector instructions (half of them the logistic function); with a lane's four channels
+// in one store, the weights and bias in registers and the next halo on its way 197 -> 161 us on
+// 256^3.  Lane (m, kb) takes taps 8 kb .. 8 kb + 7 of voxel m's row; the weights are channel 0 of
 // the packed [16 NB][27][8] layer-1 weights, staged as [16 NB][32] (taps 27..31 zero).  Tiles,
 // halo and epilogue (A1 = silu(Z1)) as in k_conv3_mfma.
 template <int NB>
@@ -350,7 +400,6 @@ __global__ void __launch_bounds__(256, 3) k_conv3_dens(const uint16_t* __restric
         const int co = i >> 5, tap = i & 31;
         swh[i] = tap < 27 ? w[(co * 27 + tap) * 8] : (uint16_t)0;
     }
-    const int nty = n / TY, ntz = n / TZ;
     const int m = lane & 15, kb = lane >> 4;
     // halo offsets of this lane's eight taps relative to the voxel's own halo position (negative
     // for the lower neighbours); taps 27..31 are padding and read nothing
@@ -361,34 +410,50 @@ __global__ void __launch_bounds__(256, 3) k_conv3_dens(const uint16_t* __restric
         const int dx = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dz = tap % 3 - 1;
         toff[j] = (dx * HY + dy) * HZ + dz;
     }
-    for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-        const int tz = tile % ntz, ty = (tile / ntz) % nty, tx = tile / (ntz * nty);
-        const int x0 = tx * TX, y0 = ty * TY, z0 = tz * TZ;
-        __syncthreads();  // the previous tile's readers are done with the halo (and the weights are staged)
-        for (int hv = tid; hv < HVOX; hv += 256) {
-            const int hz = hv % HZ, hy = (hv / HZ) % HY, hx = hv / (HZ * HY);
-            const int gx = wrap_halo(x0 + hx - 1, n), gy = wrap_halo(y0 + hy - 1, n), gz = wrap_halo(z0 + hz - 1, n);
-            sh[hv] = d0[((long)gx * n + gy) * n + gz];
-        }
-        __syncthreads();
-        Frag8 bf[NB];
+    uint16_t next[HK];  // this thread's halo voxels of the next tile
+    HaloPlace at(n, tid);
+    auto request = [&] {
 #pragma unroll
-        for (int b = 0; b < NB; ++b) bf[b].u = sw[(b * 16 + m) * 4 + kb];
+        for (int k = 0; k < HK; ++k)
+            if (tid + k * 256 < HVOX) next[k] = d0[at.voxel(k)];
+    };
+    if ((int)blockIdx.x < tiles) at.go(blockIdx.x);
+    request();
+    __syncthreads();  // the weights are staged
+    Frag8 bf[NB];
+    f32x4 bb[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        bf[b].u = sw[(b * 16 + m) * 4 + kb];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) bb[b][q] = bias[b * 16 + 4 * kb + q];
+    }
+    for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        __syncthreads();  // the previous tile's readers are done with the halo
+#pragma unroll
+        for (int k = 0; k < HK; ++k)
+            if (tid + k * 256 < HVOX) sh[tid + k * 256] = next[k];
+        __syncthreads();
+        const long o0 = ((long)((at.x0 + wave) * n + at.y0) * n + at.z0 + m) * COP + 4 * kb;
+        if (tile + (int)gridDim.x < tiles) {
+            at.go(tile + gridDim.x);
+            request();
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int hv0 = ((wave + 1) * HY + (r + 1)) * HZ + (m + 1);
             Frag8 af;
 #pragma unroll
             for (int j = 0; j < 8; ++j) af.h[j] = kb * 8 + j < 27 ? sh[hv0 + toff[j]] : (uint16_t)0;
-            const long vrow = ((long)(x0 + wave) * n + (y0 + r)) * n + z0 + 4 * kb;
+            const long o = o0 + (long)r * n * COP;
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                const f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af.v, bf[b].v, f32x4{0.f, 0.f, 0.f, 0.f},
+                const f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[b].v, af.v, f32x4{0.f, 0.f, 0.f, 0.f},
                                                                           0, 0, 0);
-                const int co = b * 16 + m;
-                const float bb = bias[co];
+                uint32_t t[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) out[(vrow + q) * COP + co] = (uint16_t)f2bf(silu_f(acc[q] + bb));
+                for (int q = 0; q < 4; ++q) t[q] = f2bf(silu_f(acc[q] + bb[b][q]));
+                *reinterpret_cast<uint2*>(out + o + b * 16) = make_uint2(t[0] | (t[1] << 16), t[2] | (t[3] << 16));
             }
         }
     }
@@ -405,6 +470,11 @@ static hipError_t run_conv_dens(const uint16_t* d0, const uint16_t* w, const flo
     return hipGetLastError();
 }
 
+// Blocks of a convolution: as many as run at a time (256 CUs, three each), so that a block's weights and
+// first halo, which nothing hides, come once (4096 blocks: 73 instead of 62 us for a 128^3 layer
+// of two tiles per block, the same on 256^3).
+constexpr long kConvBlocks = 768;
+
 static long conv_tiles(int n) { return (long)(n / TX) * (n / TY) * (n / TZ); }
 
 template <int CINP, int NB, int EPI, bool FIELDS = false>
@@ -412,12 +482,13 @@ static hipError_t run_conv(const uint16_t* in, const uint16_t* w, const float* b
                            const uint16_t* prev, int n, hipStream_t st, const FieldSrc& fs = FieldSrc{},
                            const OutDst& od = OutDst{}) {
     const long tiles = conv_tiles(n);
-    const size_t lds = (size_t)16 * NB * 27 * CINP * 2 + (size_t)HVOX * CINP * 2;
+    const size_t weights = conv_weights_in_registers(CINP, NB) ? 0 : (size_t)16 * NB * conv_weight_row(CINP) * 16;
+    const size_t lds = weights + (size_t)HVOX * CINP * 2;
     auto kern = k_conv3_mfma<CINP, NB, EPI, FIELDS>;
     if (hipError_t e = allow_lds_lc(kern, lds); e != hipSuccess) return e;
     ProfScope ps(PROF_LC_CONV, st, CINP);  // tag: input channels (padded)
-    hipLaunchKernelGGL(kern, dim3((unsigned)std::min<long>(tiles, 4096)), dim3(256), lds, st, in, w, bias, out, out2,
-                       prev, n, (int)tiles, fs, od);
+    hipLaunchKernelGGL(kern, dim3((unsigned)std::min<long>(tiles, kConvBlocks)), dim3(256), lds, st, in, w, bias, out, out2,
+                       prev, n, (int)tiles, od.w3, od.b3, fs, od);
     return hipGetLastError();
 }
 
