@@ -287,7 +287,7 @@ hipError_t compute_force(const cola_problem& p, const Layout& L, const Ws& w, co
     KickDrift none{};
     float* dens = reinterpret_cast<float*>(w.S);
     const float dscale = (float)(cells / (double)npr);
-    hipError_t e = binned ? sorted_deposit_binned(npr, p.n_real, dg, L.tg, sb, dens, dscale, -1.0f, st)
+    hipError_t e = binned ? sorted_deposit_binned(P, npr, p.n_real, dg, L.tg, sb, dens, dscale, -1.0f, st)
                           : sorted_deposit(P, npr, p.n_real, dg, false, dg, nullptr, none, L.tg, sb, dens, dscale,
                                            -1.0f, st);
     if (e != hipSuccess) return e;
@@ -365,7 +365,7 @@ int step_impl(const cola_problem* prob, const cola_cosmology* cosmo, int32_t j_b
         kd.dd1 = (float)(sc.d1[j + 1] - sc.d1[j]);
         kd.dd2 = (float)(sc.d2[j + 1] - sc.d2[j]);
         COLA_TRY(gather_kick_drift_bin(P, npr, p.n_real, fg, w.F, dg, frame_terms(kd, p), L.tg,
-                                       carve_sort(w.sort, npr, L.tg, p.n_real), st));
+                                       carve_sort(w.sort, npr, L.tg, p.n_real), j > j_begin || !cached, st));
         COLA_TRY(compute_force(p, L, w, P, st, lc, sc.a[j + 1], true));
         pending = sc.k_in[j];
     }

@@ -216,9 +216,10 @@ hipError_t gather_force(const ParticlePtrs& P, long n_per_real, int n_real, cons
                         const float* F, float* const acc[3], hipStream_t st);
 
 // Exclusive scan of nkeys counts: start[k] = sum of count[0..k), start[nkeys] = total (the sum,
-// known to the caller), cursor = start.  block_sums holds ceil(nkeys / 1024) entries.
-hipError_t scan_counts(const uint32_t* count, uint32_t* start, uint32_t* cursor, uint32_t* block_sums, long nkeys,
-                       uint32_t total, hipStream_t st);
+// known to the caller), cursor = start where it is not null; for n_real sets kstride (a multiple of 4)
+// apart, all arrays aligned to 16 bytes.  clear: the counts are left zero.  block_sums holds ceil(nkeys / 1024) entries per set.
+hipError_t scan_counts(uint32_t* count, uint32_t* start, uint32_t* cursor, uint32_t* block_sums, long nkeys,
+                       long kstride, int n_real, uint32_t total, bool clear, hipStream_t st);
 
 // ------------------------------------------------------------------ tiled deposit (deposit_sorted.hip)
 struct TileGeom {
@@ -230,15 +231,14 @@ struct TileGeom {
     long nkeys = 0;        // ntiles * 8 categories
 };
 struct SortBufs {
-    uint32_t* keys = nullptr;     // per particle
-    float4* recs = nullptr;       // per particle: (local cell bits, fx, fy, fz)
+    uint32_t* keys = nullptr;     // per particle: its rank in its key (drifted on the fly: the key)
+    float4* recs = nullptr;       // per particle drifted on the fly: (local cell bits, fx, fy, fz)
     float4* sorted = nullptr;     // records in key order
     uint32_t* count = nullptr;    // per key (per realization stride kstride)
     uint32_t* start = nullptr;    // exclusive prefix, nkeys + 1 entries
-    uint32_t* cursor = nullptr;
+    uint32_t* cursor = nullptr;   // next free slot of a key (drifted on the fly)
     uint32_t* block_sums = nullptr;
     long kstride = 0;
-    int nblocks = 0;
 };
 TileGeom make_tiles(int n, long n_particles);
 size_t sort_bytes(long n_particles_per_real, const TileGeom& tg, int n_real);
@@ -253,12 +253,13 @@ hipError_t sorted_deposit(const ParticlePtrs& P, long npr, int n_real, const Lat
 // The step's gather, kick and drift (as gather_kick_drift with a drift) fused with the binning of
 // the moved particles onto fg's mesh for the next force evaluation; sorted_deposit_binned then
 // finishes that deposit (sort and tile passes).  F: the interleaved force mesh, with the ghost
-// cells; dg: the geometry of the density mesh the particles are binned for.
+// cells; dg: the geometry of the density mesh the particles are binned for.  counts_zero: sb's counts
+// are zero, as a deposit leaves them.
 hipError_t gather_kick_drift_bin(const ParticlePtrs& P, long npr, int n_real, const LatticeGeom& fg, const float* F,
                                  const LatticeGeom& dg, const KickDrift& kd, const TileGeom& tg, const SortBufs& sb,
-                                 hipStream_t st);
-hipError_t sorted_deposit_binned(long npr, int n_real, const LatticeGeom& dg, const TileGeom& tg, const SortBufs& sb,
-                                 float* mesh, float scale, float offset, hipStream_t st);
+                                 bool counts_zero, hipStream_t st);
+hipError_t sorted_deposit_binned(const ParticlePtrs& P, long npr, int n_real, const LatticeGeom& dg, const TileGeom& tg,
+                                 const SortBufs& sb, float* mesh, float scale, float offset, hipStream_t st);
 // Rewrites the ghost cells (z = 0, 1 again at z = n, n + 1) of n_real interleaved force meshes with
 // `row` floats per row, after something other than the z c2r pass changed the meshes.
 hipError_t mesh_ghosts(float* F, long row, int n, long bstride, int n_real, hipStream_t st);

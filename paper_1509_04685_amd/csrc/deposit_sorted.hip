@@ -79,11 +79,15 @@ __device__ __forceinline__ float4 load_rec_stream(const float4* p) {
     return v;
 }
 
-// Binning of the particles onto the mesh of dg (key and cell record per particle, counts per
-// key).  MODE 0: at their positions; 1: drifted on the fly (kick with the force gathered from fg's
+// Binning of the particles onto the mesh of dg (counts per key).  MODE 0: at their positions; 1: drifted
+// on the fly (kick with the force gathered from fg's
 // meshes, then the drift of kd) without changing the state -- outputs between nodes and the
 // redshift-space mapping; 2: the step's gather, kick and drift, written back to p and x, then
 // binned at the new positions for the next force evaluation (dg = fg).
+// Modes 0 and 2 leave each particle's rank in its key, from which, with its position, k_dep_place
+// forms the record again: 4 bytes written and 16 read per particle instead of 20 and 20, and no
+// atomics in the second pass (256^3 particles and cells: 439 + 171 -> 390 + 142 us; both bound by their
+// memory traffic, the second by its scattered 16-byte stores).  The drifted positions of mode 1 are not kept, so it stores key and record.
 template <int MODE>
 __global__ void __launch_bounds__(256) k_dep_bin(ParticlePtrs P, long npr, LatticeGeom dg, TileGeom tg,
                                                  LatticeGeom fg, const float* F, KickDrift kd, SortBufs sb) {
@@ -93,7 +97,6 @@ __global__ void __launch_bounds__(256) k_dep_bin(ParticlePtrs P, long npr, Latti
     const bool valid = site.valid;
     const long gid = (long)r * npr + site.p;
     uint32_t key = 0;
-    float4 rec = make_float4(0.f, 0.f, 0.f, 0.f);
     if (valid) {
         float x[3];
 #pragma unroll
@@ -137,11 +140,29 @@ __global__ void __launch_bounds__(256) k_dep_bin(ParticlePtrs P, long npr, Latti
         for (int d = 0; d < 3; ++d) c[d] = lattice_cell(dg, site.i[d], x[d]);
         int local;
         key = tile_key(tg, c[0].m, c[1].m, c[2].m, local);
-        rec = make_float4(__int_as_float(local), c[0].f, c[1].f, c[2].f);
-        __builtin_nontemporal_store(key, sb.keys + gid);
-        store_rec_stream(sb.recs + gid, rec);
+        if (MODE == 1) {
+            __builtin_nontemporal_store(key, sb.keys + gid);
+            store_rec_stream(sb.recs + gid, make_float4(__int_as_float(local), c[0].f, c[1].f, c[2].f));
+        }
     }
-    (void)wave_increment(sb.count + (long)r * sb.kstride, key, valid);
+    const uint32_t rank = wave_increment(sb.count + (long)r * sb.kstride, key, valid);
+    if (MODE != 1 && valid) __builtin_nontemporal_store(rank, sb.keys + gid);
+}
+
+// The record of every particle at its key's start plus its rank.
+__global__ void __launch_bounds__(256) k_dep_place(ParticlePtrs P, long npr, LatticeGeom dg, TileGeom tg, SortBufs sb) {
+    const LatticeSite site = lattice_site(dg);
+    if (!site.valid) return;
+    const int r = blockIdx.z;
+    const long gid = (long)r * npr + site.p;
+    LatticeCell c[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) c[d] = lattice_cell(dg, site.i[d], __builtin_nontemporal_load(P.x[d] + gid));
+    const uint32_t rank = __builtin_nontemporal_load(sb.keys + gid);
+    int local;
+    const uint32_t key = tile_key(tg, c[0].m, c[1].m, c[2].m, local);
+    sb.sorted[(long)r * npr + sb.start[(long)r * sb.kstride + key] + rank] =
+        make_float4(__int_as_float(local), c[0].f, c[1].f, c[2].f);
 }
 
 // Absolute positions (the component entry points): the cell of a coordinate is floor(pos n / L) modulo
@@ -201,80 +222,128 @@ __global__ void __launch_bounds__(256) k_abs_scatter(const float* px, const floa
     sorted[start[key] + r] = make_float4(__int_as_float(local), a.c[0].f, a.c[1].f, a.c[2].f);
 }
 
-// Exclusive scan, phase 1: each block scans 1024 counts (4 per thread) and stores its total.
-__global__ void k_scan_blocks(const uint32_t* count, uint32_t* start, uint32_t* block_sums, long nkeys,
-                              long kstride, int nblocks) {
-    __shared__ uint32_t sh[256];
+// Exclusive scan of the key counts in at most two launches (three for more than 4096 blocks of keys).  At a
+// few microseconds a launch is what these passes cost on most meshes, so they are few: per block of 4096
+// keys one sum, then every block adds up the sums before it and scans its own keys; one block does all
+// where it can.  Blocks of 1024 keys, a pass for their sums and one to add them took three launches
+// on every mesh: 10 steps of 32^3 particles 1218 -> 1170 us; 16.8e6 cells of friends-of-friends 94 -> 35 us
+// (four-key vectors in rows of a wave; with a thread's 16 keys next to each other 210 us).
+constexpr int kScanKeys = 16;                     // keys of a thread: four of each of its wave's four rows of 256
+constexpr int kScanBlock = 256 * kScanKeys;       // keys of a block of 256
+constexpr int kScanOne = 1024 * kScanKeys;        // up to these, one block of 1024 threads
+constexpr int kScanSums = 4096;                   // up to these blocks, each adds up the sums before it
+
+__device__ __forceinline__ long scan_key(int row) {  // the thread's first key of a row (a multiple of 4)
+    return ((long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * (64 * kScanKeys) + row * 256 +
+           (threadIdx.x & 63) * 4;
+}
+__device__ __forceinline__ uint4 load_counts(const uint32_t* count, long k, long nkeys) {
+    if (k + 3 < nkeys) return *reinterpret_cast<const uint4*>(count + k);
+    return make_uint4(k < nkeys ? count[k] : 0u, k + 1 < nkeys ? count[k + 1] : 0u, k + 2 < nkeys ? count[k + 2] : 0u, 0u);
+}
+__device__ __forceinline__ void store_keys(uint32_t* out, long k, long nkeys, uint4 v) {
+    if (k + 3 < nkeys) {
+        *reinterpret_cast<uint4*>(out + k) = v;
+    } else {
+        if (k < nkeys) out[k] = v.x;
+        if (k + 1 < nkeys) out[k + 1] = v.y;
+        if (k + 2 < nkeys) out[k + 2] = v.z;
+    }
+}
+
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t s) {  // inclusive
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t t = __shfl_up(s, off);
+        s += lane >= off ? t : 0u;
+    }
+    return s;
+}
+
+// Sum over the earlier waves of the block (at most 16) of their s, the same in all lanes of a wave; `all` is the
+// block's sum.
+__device__ __forceinline__ uint32_t waves_before(uint32_t s, uint32_t& all) {
+    __shared__ uint32_t wave_sum[16];
+    const int wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    __syncthreads();  // an earlier use has been read
+    if ((threadIdx.x & 63) == 0) wave_sum[wave] = s;
+    __syncthreads();
+    uint32_t before = 0;
+    all = 0;
+    for (int w = 0; w < waves; ++w) {
+        before += w < wave ? wave_sum[w] : 0u;
+        all += wave_sum[w];
+    }
+    return before;
+}
+
+__global__ void __launch_bounds__(256) k_scan_sums(const uint32_t* count, uint32_t* sums, long nkeys, long kstride,
+                                                   int nblocks) {
+    const int r = blockIdx.y;
+    uint32_t s = 0, all;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint4 v = load_counts(count + (long)r * kstride, scan_key(j), nkeys);
+        s += v.x + v.y + v.z + v.w;
+    }
+    waves_before(__shfl(wave_prefix(s), 63), all);
+    if (threadIdx.x == 0) sums[(long)r * nblocks + blockIdx.x] = all;
+}
+
+// The block sums' exclusive prefix, in place (more than kScanSums blocks).
+__global__ void __launch_bounds__(1024) k_scan_totals(uint32_t* sums, int nblocks) {
+    sums += (long)blockIdx.y * nblocks;
+    const int per = (nblocks + 1023) / 1024;
+    const int b0 = min(nblocks, (int)threadIdx.x * per), b1 = min(nblocks, b0 + per);
+    uint32_t s = 0, all;
+    for (int b = b0; b < b1; ++b) s += sums[b];
+    const uint32_t incl = wave_prefix(s);
+    uint32_t run = waves_before(__shfl(incl, 63), all) + incl - s;
+    for (int b = b0; b < b1; ++b) {
+        const uint32_t v = sums[b];
+        sums[b] = run;
+        run += v;
+    }
+}
+
+// start[k] = sum of the counts before k, cursor[k] the same (null: not wanted), start[nkeys] = total; clear: the
+// counts become zero, for the next binning.  prefix: the sums are already prefixes.
+__global__ void __launch_bounds__(1024) k_scan_keys(uint32_t* count, uint32_t* start, uint32_t* cursor,
+                                                    const uint32_t* sums, bool prefix, bool clear, long nkeys,
+                                                    long kstride, int nblocks, uint32_t total) {
     const int r = blockIdx.y;
     count += (long)r * kstride;
     start += (long)r * kstride;
-    block_sums += (long)r * nblocks;
-    const long base = (long)blockIdx.x * 1024 + threadIdx.x * 4;
-    uint32_t v[4], s = 0;
+    sums += (long)r * nblocks;
+    uint4 v[4];
+    uint32_t incl[4], sum = 0, base = 0, all;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        v[i] = (base + i < nkeys) ? count[base + i] : 0u;
-        s += v[i];
+    for (int j = 0; j < 4; ++j) v[j] = load_counts(count, scan_key(j), nkeys);
+    if (prefix) {
+        base = sums[blockIdx.x];
+    } else if (blockIdx.x > 0) {
+        uint32_t s = 0;
+        for (int b = threadIdx.x; b < (int)blockIdx.x; b += blockDim.x) s += sums[b];
+        waves_before(__shfl(wave_prefix(s), 63), base);
     }
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {  // Hillis-Steele inclusive scan of thread sums
-        uint32_t t = threadIdx.x >= off ? sh[threadIdx.x - off] : 0u;
-        __syncthreads();
-        sh[threadIdx.x] += t;
-        __syncthreads();
-    }
-    uint32_t run = sh[threadIdx.x] - s;  // exclusive prefix of this thread
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (base + i < nkeys) start[base + i] = run;
-        run += v[i];
+    for (int j = 0; j < 4; ++j) {
+        incl[j] = wave_prefix(v[j].x + v[j].y + v[j].z + v[j].w);
+        sum += __shfl(incl[j], 63);
     }
-    if (threadIdx.x == 255) block_sums[blockIdx.x] = sh[255];
-}
-
-// Phase 2: one block scans the block totals (up to 8192) in place, exclusive.
-__global__ void k_scan_totals(uint32_t* block_sums, int nblocks) {
-    __shared__ uint32_t sh[1024];
-    const int r = blockIdx.y;
-    block_sums += (long)r * nblocks;
-    const int per = (nblocks + 1023) / 1024;
-    const int b0 = threadIdx.x * per;
-    uint32_t s = 0;
-    for (int i = 0; i < per; ++i)
-        if (b0 + i < nblocks) s += block_sums[b0 + i];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        uint32_t t = threadIdx.x >= off ? sh[threadIdx.x - off] : 0u;
-        __syncthreads();
-        sh[threadIdx.x] += t;
-        __syncthreads();
+    uint32_t row = base + waves_before(sum, all);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const long k = scan_key(j);
+        const uint32_t a = row + incl[j] - (v[j].x + v[j].y + v[j].z + v[j].w);
+        const uint4 o = make_uint4(a, a + v[j].x, a + v[j].x + v[j].y, a + v[j].x + v[j].y + v[j].z);
+        store_keys(start, k, nkeys, o);
+        if (cursor) store_keys(cursor + (long)r * kstride, k, nkeys, o);
+        if (clear) store_keys(count, k, nkeys, make_uint4(0u, 0u, 0u, 0u));
+        row += __shfl(incl[j], 63);
     }
-    uint32_t run = sh[threadIdx.x] - s;
-    for (int i = 0; i < per; ++i)
-        if (b0 + i < nblocks) {
-            uint32_t v = block_sums[b0 + i];
-            block_sums[b0 + i] = run;
-            run += v;
-        }
-}
-
-// Phase 3: add the block offsets; cursor = start; start[nkeys] = total.
-__global__ void k_scan_finish(uint32_t* start, uint32_t* cursor, const uint32_t* block_sums,
-                              long nkeys, long kstride, int nblocks, uint32_t total) {
-    const int r = blockIdx.y;
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    start += (long)r * kstride;
-    cursor += (long)r * kstride;
-    block_sums += (long)r * nblocks;
-    if (i < nkeys) {
-        uint32_t v = start[i] + block_sums[i / 1024];
-        start[i] = v;
-        cursor[i] = v;
-    } else if (i == nkeys) {
-        start[i] = total;
-    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) start[nkeys] = total;
 }
 
 __global__ void k_dep_scatter(long npr, SortBufs sb) {
@@ -387,14 +456,18 @@ __global__ void __launch_bounds__(256) k_dep_tile(TileGeom tg, SortBufs sb, long
 
 }  // namespace
 
-hipError_t scan_counts(const uint32_t* count, uint32_t* start, uint32_t* cursor, uint32_t* block_sums, long nkeys,
-                       uint32_t total, hipStream_t st) {
-    const int nblocks = (int)((nkeys + 1023) / 1024);
-    hipLaunchKernelGGL(k_scan_blocks, dim3(nblocks, 1), dim3(256), 0, st, count, start, block_sums, nkeys, 0L,
-                       nblocks);
-    hipLaunchKernelGGL(k_scan_totals, dim3(1, 1), dim3(1024), 0, st, block_sums, nblocks);
-    hipLaunchKernelGGL(k_scan_finish, dim3((unsigned)((nkeys + 1 + 255) / 256), 1), dim3(256), 0, st, start, cursor,
-                       block_sums, nkeys, 0L, nblocks, total);
+hipError_t scan_counts(uint32_t* count, uint32_t* start, uint32_t* cursor, uint32_t* block_sums, long nkeys,
+                       long kstride, int n_real, uint32_t total, bool clear, hipStream_t st) {
+    const bool one = nkeys <= kScanOne;
+    const int threads = one ? (int)((nkeys + 64 * kScanKeys - 1) / (64 * kScanKeys)) * 64 : 256;
+    const int nblocks = one ? 1 : (int)((nkeys + kScanBlock - 1) / kScanBlock);
+    const bool prefix = nblocks > kScanSums;
+    if (!one)
+        hipLaunchKernelGGL(k_scan_sums, dim3(nblocks, n_real), dim3(256), 0, st, count, block_sums, nkeys, kstride,
+                           nblocks);
+    if (prefix) hipLaunchKernelGGL(k_scan_totals, dim3(1, n_real), dim3(1024), 0, st, block_sums, nblocks);
+    hipLaunchKernelGGL(k_scan_keys, dim3(nblocks, n_real), dim3(threads), 0, st, count, start, cursor, block_sums, prefix,
+                       clear, nkeys, kstride, nblocks, total);
     return hipGetLastError();
 }
 
@@ -409,8 +482,7 @@ SortBufs carve_sort(void* base, long npr, const TileGeom& tg, int n_real) {
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
     char* b = static_cast<char*>(base);
     SortBufs s;
-    s.kstride = tg.nkeys + 1;
-    s.nblocks = (int)((tg.nkeys + 1023) / 1024);
+    s.kstride = tg.nkeys + 4;  // nkeys + 1 entries, every realization's aligned to 16 bytes (nkeys is a multiple of 8)
     size_t off = 0;
     s.keys = reinterpret_cast<uint32_t*>(b + off); off = al(off + (size_t)npr * n_real * 4);
     s.recs = reinterpret_cast<float4*>(b + off); off = al(off + (size_t)npr * n_real * 16);
@@ -423,15 +495,6 @@ SortBufs carve_sort(void* base, long npr, const TileGeom& tg, int n_real) {
 }
 
 namespace {
-// Exclusive scan of the key counts of every realization; cursor = start.
-void scan_keys(int n_real, const TileGeom& tg, const SortBufs& sb, long npr, hipStream_t st) {
-    hipLaunchKernelGGL(k_scan_blocks, dim3(sb.nblocks, n_real), dim3(256), 0, st, sb.count, sb.start, sb.block_sums,
-                       tg.nkeys, sb.kstride, sb.nblocks);
-    hipLaunchKernelGGL(k_scan_totals, dim3(1, n_real), dim3(1024), 0, st, sb.block_sums, sb.nblocks);
-    hipLaunchKernelGGL(k_scan_finish, dim3((unsigned)((tg.nkeys + 1 + 255) / 256), n_real), dim3(256), 0, st,
-                       sb.start, sb.cursor, sb.block_sums, tg.nkeys, sb.kstride, sb.nblocks, (uint32_t)npr);
-}
-
 // Tile accumulation of the sorted records.
 hipError_t run_tiles(long npr, int n_real, const TileGeom& tg, const SortBufs& sb, float* mesh, long row,
                      long mesh_bstride, float scale, float offset, hipStream_t st) {
@@ -442,24 +505,30 @@ hipError_t run_tiles(long npr, int n_real, const TileGeom& tg, const SortBufs& s
     return hipGetLastError();
 }
 
-// Scan of the key counts, scatter of the records into key order, tile accumulation: the passes
-// after the binning of the step's deposit.
-hipError_t sort_and_tile(long npr, int n_real, const TileGeom& tg, const SortBufs& sb, float* mesh, long row,
-                         long mesh_bstride, float scale, float offset, hipStream_t st) {
+// Scan of the key counts, records into key order, tile accumulation: the passes after the binning.
+// drifted: key and record of every particle are in keys and recs, else its rank is in keys.
+hipError_t sort_and_tile(const ParticlePtrs& P, long npr, int n_real, const LatticeGeom& dg, bool drifted,
+                         const TileGeom& tg, const SortBufs& sb, float* mesh, float scale, float offset,
+                         hipStream_t st) {
     {
         ProfScope ps(PROF_DEP_SORT, st);
-        scan_keys(n_real, tg, sb, npr, st);
-        hipLaunchKernelGGL(k_dep_scatter, dim3((unsigned)((npr + 255) / 256), n_real), dim3(256), 0, st, npr, sb);
+        hipError_t e = scan_counts(sb.count, sb.start, drifted ? sb.cursor : nullptr, sb.block_sums, tg.nkeys, sb.kstride,
+                                   n_real, (uint32_t)npr, true, st);
+        if (e != hipSuccess) return e;
+        if (drifted)
+            hipLaunchKernelGGL(k_dep_scatter, dim3((unsigned)((npr + 255) / 256), n_real), dim3(256), 0, st, npr, sb);
+        else
+            hipLaunchKernelGGL(k_dep_place, lattice_grid(dg.n_part, n_real), dim3(256), 0, st, P, npr, dg, tg, sb);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return run_tiles(npr, n_real, tg, sb, mesh, row, mesh_bstride, scale, offset, st);
+    return run_tiles(npr, n_real, tg, sb, mesh, dg.row, dg.mesh_bstride, scale, offset, st);
 }
 }  // namespace
 
 size_t abs_sort_bytes(long n, const TileGeom& tg) {
     const size_t nblocks = (size_t)((tg.nkeys + 1023) / 1024);
-    return (size_t)n * (4 + 16) + ((size_t)tg.nkeys + 1) * 4 * 3 + nblocks * 4 + 256 * 6;
+    return (size_t)n * (4 + 16) + ((size_t)tg.nkeys + 1) * 4 * 2 + nblocks * 4 + 256 * 5;
 }
 
 hipError_t sorted_deposit_absolute(const float* const pos[3], long n, int n_mesh, float inv_h, const TileGeom& tg,
@@ -468,7 +537,6 @@ hipError_t sorted_deposit_absolute(const float* const pos[3], long n, int n_mesh
     char* b = static_cast<char*>(scratch);
     SortBufs sb;
     sb.kstride = tg.nkeys + 1;
-    sb.nblocks = (int)((tg.nkeys + 1023) / 1024);
     size_t off = 0;
     auto take = [&](size_t bytes) {
         char* p = b + off;
@@ -479,8 +547,7 @@ hipError_t sorted_deposit_absolute(const float* const pos[3], long n, int n_mesh
     uint32_t* rank = reinterpret_cast<uint32_t*>(take((size_t)n * 4));
     sb.count = reinterpret_cast<uint32_t*>(take((size_t)sb.kstride * 4));
     sb.start = reinterpret_cast<uint32_t*>(take((size_t)sb.kstride * 4));
-    sb.cursor = reinterpret_cast<uint32_t*>(take((size_t)sb.kstride * 4));
-    sb.block_sums = reinterpret_cast<uint32_t*>(take((size_t)sb.nblocks * 4));
+    sb.block_sums = reinterpret_cast<uint32_t*>(take((size_t)(tg.nkeys + 1023) / 1024 * 4));
     hipError_t e = launch_fill(reinterpret_cast<float*>(sb.count), sb.kstride, 0.0f, st);
     if (e != hipSuccess) return e;
     const dim3 grid((unsigned)((n + 255) / 256));
@@ -491,7 +558,9 @@ hipError_t sorted_deposit_absolute(const float* const pos[3], long n, int n_mesh
     }
     {
         ProfScope ps(PROF_DEP_SORT, st);
-        scan_keys(1, tg, sb, n, st);
+        if ((e = scan_counts(sb.count, sb.start, nullptr, sb.block_sums, tg.nkeys, 0, 1, (uint32_t)n, false, st)) !=
+            hipSuccess)
+            return e;
         hipLaunchKernelGGL(k_abs_scatter, grid, dim3(256), 0, st, pos[0], pos[1], pos[2], n, n_mesh, inv_h, tg,
                            sb.start, rank, sb.sorted);
     }
@@ -514,14 +583,15 @@ hipError_t sorted_deposit(const ParticlePtrs& P, long npr, int n_real, const Lat
     }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return sort_and_tile(npr, n_real, tg, sb, mesh, dg.row, dg.mesh_bstride, scale, offset, st);
+    return sort_and_tile(P, npr, n_real, dg, drift, tg, sb, mesh, scale, offset, st);
 }
 
 hipError_t gather_kick_drift_bin(const ParticlePtrs& P, long npr, int n_real, const LatticeGeom& fg, const float* F,
                                  const LatticeGeom& dg, const KickDrift& kd, const TileGeom& tg, const SortBufs& sb,
-                                 hipStream_t st) {
-    hipError_t e = launch_fill(reinterpret_cast<float*>(sb.count), sb.kstride * n_real, 0.0f, st);
-    if (e != hipSuccess) return e;
+                                 bool counts_zero, hipStream_t st) {
+    if (!counts_zero)
+        if (hipError_t e = launch_fill(reinterpret_cast<float*>(sb.count), sb.kstride * n_real, 0.0f, st); e != hipSuccess)
+            return e;
     KickDrift k = kd;
     k.los = -1;
     ProfScope ps(PROF_GKD, st);
@@ -529,9 +599,9 @@ hipError_t gather_kick_drift_bin(const ParticlePtrs& P, long npr, int n_real, co
     return hipGetLastError();
 }
 
-hipError_t sorted_deposit_binned(long npr, int n_real, const LatticeGeom& dg, const TileGeom& tg, const SortBufs& sb,
-                                 float* mesh, float scale, float offset, hipStream_t st) {
-    return sort_and_tile(npr, n_real, tg, sb, mesh, dg.row, dg.mesh_bstride, scale, offset, st);
+hipError_t sorted_deposit_binned(const ParticlePtrs& P, long npr, int n_real, const LatticeGeom& dg, const TileGeom& tg,
+                                 const SortBufs& sb, float* mesh, float scale, float offset, hipStream_t st) {
+    return sort_and_tile(P, npr, n_real, dg, false, tg, sb, mesh, scale, offset, st);
 }
 
 }  // namespace cola

@@ -589,7 +589,6 @@ struct FofWs {
     float4* recs;       // n
     uint32_t* count;    // keys + 1
     uint32_t* start;    // keys + 1 (catalogue: the halo index of each root)
-    uint32_t* cursor;   // keys + 1
     uint32_t* block_sums;
     size_t total;
 };
@@ -609,7 +608,6 @@ FofWs fof_ws(long n, const FofGrid& g, void* base) {
     w.recs = reinterpret_cast<float4*>(take((size_t)n * 16));
     w.count = reinterpret_cast<uint32_t*>(take((size_t)(keys + 1) * 4));
     w.start = reinterpret_cast<uint32_t*>(take((size_t)(keys + 1) * 4));
-    w.cursor = reinterpret_cast<uint32_t*>(take((size_t)(keys + 1) * 4));
     w.block_sums = reinterpret_cast<uint32_t*>(take((size_t)((keys + 1023) / 1024 + 1) * 4));
     w.total = off;
     return w;
@@ -674,7 +672,7 @@ int cola_fof(const float* pos[3], int64_t n, double box, double link, int32_t* g
     hipLaunchKernelGGL(k_fof_bin, dim3(blocks_of(n)), dim3(256), 0, st, pos[0], pos[1], pos[2], (long)n, g,
                        w.rank, w.count);
     FOF_TRY(hipGetLastError());
-    FOF_TRY(scan_counts(w.count, w.start, w.cursor, w.block_sums, g.ncell, (uint32_t)n, st));
+    FOF_TRY(scan_counts(w.count, w.start, nullptr, w.block_sums, g.ncell, 0, 1, (uint32_t)n, false, st));
     hipLaunchKernelGGL(k_fof_scatter, dim3(blocks_of(n)), dim3(256), 0, st, pos[0], pos[1], pos[2], (long)n, g,
                        w.rank, w.start, w.recs);
     const unsigned blocks = (unsigned)(((long)n + kFofBlock - 1) / kFofBlock);

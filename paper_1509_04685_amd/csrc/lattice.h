@@ -4,7 +4,7 @@
 // three axes per particle they were most of the instructions of the gather/kick/drift pass (556 per wave,
 // 237 of its 445 us at 256^3 particles on 256^3 cells).  So the grid gives the lattice plane, one float
 // product the row, and the lattice's own mesh (n_mesh a multiple of n_part) needs no division at all:
-// 258 instructions, 408 us; on 768^3 cells 1163 -> 1096 us.
+// 258 instructions, 408 us (390 without the records that the pass then wrote); on 768^3 cells 1163 -> 1096 us.
 #pragma once
 
 #include "cola_internal.h"
@@ -55,7 +55,7 @@ __device__ __forceinline__ LatticeCell lattice_cell(const LatticeGeom& g, int i,
         q = (int)(a / (uint32_t)g.n_part);
         base = (float)(int)(a - (uint32_t)q * (uint32_t)g.n_part) / (float)g.n_part + g.qoff;
     }
-    const float w = base + x * g.inv_h, fl = floorf(w);
+    const float w = fmaf(x, g.inv_h, base), fl = floorf(w);
     LatticeCell c;
     c.f = w - fl;
     int m = q + (int)fl;

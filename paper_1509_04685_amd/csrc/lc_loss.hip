@@ -37,7 +37,7 @@ constexpr int kLossCells = 1024;  // most cells of a tile: three 64-bit sums eac
 struct LossSort {
     float4* resid;    // per particle: r, rank in its key
     float4* sorted;   // two per particle, in key order
-    uint32_t *count, *start, *cursor, *block_sums;
+    uint32_t *count, *start, *block_sums;
     uint32_t* rmax;   // bits of the largest |r| component
     size_t total;
 };
@@ -58,7 +58,6 @@ LossSort carve_loss(void* base, long np, const TileGeom& tg) {
     w.sorted = reinterpret_cast<float4*>(take((size_t)np * 32));
     w.count = reinterpret_cast<uint32_t*>(take(((size_t)tg.nkeys + 1) * 4));
     w.start = reinterpret_cast<uint32_t*>(take(((size_t)tg.nkeys + 1) * 4));
-    w.cursor = reinterpret_cast<uint32_t*>(take(((size_t)tg.nkeys + 1) * 4));
     w.block_sums = reinterpret_cast<uint32_t*>(take(((size_t)tg.nkeys / 1024 + 2) * 4));
     w.rmax = reinterpret_cast<uint32_t*>(take(4));
     w.total = off;
@@ -215,7 +214,7 @@ hipError_t lc_loss_tiled(const float* const pos[3], long np, int n, double box, 
     const dim3 grid((unsigned)((np + 255) / 256));
     hipLaunchKernelGGL(k_loss_resid, grid, dim3(256), 0, st, P, np, n, inv_h, Ptr3{{df[0], df[1], df[2]}},
                        Ptr3{{g1[0], g1[1], g1[2]}}, Ptr3{{g3[0], g3[1], g3[2]}}, tg, stats, w.count, w.rmax, w.resid);
-    if ((e = scan_counts(w.count, w.start, w.cursor, w.block_sums, tg.nkeys, (uint32_t)np, st)) != hipSuccess) return e;
+    if ((e = scan_counts(w.count, w.start, nullptr, w.block_sums, tg.nkeys, 0, 1, (uint32_t)np, false, st)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_loss_scatter, grid, dim3(256), 0, st, P, np, n, inv_h, tg, w.start, w.resid, w.sorted);
     hipLaunchKernelGGL(k_loss_tile, dim3((unsigned)tg.ntiles), dim3(256), 0, st, tg, w.start, w.sorted, bits, w.rmax,
                        stats, ddf);
