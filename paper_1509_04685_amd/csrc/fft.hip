@@ -227,9 +227,9 @@ static long shape_threads(FftKind k, int n, const FftShape& sh) {
     return (long)sh.width * (line_len(k, n) / sh.R) * (k == FK_Z_C2R3 ? 3 : 1);
 }
 
-// LDS of one block: z passes keep their lines L + 2 complex values apart (the line, its kz Nyquist
-// value and one value against bank conflicts of the transposed accesses); z_c2r3 holds one group
-// of lines per force component.
+// LDS of one block, before what a plan adds against bank conflicts (z_line_stride, exchange_pad; with it no
+// plan of a shape that fits here takes more than 160 KB): z passes hold a line and its kz Nyquist
+// value, z_c2r3 one group of lines per force component.
 static size_t shape_lds(FftKind k, int n, const FftShape& sh) {
     int L = line_len(k, n);
     if (is_z(k)) return (size_t)sh.width * (L + 2) * sizeof(float2) * (k == FK_Z_C2R3 ? 3 : 1);
@@ -438,7 +438,6 @@ static hipError_t run_z_r2c_shape(const float* in, long in_row, long in_bstride,
     FftLaunch L;
     L.op = OP_Z_R2C;
     const int lpb = sh.width;
-    L.lds = shape_lds(FK_Z_R2C, g.n, sh);
     L.grid = dim3((unsigned)z_blocks(g.n, lpb), n_real);
     L.block = dim3(lpb * (g.m / sh.R));
     L.st = st;
@@ -470,7 +469,6 @@ static hipError_t run_z_c2r_shape(const float2* in, long in_bstride, float* out,
     FftLaunch L;
     L.op = OP_Z_C2R;
     const int lpb = sh.width;
-    L.lds = shape_lds(FK_Z_C2R, g.n, sh);
     L.grid = dim3((unsigned)z_blocks(g.n, lpb), n_real);
     L.block = dim3(lpb * (g.m / sh.R));
     L.st = st;
@@ -504,7 +502,6 @@ static hipError_t run_z_c2r3_shape(const float2* fx, const float2* fy, const flo
     FftLaunch L;
     L.op = OP_Z_C2R3;
     const int lpb = sh.width;
-    L.lds = shape_lds(FK_Z_C2R3, g.n, sh);
     L.grid = dim3((unsigned)(z_blocks(g.n, lpb) / g.n * (planes < 0 ? g.n : planes)), n_real);
     L.block = dim3((unsigned)shape_threads(FK_Z_C2R3, g.n, sh));
     L.st = st;

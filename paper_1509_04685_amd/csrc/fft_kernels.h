@@ -118,11 +118,16 @@ __device__ __forceinline__ void store_col(float2* p, float2 v) {
 
 // ------------------------------------------------------------------ z pass: real -> half complex
 
-// LDS stride of the lines of a z pass block: M + 1 complex values fit a line with its kz Nyquist
-// value.  A wave's transposed LDS accesses cover W lines x 64 / W planes k at j stride + k; with M
-// a multiple of 32 the stride M + 2 puts half as many of its lanes on one LDS bank pair as M + 1
-// does at W = 8 and 16 (4 instead of 8, 2 instead of 4).
-__device__ __forceinline__ constexpr int z_line_stride(int M) { return M + 2; }
+// LDS stride of the W = 2^lw lines of a z pass block: a line and its kz Nyquist value, or its exchanges.  A
+// half wave's transposed accesses cover W lines x 32 / W planes k at j stride + k, so the stride is an odd
+// multiple of 32 / W: its 32 lanes then meet the 32 bank pairs of the LDS once each.
+template <class LE>
+__host__ __device__ __forceinline__ constexpr int z_line_stride(int M, int lw) {
+    const int least = M + (LE::kPad > 1 ? LE::kPad : 1);
+    const int q = lw < 5 ? 32 >> lw : 1;
+    const int odd = ((least + q - 1) / q) | 1;
+    return odd * q;
+}
 
 // The lines of block b: `count` lines from (x, y0).  A plane's last block holds the n mod W lines that
 // are left; its other line slots repeat the last line and store nothing.  With W a power of two that
@@ -160,7 +165,7 @@ __global__ void __launch_bounds__(512) k_fft_z_r2c(const float* in, long in_row,
     in += (long)blockIdx.y * in_bstride;
     out += (long)blockIdx.y * out_bstride;
     float2* const Lb = lds + TW;
-    const int LS = z_line_stride(M);
+    const int LS = z_line_stride<LE>(M, lw);
     float2* L = Lb + line * LS;
     float2 v[R];
     const float2* src = reinterpret_cast<const float2*>(in + (first + min(line, zb.count - 1)) * in_row);
@@ -217,7 +222,7 @@ __global__ void __launch_bounds__(512) k_fft_z_c2r(const float2* in, long in_bst
     in += (long)blockIdx.y * in_bstride;
     out += (long)blockIdx.y * out_bstride;
     float2* const Lb = lds + TW;
-    const int LS = z_line_stride(M);
+    const int LS = z_line_stride<LE>(M, lw);
     const float2* twl = stage_twiddles<TW>(tw, lds);  // visible after the barrier below
     {
         // every load of this thread is issued before the first LDS store
@@ -278,7 +283,7 @@ __global__ void __launch_bounds__(1024) k_fft_z_c2r3(const float2* in0, const fl
     const ZBlock zb = z_block(xcd_block(), n, lw);
     const long first = (long)zb.x * n + zb.y0;
     float2* const Lb = lds + TW;
-    const int LS = z_line_stride(M);  // this group's lines
+    const int LS = z_line_stride<LE>(M, lw);  // this group's lines
     float2* const Lg = Lb + (long)comp * W * LS;
     const float2* twl = stage_twiddles<TW>(tw, lds);  // visible after the barrier below
     {
@@ -354,7 +359,7 @@ __global__ void __launch_bounds__(512) k_fft_rows(float2* A, float2* S, long bst
     const long kz = row / n;
     const long roff = kz * plane + (row - kz * n) * n;  // row (kz, x) of the transposed spectrum
     A += (long)blockIdx.y * bstride + roff;
-    float2* L = lds + TW + line * n;
+    float2* L = lds + TW + line * (n + LE::kPad);
     float2 v[R], h[R];
     if (active) {
         eng.first(t, [&](int q, int e) {
@@ -579,10 +584,22 @@ inline hipError_t allow_lds_fft(K kernel, size_t bytes) {
                                (int)bytes);
 }
 
+template <int R>
+inline int line_length(const DynLine<R>& e) { return e.p.n; }
+template <class LE>
+inline int line_length(const LE&) { return LE::kN; }
+
+// LDS of a z pass whose blocks hold `lines` sets of W lines.
+template <class LE>
+inline size_t z_lds_bytes(const FftLaunch& L, const LE& e, int lines) {
+    const int M = line_length(e);
+    return ((size_t)lines << L.lw) * z_line_stride<LE>(M, L.lw) * sizeof(float2) + tw_lds_bytes(z_tw_entries<LE>());
+}
+
 template <class LE>
 inline hipError_t go_z_r2c(const FftLaunch& L, LE e) {
     auto kern = k_fft_z_r2c<LE>;
-    const size_t lds = L.lds + tw_lds_bytes(z_tw_entries<LE>());
+    const size_t lds = z_lds_bytes<LE>(L, e, 1);
     if (hipError_t ea = allow_lds_fft(kern, lds); ea != hipSuccess) return ea;
     hipLaunchKernelGGL(kern, L.grid, L.block, lds, L.st, L.rin, L.in_row, L.in_bstride, L.cout, L.out_bstride,
                        L.mesh_n, L.plane, L.lw, e, L.tw, L.pa, L.pb);
@@ -592,7 +609,7 @@ inline hipError_t go_z_r2c(const FftLaunch& L, LE e) {
 template <class LE>
 inline hipError_t go_z_c2r(const FftLaunch& L, LE e) {
     auto kern = k_fft_z_c2r<LE>;
-    const size_t lds = L.lds + tw_lds_bytes(z_tw_entries<LE>());
+    const size_t lds = z_lds_bytes<LE>(L, e, 1);
     if (hipError_t ea = allow_lds_fft(kern, lds); ea != hipSuccess) return ea;
     hipLaunchKernelGGL(kern, L.grid, L.block, lds, L.st, L.cin, L.in_bstride, L.rout, L.out_row, L.out_bstride,
                        L.mesh_n, L.plane, L.lw, L.ghost, e, L.tw, L.scale);
@@ -602,7 +619,7 @@ inline hipError_t go_z_c2r(const FftLaunch& L, LE e) {
 template <class LE>
 inline hipError_t go_z_c2r3(const FftLaunch& L, LE e) {
     auto kern = k_fft_z_c2r3<LE>;
-    const size_t lds = L.lds + tw_lds_bytes(z_tw_entries<LE>());
+    const size_t lds = z_lds_bytes<LE>(L, e, 3);
     if (hipError_t ea = allow_lds_fft(kern, lds); ea != hipSuccess) return ea;
     hipLaunchKernelGGL(kern, L.grid, L.block, lds, L.st, L.cin, L.cin1, L.cin2, L.in_bstride, L.rout, L.out_row,
                        L.out_bstride, L.mesh_n, L.plane, L.lw, e, L.tw, L.kf, L.scale);
@@ -612,7 +629,8 @@ inline hipError_t go_z_c2r3(const FftLaunch& L, LE e) {
 template <class LE, int OPR>
 inline hipError_t go_rows(const FftLaunch& L, LE e) {
     auto kern = k_fft_rows<LE, OPR>;
-    const size_t lds = L.lds + tw_lds_bytes(LE::kTwN);
+    const size_t pads = LE::kPad > 0 ? (size_t)(L.block.x / (LE::kT > 0 ? LE::kT : 1)) * LE::kPad * sizeof(float2) : 0;
+    const size_t lds = L.lds + pads + tw_lds_bytes(LE::kTwN);
     if (hipError_t ea = allow_lds_fft(kern, lds); ea != hipSuccess) return ea;
     hipLaunchKernelGGL(kern, L.grid, L.block, lds, L.st, L.d0, L.d1, L.b0, L.nrows, L.plane, e, L.tw, L.kf);
     return hipGetLastError();
