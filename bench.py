@@ -67,8 +67,8 @@ def algorithmic_bytes(kind, tag, n_g, n_part):
     C = n * n * (n // 2 + 1)
     N = n_part ** 3
     table = {
-        "cic_deposit": 32 * N,                  # binning: displacements in; tile key + cell record out
-        "cic_sort": 36 * N,                     # scatter: key + record in, record out (scans: O(G/512))
+        "cic_deposit": 16 * N,                  # binning: displacements in; rank in the tile key out
+        "cic_sort": 32 * N,                     # displacements + rank in, record out (scans: O(G/512))
         "cic_tile": 16 * N + 4 * G,             # sorted records in, density mesh out
         "fft_z_r2c": 4 * G + 8 * C,
         "fft_y_forward": 16 * C,
@@ -79,8 +79,8 @@ def algorithmic_bytes(kind, tag, n_g, n_part):
         "fft_z_c2r": 8 * C + 4 * G,
         "fft_z_c2r3": 24 * C + 12 * G,          # the three force spectra in; (F_x, F_y, F_z) out,
                                                 # interleaved (ghost cells and row padding not counted)
-        "gather_kick_drift": 12 * G + 92 * N,   # the force mesh; x,p,psi1,psi2 in; x,p out; key +
-                                                # record of the next deposit out (binning fused in)
+        "gather_kick_drift": 12 * G + 76 * N,   # the force mesh; x,p,psi1,psi2 in; x,p out; rank in
+                                                # the key of the next deposit out (binning fused in)
         "gather_kick": 12 * G + 60 * N,
         "pk_deposit": 12 * G + 68 * N,          # binning with the partial drift: x, p, psi1, psi2 and
                                                 # the force meshes in; key + record out
@@ -124,10 +124,12 @@ def node_index(table, a_out):
 
 
 KERNEL_SOURCES = {"fft": ("fft.hip", "fft_core.h", "fft_kernels.h", "fft_static_1536.hip", "fft_static_768.hip",
-                          "fft_static_512.hip", "fft_static_384.hip", "fft_static_288.hip", "fft_static_256.hip"), "cic": ("deposit_sorted.hip",),
-                  "pk_deposit": ("deposit_sorted.hip", "force_gather.h"),
-                  "gather_kick_drift": ("deposit_sorted.hip", "pm_kernels.hip", "force_gather.h"),
-                  "gather": ("pm_kernels.hip", "force_gather.h"), "lc": ("lc_kernels.hip",),
+                          "fft_static_512.hip", "fft_static_384.hip", "fft_static_288.hip", "fft_static_256.hip"), "cic": ("deposit_sorted.hip", "lattice.h", "tile_pull.h", "wave_ops.h"),
+                  "pk_deposit": ("deposit_sorted.hip", "force_gather.h", "lattice.h", "wave_ops.h"),
+                  "gather_kick_drift": ("deposit_sorted.hip", "pm_kernels.hip", "force_gather.h", "lattice.h",
+                                        "wave_ops.h"),
+                  "gather": ("pm_kernels.hip", "force_gather.h", "lattice.h"),
+                  "lc": ("lc_kernels.hip", "lc_loss.hip", "lc_cic.h"),
                   "pk_alias": ("pk_kernels.hip",)}
 
 
