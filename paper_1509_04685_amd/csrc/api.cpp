@@ -779,7 +779,7 @@ int cola_cic_density(const float* pos[3], int64_t n, int32_t n_mesh, double box,
     ws_forget(ws);
     (void)hipGetLastError();
     COLA_TRY(sorted_deposit_absolute(pos, (long)n, n_mesh, (float)(n_mesh / box), tg, ws, delta, n_mesh,
-                                     (float)(cells / (double)n), -1.0f, st));
+                                     (float)(cells / (double)n), -1.0f, false, st));
     return COLA_OK;
 }
 

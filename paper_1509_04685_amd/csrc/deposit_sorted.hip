@@ -15,6 +15,8 @@
 // counts, scatter of the records into key order, tile accumulation.  Records keep the CIC
 // fractions exactly as computed from the lattice index and displacement.
 
+#include <algorithm>
+
 #include "cola_internal.h"
 #include "force_gather.h"
 #include "lattice.h"
@@ -364,6 +366,17 @@ __device__ __forceinline__ unsigned long long fixed_weight(float w) {
     return (unsigned long long)(whole ? 1u : 0u) << 32 | (whole ? 0u : (uint32_t)t);
 }
 
+// A CIC weight of either sign, below 2 in magnitude, in fixed point with `frac` bits after the point (rounded to even).
+__device__ __forceinline__ unsigned long long signed_weight(float w, int frac) {
+    const uint32_t b = __float_as_uint(w), e = (b >> 23) & 255u;
+    const uint32_t m = (b & 0x7fffffu) | (e ? 0x800000u : 0u);  // w = m 2^(max(e, 1) - 150)
+    const int s = (int)max(e, 1u) - 150 + frac;
+    unsigned long long v = 0ull;
+    if (s >= 0) v = (unsigned long long)m << min(s, 63);
+    else if (s > -25) v = (m + (1u << (-s - 1)) - 1u + ((m >> -s) & 1u)) >> -s;
+    return (int)b < 0 ? 0ull - v : v;
+}
+
 // A 32.32 fixed-point sum as float, rounded once: its 32 leading bits, the last of them also set for any
 // bit below (round to nearest even of the conversion then sees them).
 __device__ __forceinline__ float mass_of(unsigned long long v) {
@@ -371,6 +384,9 @@ __device__ __forceinline__ float mass_of(unsigned long long v) {
     const int s = hi ? __clz((int)hi) : 32;
     const unsigned long long t = v << s;
     return ldexpf((float)((uint32_t)(t >> 32) | min((uint32_t)t, 1u)), -s);
+}
+__device__ __forceinline__ float signed_mass_of(unsigned long long v) {
+    return (long long)v < 0 ? -mass_of(0ull - v) : mass_of(v);
 }
 
 // One block per tile: pull the records whose corners reach into the tile, accumulate in LDS,
@@ -380,12 +396,18 @@ __device__ __forceinline__ float mass_of(unsigned long long v) {
 // instructions per wave, 121 of 130 us, with 64-bit conversions of every weight and cell and 64-bit
 // addresses, on 256^3 cells and particles), hence 32-bit arithmetic for both: 121 us there; 653 -> 636 us for
 // 256^3 particles on 768^3 cells, where the chain of loads of a tile is longer than its arithmetic.
+//
+// Cell masses accumulate in fixed point in 64-bit integers: LDS integer atomics run at tens of times the
+// rate of LDS float atomics on this hardware, and integer sums do not depend on the order of the adds
+// (the deposit is bitwise reproducible).  32.32 for FRAC = 0: a CIC weight is rounded to 2^-32, a negative one
+// is 0, a cell overflows only beyond 2^32 particles.  A mesh with many more cells than particles multiplies
+// that rounding by their ratio, and the fields of the learned correction had float sums, with 24 bits of a weight
+// of any size and its sign.  So theirs (FRAC = 1) are signed, with `frac` = 61 - ceil(log2 particles) bits after the
+// point where cells are more than three to two particles (rounded to cells 2^-61 a term, in units of the mean
+// density), and 32 otherwise (rounded to 2^-32; the contrast itself is rounded to 2^-25; the bits of cic_density).
+template <bool FRAC>
 __global__ void __launch_bounds__(256) k_dep_tile(TileGeom tg, SortBufs sb, long npr, float* mesh, long row,
-                                                  long mesh_bstride, float scale, float offset) {
-    // Cell masses accumulate as 32.32 fixed point in 64-bit integers: LDS integer atomics run at
-    // tens of times the rate of LDS float atomics on this hardware, and integer sums do not depend
-    // on the order of the adds (the deposit is bitwise reproducible).  A CIC weight is rounded to
-    // 2^-32; a cell overflows only beyond 2^32 particles.
+                                                  long mesh_bstride, float scale, float offset, int frac) {
     extern __shared__ unsigned long long acc[];
     __shared__ PullRanges pr;
     const int r = blockIdx.y;
@@ -401,6 +423,8 @@ __global__ void __launch_bounds__(256) k_dep_tile(TileGeom tg, SortBufs sb, long
     __syncthreads();
     const uint32_t total = pr.len[14];
     const PullStarts ps = pull_starts(pr);
+    auto fixed = [&](float w) { return FRAC ? signed_weight(w, frac) : fixed_weight(w); };
+    auto cell = [&](unsigned long long v) { return fmaf(FRAC ? signed_mass_of(v) : mass_of(v), scale, offset); };
     // Each thread sweeps a contiguous chunk of the concatenated records, so that the lanes of a
     // wave work on records far apart in the sorted order: records of one key range are in
     // Lagrangian order, and neighbouring particles hit the same cells -- consecutive records on
@@ -426,8 +450,8 @@ __global__ void __launch_bounds__(256) k_dep_tile(TileGeom tg, SortBufs sb, long
                 if (!(okx[cx] && oky[cy])) continue;
                 const float wxy = wx[cx] * wy[cy];
                 const int c = cell0 + (((cx << tg.ly) + cy) << tg.lz);
-                if (okz[0]) atomicAdd(&acc[c], fixed_weight(wxy * wz[0]));
-                if (okz[1]) atomicAdd(&acc[c + 1], fixed_weight(wxy * wz[1]));
+                if (okz[0]) atomicAdd(&acc[c], fixed(wxy * wz[0]));
+                if (okz[1]) atomicAdd(&acc[c + 1], fixed(wxy * wz[1]));
             }
     }
     __syncthreads();
@@ -440,8 +464,7 @@ __global__ void __launch_bounds__(256) k_dep_tile(TileGeom tg, SortBufs sb, long
             if (ux >= tb.nx || uy >= tb.ny || uz >= tb.nz) continue;
             const ulonglong2 u = reinterpret_cast<const ulonglong2*>(acc)[i >> 1],
                              v = reinterpret_cast<const ulonglong2*>(acc)[(i >> 1) + 1];
-            const float4 a = make_float4(fmaf(mass_of(u.x), scale, offset), fmaf(mass_of(u.y), scale, offset),
-                                         fmaf(mass_of(v.x), scale, offset), fmaf(mass_of(v.y), scale, offset));
+            const float4 a = make_float4(cell(u.x), cell(u.y), cell(v.x), cell(v.y));
             const uint32_t o = __umul24(__umul24(ux, tg.n) + uy, row32) + uz;
             store_rec_stream(reinterpret_cast<float4*>(out + o), a);
         }
@@ -449,7 +472,7 @@ __global__ void __launch_bounds__(256) k_dep_tile(TileGeom tg, SortBufs sb, long
         for (int i = threadIdx.x; i < ncell; i += 256) {
             const int uz = i & (tg.tz - 1), uy = (i >> tg.lz) & (tg.ty - 1), ux = i >> (tg.lz + tg.ly);
             if (ux >= tb.nx || uy >= tb.ny || uz >= tb.nz) continue;
-            out[__umul24(__umul24(ux, tg.n) + uy, row32) + uz] = fmaf(mass_of(acc[i]), scale, offset);
+            out[__umul24(__umul24(ux, tg.n) + uy, row32) + uz] = cell(acc[i]);
         }
     }
 }
@@ -495,13 +518,18 @@ SortBufs carve_sort(void* base, long npr, const TileGeom& tg, int n_real) {
 }
 
 namespace {
-// Tile accumulation of the sorted records.
+// Tile accumulation of the sorted records.  frac: bits after the point of the signed sums, 0: 32.32.
 hipError_t run_tiles(long npr, int n_real, const TileGeom& tg, const SortBufs& sb, float* mesh, long row,
-                     long mesh_bstride, float scale, float offset, hipStream_t st) {
+                     long mesh_bstride, float scale, float offset, int frac, hipStream_t st) {
     ProfScope ps(PROF_DEP_TILE, st);
     size_t lds = (size_t)tg.tx * tg.ty * tg.tz * sizeof(unsigned long long);
-    hipLaunchKernelGGL(k_dep_tile, dim3((unsigned)tg.ntiles, n_real), dim3(256), lds, st, tg, sb, npr, mesh, row,
-                       mesh_bstride, scale, offset);
+    const dim3 grid((unsigned)tg.ntiles, n_real);
+    if (frac)
+        hipLaunchKernelGGL(k_dep_tile<true>, grid, dim3(256), lds, st, tg, sb, npr, mesh, row, mesh_bstride,
+                           ldexpf(scale, 32 - frac), offset, frac);
+    else
+        hipLaunchKernelGGL(k_dep_tile<false>, grid, dim3(256), lds, st, tg, sb, npr, mesh, row, mesh_bstride, scale,
+                           offset, 0);
     return hipGetLastError();
 }
 
@@ -522,7 +550,7 @@ hipError_t sort_and_tile(const ParticlePtrs& P, long npr, int n_real, const Latt
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return run_tiles(npr, n_real, tg, sb, mesh, dg.row, dg.mesh_bstride, scale, offset, st);
+    return run_tiles(npr, n_real, tg, sb, mesh, dg.row, dg.mesh_bstride, scale, offset, 0, st);
 }
 }  // namespace
 
@@ -532,7 +560,8 @@ size_t abs_sort_bytes(long n, const TileGeom& tg) {
 }
 
 hipError_t sorted_deposit_absolute(const float* const pos[3], long n, int n_mesh, float inv_h, const TileGeom& tg,
-                                   void* scratch, float* mesh, long row, float scale, float offset, hipStream_t st) {
+                                   void* scratch, float* mesh, long row, float scale, float offset, bool full_weights,
+                                   hipStream_t st) {
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
     char* b = static_cast<char*>(scratch);
     SortBufs sb;
@@ -565,7 +594,11 @@ hipError_t sorted_deposit_absolute(const float* const pos[3], long n, int n_mesh
                            sb.start, rank, sb.sorted);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    return run_tiles(n, 1, tg, sb, mesh, row, 0, scale, offset, st);
+    int lg = 0;
+    while ((1L << lg) < n) ++lg;
+    const bool sparse = (double)n_mesh * n_mesh * n_mesh > 1.5 * (double)n;
+    const int frac = full_weights ? (sparse ? 61 - lg : std::min(32, 61 - lg)) : 0;
+    return run_tiles(n, 1, tg, sb, mesh, row, 0, scale, offset, frac, st);
 }
 
 hipError_t sorted_deposit(const ParticlePtrs& P, long npr, int n_real, const LatticeGeom& dg, bool drift,

@@ -276,7 +276,7 @@ int cola_pm_fields(int32_t n_mesh, double box, const float* pos[3], int64_t n, f
     const size_t room = 2 * lc_align(gm.bytes()) + fields_f_bytes(n_mesh);
     if (n <= (int64_t)INT32_MAX - 1 && abs_sort_bytes(n, tg) <= room) {
         LC_TRY(sorted_deposit_absolute(pos, n, n_mesh, (float)(n_mesh / box), tg, w.A, s_real, row,
-                                       (float)(cells / (double)n), -1.0f, st));
+                                       (float)(cells / (double)n), -1.0f, true, st));
     } else {
         LC_TRY(launch_fill(s_real, 2L * gm.total_c(), 0.0f, st));
         LC_TRY(cic_deposit_absolute(pos, n, n_mesh, (float)(n_mesh / box), row, s_real, st));
