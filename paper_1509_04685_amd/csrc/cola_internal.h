@@ -266,8 +266,9 @@ hipError_t mesh_ghosts(float* F, long row, int n, long bstride, int n_real, hipS
 
 // The same deposit for absolute positions pos[3] (n floats each, wrapped into the mesh), one
 // realization, onto a mesh of n_mesh cells per side with rows of `row` floats.  scratch: at least
-// abs_sort_bytes, which no mesh with tiles tg needs more of than sort_bytes.  full_weights: weights keep their 24
-// bits and their sign at any size, as in float sums (n below 2^31).
+// abs_sort_bytes, which no mesh with tiles tg needs more of than sort_bytes.  full_weights: as in
+// float sums, weights keep their 24 bits and their sign at any size, and ones that are not finite reach the mesh
+// (n below 2^31).
 size_t abs_sort_bytes(long n, const TileGeom& tg);
 hipError_t sorted_deposit_absolute(const float* const pos[3], long n, int n_mesh, float inv_h, const TileGeom& tg,
                                    void* scratch, float* mesh, long row, float scale, float offset, bool full_weights,

@@ -197,6 +197,12 @@ __device__ __forceinline__ AbsCells abs_cells(const float* px, const float* py, 
     return a;
 }
 
+// Whether all fractions are those of a finite position near enough for its float32 cell coordinate to hold them:
+// within a quarter of [0, 1], which up to 2^22 cells from the origin they are.
+__device__ __forceinline__ bool regular(const AbsCells& a) {
+    return fabsf(a.c[0].f - 0.5f) <= 0.75f && fabsf(a.c[1].f - 0.5f) <= 0.75f && fabsf(a.c[2].f - 0.5f) <= 0.75f;
+}
+
 __global__ void __launch_bounds__(256) k_abs_count(const float* px, const float* py, const float* pz, long n,
                                                    int n_mesh, float inv_h, TileGeom tg, uint32_t* count,
                                                    uint32_t* rank) {
@@ -212,16 +218,43 @@ __global__ void __launch_bounds__(256) k_abs_count(const float* px, const float*
     if (valid) __builtin_nontemporal_store(r, rank + p);
 }
 
+// odd (null: all points go the same way): set where a point is not regular; its record then has no weight, and
+// k_abs_odd adds it.
 __global__ void __launch_bounds__(256) k_abs_scatter(const float* px, const float* py, const float* pz, long n,
                                                      int n_mesh, float inv_h, TileGeom tg, const uint32_t* start,
-                                                     const uint32_t* rank, float4* sorted) {
+                                                     const uint32_t* rank, float4* sorted, uint32_t* odd) {
     const long p = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n) return;
     const uint32_t r = __builtin_nontemporal_load(rank + p);
-    const AbsCells a = abs_cells(px, py, pz, p, n_mesh, inv_h);
+    AbsCells a = abs_cells(px, py, pz, p, n_mesh, inv_h);
     int local;
     const uint32_t key = tile_key(tg, a.c[0].m, a.c[1].m, a.c[2].m, local);
+    if (odd && !regular(a)) {
+        *odd = 1u;
+        a.c[0].f = __int_as_float(0x7fc00000);
+    }
     sorted[start[key] + r] = make_float4(__int_as_float(local), a.c[0].f, a.c[1].f, a.c[2].f);
+}
+
+// The points that are not regular, added to the finished mesh with float atomics: NaN and infinite weights reach
+// the cells that they have there, as in a mesh of float sums.
+__global__ void __launch_bounds__(256) k_abs_odd(const float* px, const float* py, const float* pz, long n, int n_mesh,
+                                                 float inv_h, const uint32_t* odd, float* mesh, long row, float scale) {
+    if (!*odd) return;
+    for (long p = (long)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += (long)gridDim.x * blockDim.x) {
+        const AbsCells a = abs_cells(px, py, pz, p, n_mesh, inv_h);
+        if (regular(a)) continue;
+        for (int c = 0; c < 8; ++c) {
+            const int o[3] = {c >> 2, (c >> 1) & 1, c & 1};
+            float w = 1.0f;
+            long i[3];
+            for (int d = 0; d < 3; ++d) {
+                w *= o[d] ? a.c[d].f : 1.0f - a.c[d].f;
+                i[d] = o[d] && a.c[d].m + 1 == n_mesh ? 0 : a.c[d].m + o[d];
+            }
+            atomicAdd(mesh + (i[0] * n_mesh + i[1]) * row + i[2], w * scale);
+        }
+    }
 }
 
 // Exclusive scan of the key counts in at most two launches (three for more than 4096 blocks of keys).  At a
@@ -369,6 +402,7 @@ __device__ __forceinline__ unsigned long long fixed_weight(float w) {
 // A CIC weight of either sign, below 2 in magnitude, in fixed point with `frac` bits after the point (rounded to even).
 __device__ __forceinline__ unsigned long long signed_weight(float w, int frac) {
     const uint32_t b = __float_as_uint(w), e = (b >> 23) & 255u;
+    if (e == 255u) return 0ull;  // not finite: k_abs_odd adds it
     const uint32_t m = (b & 0x7fffffu) | (e ? 0x800000u : 0u);  // w = m 2^(max(e, 1) - 150)
     const int s = (int)max(e, 1u) - 150 + frac;
     unsigned long long v = 0ull;
@@ -579,6 +613,7 @@ hipError_t sorted_deposit_absolute(const float* const pos[3], long n, int n_mesh
     sb.block_sums = reinterpret_cast<uint32_t*>(take((size_t)(tg.nkeys + 1023) / 1024 * 4));
     hipError_t e = launch_fill(reinterpret_cast<float*>(sb.count), sb.kstride, 0.0f, st);
     if (e != hipSuccess) return e;
+    uint32_t* const odd = full_weights ? sb.count + tg.nkeys : nullptr;  // the entry that no key counts in
     const dim3 grid((unsigned)((n + 255) / 256));
     {
         ProfScope ps(PROF_DEPOSIT, st);
@@ -591,14 +626,18 @@ hipError_t sorted_deposit_absolute(const float* const pos[3], long n, int n_mesh
             hipSuccess)
             return e;
         hipLaunchKernelGGL(k_abs_scatter, grid, dim3(256), 0, st, pos[0], pos[1], pos[2], n, n_mesh, inv_h, tg,
-                           sb.start, rank, sb.sorted);
+                           sb.start, rank, sb.sorted, odd);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     int lg = 0;
     while ((1L << lg) < n) ++lg;
     const bool sparse = (double)n_mesh * n_mesh * n_mesh > 1.5 * (double)n;
     const int frac = full_weights ? (sparse ? 61 - lg : std::min(32, 61 - lg)) : 0;
-    return run_tiles(n, 1, tg, sb, mesh, row, 0, scale, offset, frac, st);
+    e = run_tiles(n, 1, tg, sb, mesh, row, 0, scale, offset, frac, st);
+    if (e != hipSuccess || !odd) return e;
+    hipLaunchKernelGGL(k_abs_odd, dim3(std::min(grid.x, 1024u)), dim3(256), 0, st, pos[0], pos[1], pos[2], n, n_mesh, inv_h,
+                       odd, mesh, row, scale);
+    return hipGetLastError();
 }
 
 hipError_t sorted_deposit(const ParticlePtrs& P, long npr, int n_real, const LatticeGeom& dg, bool drift,

@@ -63,3 +63,29 @@ def test_fields_density(cola, n, count, where):
     bound = 2.0 ** -24 * ((terms + 5.0) * size + want.abs().clamp(min=1.0))
     worst = float(((got - want).abs() / bound).max())
     assert worst <= 1.0, worst
+
+
+@pytest.mark.parametrize("n,count", [(32, 40000), (48, 40000), (48, 100)])
+def test_positions_that_are_not_finite(cola, n, count):
+    """A NaN or infinite coordinate, or one beyond float32 once in cells, makes the eight cells that it reaches
+    and the force NaN or infinite, on either side of the size at which the deposit changes its form; NaN falls into
+    cell 0, infinity into that of the largest int32."""
+    box = 1.0
+    big = (2 ** 31 - 1) % n
+    small = (-(2 ** 31)) % n
+    for value, cell in ((float("nan"), 0), (float("inf"), big), (float("-inf"), small), (3e38, big)):
+        print(f"fields deposit: {value} among {count} on {n}^3", file=sys.stderr, flush=True)
+        gen = torch.Generator(device="cuda").manual_seed(count)
+        pos = torch.rand((3, count), generator=gen, device="cuda") * box
+        pos[:, 57] = torch.tensor([4.25, 5.5, (n - 1) + 0.75], device="cuda") / n
+        pos[1, 57] = value
+        out = cola.pm_fields(pos, n, box, acc=False)
+        want = torch.zeros((n, n, n), dtype=torch.bool, device="cuda")
+        for x in (4, 5):
+            for y in (cell, (cell + 1) % n):
+                for z in (n - 1, 0):
+                    want[x, y, z] = True
+        assert torch.equal(~torch.isfinite(out["delta"]), want)
+        assert not bool(torch.isfinite(out["g"]).any())
+    out = cola.pm_fields(torch.rand((3, count), device="cuda") * box, n, box, acc=False)
+    assert bool(torch.isfinite(out["delta"]).all()) and bool(torch.isfinite(out["g"]).all())
