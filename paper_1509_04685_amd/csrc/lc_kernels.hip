@@ -797,7 +797,8 @@ __global__ void __launch_bounds__(256, 2) k_conv3_wgrad(const uint16_t* __restri
     }
 }
 
-// dw[i] += sum over rows of part[row][i], the bias after the weights; 64 values by 16 groups of rows per block.
+// dw[i] += sum over rows of part[row][i], the bias after the weights; 64 values by 16 groups of rows per block.  The
+// sum is added with one atomic per value: backward passes of one network may overlap on several streams.
 __global__ void __launch_bounds__(1024) k_wgrad_reduce(const float* part, int rows, int np, int nw, float* dw, float* db) {
     __shared__ float red[16][64];
     const int c = threadIdx.x & 63, g = threadIdx.x >> 6;
@@ -812,8 +813,7 @@ __global__ void __launch_bounds__(1024) k_wgrad_reduce(const float* part, int ro
     if (g == 0 && i < np) {
 #pragma unroll
         for (int k = 1; k < 16; ++k) s += red[k][c];
-        if (i < nw) dw[i] += s;
-        else db[i - nw] += s;
+        atomicAdd(i < nw ? dw + i : db + (i - nw), s);
     }
 }
 
