@@ -508,8 +508,17 @@ def lc_backward(net, d_df, ws):
                "cola_lc_backward")
 
 
-def lc_loss(pos, box, df, g1, g3, stats=None, d_df=None):
-    """(stats, d_df): stats = [L, denominator] float64 device tensor, d_df = dL/d(dF) (3, n, n, n)."""
+# Up to these particles lc_loss takes the form with atomics to memory: its few launches then cost more than its
+# atomics (32^3 particles 31 us, tiled 43; 64^3 114 and 65).
+LC_LOSS_ATOMIC = 32768
+
+
+def lc_loss(pos, box, df, g1, g3, stats=None, d_df=None, ws=None):
+    """(stats, d_df): stats = [L, denominator] float64 device tensor, d_df = dL/d(dF) (3, n, n, n).
+
+    ws: scratch of cola_lc_loss_workspace_bytes(n, particles), about 50 bytes per particle, for the tiled form;
+    without it the call allocates it for its own duration, and takes the form with atomics to memory where
+    the particles are few or the memory is not to be had."""
     torch = _torch()
     n = df.shape[-1]
     if stats is None:
@@ -517,11 +526,15 @@ def lc_loss(pos, box, df, g1, g3, stats=None, d_df=None):
     if d_df is None:
         d_df = torch.empty((3, n, n, n), dtype=torch.float32, device=df.device)
     count = int(pos.shape[1])
-    nb = int(_lib.lib().cola_lc_loss_workspace_bytes(n, count))
-    ws = torch.empty(nb, dtype=torch.uint8, device=df.device) if nb else None
+    if ws is None and count > LC_LOSS_ATOMIC:
+        nb = int(_lib.lib().cola_lc_loss_workspace_bytes(n, count))
+        try:
+            ws = torch.empty(nb, dtype=torch.uint8, device=df.device) if nb else None
+        except torch.OutOfMemoryError:
+            ws = None
     _lib.check(_lib.lib().cola_lc_loss_ws(n, float(box), _ptrs3(pos), count, _ptrs3(df), _ptrs3(g1), _ptrs3(g3),
-                                          _ptr(stats), _ptr(d_df), _ptr(ws) if nb else None, nb, _stream()),
-               "cola_lc_loss")
+                                          _ptr(stats), _ptr(d_df), _ptr(ws) if ws is not None else None,
+                                          ws.numel() if ws is not None else 0, _stream()), "cola_lc_loss")
     return stats, d_df
 
 

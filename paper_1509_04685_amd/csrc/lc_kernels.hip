@@ -982,7 +982,7 @@ __global__ void k_lc_loss(const float* px, const float* py, const float* pz, lon
         loss_resid(c, n, df, g1, g3, p, r0, r1, r2);
         const double inv = 1.0 / stats[1];
         l2 = ((double)r0 * r0 + (double)r1 * r1 + (double)r2 * r2) * inv;
-        const float s = (float)(2.0 * inv);
+        const double s = 2.0 * inv;  // a float of it is denormal for a denominator beyond 1e38
         const float wx[2] = {1.0f - c.f[0], c.f[0]}, wy[2] = {1.0f - c.f[1], c.f[1]}, wz[2] = {1.0f - c.f[2], c.f[2]};
         const long V = (long)n * n * n;
 #pragma unroll
@@ -992,10 +992,10 @@ __global__ void k_lc_loss(const float* px, const float* py, const float* pz, lon
 #pragma unroll
                 for (int d = 0; d < 2; ++d) {
                     const long v = ((long)c.i[0][a] * n + c.i[1][b]) * n + c.i[2][d];
-                    const float w = wx[a] * wy[b] * wz[d] * s;
-                    atomicAdd(&ddf[v], w * r0);
-                    atomicAdd(&ddf[V + v], w * r1);
-                    atomicAdd(&ddf[2 * V + v], w * r2);
+                    const double w = (double)(wx[a] * wy[b] * wz[d]) * s;
+                    atomicAdd(&ddf[v], (float)(w * r0));
+                    atomicAdd(&ddf[V + v], (float)(w * r1));
+                    atomicAdd(&ddf[2 * V + v], (float)(w * r2));
                 }
     }
     red[threadIdx.x] = l2;
