@@ -186,10 +186,9 @@ __global__ void __launch_bounds__(256, 3) k_conv3_mfma(const uint16_t* __restric
         for (int ks = 0; ks < KSTEPS; ++ks)
             wreg[ks].u = ks * 4 + kb < 27 * C8 ? wg[m * 27 * C8 + ks * 4 + kb] : make_uint4(0, 0, 0, 0);
     } else {
-        for (int i = tid; i < COP * WS; i += 256) {
-            const int co = i / WS, v = i - co * WS;
-            sw[i] = v < 27 * C8 ? wg[co * 27 * C8 + v] : make_uint4(0, 0, 0, 0);
-        }
+        for (int i = tid; i < COP * 27 * C8; i += 256) sw[i / (27 * C8) * WS + i % (27 * C8)] = wg[i];
+        for (int i = tid; i < COP * (WS - 27 * C8); i += 256)
+            sw[i % COP * WS + 27 * C8 + i / COP] = make_uint4(0, 0, 0, 0);
     }
     const uint4* const aw = sw + m * WS + kb;
     // K step ks of lane (m, kb) holds channels (32 ks + 8 kb) % CINP .. + 7 of tap t = (32 ks + 8 kb) / CINP.  The taps'
@@ -470,10 +469,15 @@ static hipError_t run_conv_dens(const uint16_t* d0, const uint16_t* w, const flo
     return hipGetLastError();
 }
 
-// Blocks of a convolution: as many as run at a time (256 CUs, three each), so that a block's weights and
-// first halo, which nothing hides, come once (4096 blocks: 73 instead of 62 us for a 128^3 layer
-// of two tiles per block, the same on 256^3).
-constexpr long kConvBlocks = 768;
+// Blocks of a convolution: as many as run at a time, so that a block's weights and first halo, which nothing hides,
+// come once (16 -> 16 channels, three on each of 256 CUs: 4096 blocks 73 instead of 62 us for a 128^3 layer, the
+// same on 256^3; 32 -> 32 channels, whose 97 KB leave room for one: 64^3 47 us with 768 blocks, 38 with 256; 8 -> 32,
+// five: 128^3 71 us with 768 blocks, 67 with 1280).
+template <class K>
+static int conv_blocks_per_cu(K kernel, size_t lds) {
+    int n = 0;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, 256, lds) == hipSuccess && n > 0 ? n : 1;
+}
 
 static long conv_tiles(int n) { return (long)(n / TX) * (n / TY) * (n / TZ); }
 
@@ -486,9 +490,10 @@ static hipError_t run_conv(const uint16_t* in, const uint16_t* w, const float* b
     const size_t lds = weights + (size_t)HVOX * CINP * 2;
     auto kern = k_conv3_mfma<CINP, NB, EPI, FIELDS>;
     if (hipError_t e = allow_lds_lc(kern, lds); e != hipSuccess) return e;
+    static const long at_a_time = 256L * conv_blocks_per_cu(kern, lds);
     ProfScope ps(PROF_LC_CONV, st, CINP);  // tag: input channels (padded)
-    hipLaunchKernelGGL(kern, dim3((unsigned)std::min<long>(tiles, kConvBlocks)), dim3(256), lds, st, in, w, bias, out, out2,
-                       prev, n, (int)tiles, od.w3, od.b3, fs, od);
+    hipLaunchKernelGGL(kern, dim3((unsigned)std::min(tiles, at_a_time)), dim3(256), lds, st, in, w, bias, out, out2, prev,
+                       n, (int)tiles, od.w3, od.b3, fs, od);
     return hipGetLastError();
 }
 
