@@ -616,14 +616,21 @@ hipError_t lc_band(const float* T, int n, float beta, float* const out[3], long 
 // The four waves split the 8 K steps of a tile (KS = 4), or with 32 x 32 channels, whose sums need all
 // registers of a wave for a third of the taps, the (dx, dy) pairs.  The bias is one more product, with ones.
 //
-// A block sums its tiles in registers and writes its sums once, as its row of `part`; k_wgrad_reduce adds
-// the rows.  Flushing with float atomics from 1024 blocks, 7e6 atomics on 6912 addresses, and fragments
+// A block sums its tiles in registers and writes its sums once, as its row of partial sums; k_wgrad_reduce adds
+// the rows.  They lie in activations that are dead by then (WgradRows), which on the smallest meshes have room for few:
+// 32 channels on 16^3 ran 2 blocks, 84 us, with one such array, and run 4, 48 us, with both.  Flushing with float atomics from 1024 blocks, 7e6 atomics on 6912 addresses, and fragments
 // gathered by eight 16-bit reads each, took 574 us (16 x 16 channels) and 501 us (layer 1) on 128^3;
 // so 72 and 39 us, and 5 each for the rows.
 constexpr int SDZ = TV + 8;         // channel row of the staged upstream gradient
 constexpr int HZP = 24;             // z row of the staged halo (HZ used)
 constexpr int SXP = HX * HY * HZP + 8;  // channel row: an odd multiple of 16 bytes
 constexpr int HPAIRS = HX * HY * (HZ / 2);
+
+struct WgradRows {
+    float *a, *b;  // the first na rows, the others
+    int na;
+    __device__ __forceinline__ float* row(int r, int np) const { return r < na ? a + (long)r * np : b + (long)(r - na) * np; }
+};
 
 template <int C, bool FIRST>
 struct WgradShape {
@@ -638,7 +645,7 @@ struct WgradShape {
 
 template <int C, bool FIRST>
 __global__ void __launch_bounds__(256, 2) k_conv3_wgrad(const uint16_t* __restrict__ dz, const uint16_t* __restrict__ x,
-                                                        float* part, int n, int tiles) {
+                                                        WgradRows part, int n, int tiles) {
     using S = WgradShape<C, FIRST>;
     constexpr int MB = S::MB, NBN = S::NBN, KS = S::KS, TS = S::TS, NJ = S::NJ;
     constexpr int C8 = C / 8, X8 = FIRST ? 1 : C8;
@@ -765,7 +772,7 @@ __global__ void __launch_bounds__(256, 2) k_conv3_wgrad(const uint16_t* __restri
         }
     }
     // lane holds rows co = 16 i + 4 kb + q, column m of each product
-    float* const row = part + (long)blockIdx.x * S::NP;
+    float* const row = part.row(blockIdx.x, S::NP);
     float* const red = reinterpret_cast<float*>(smem);
     auto emit = [&](auto&& put) {
 #pragma unroll
@@ -804,14 +811,14 @@ __global__ void __launch_bounds__(256, 2) k_conv3_wgrad(const uint16_t* __restri
 
 // dw[i] += sum over rows of part[row][i], the bias after the weights; 64 values by 16 groups of rows per block.  The
 // sum is added with one atomic per value: backward passes of one network may overlap on several streams.
-__global__ void __launch_bounds__(1024) k_wgrad_reduce(const float* part, int rows, int np, int nw, float* dw, float* db) {
+__global__ void __launch_bounds__(1024) k_wgrad_reduce(WgradRows part, int rows, int np, int nw, float* dw, float* db) {
     __shared__ float red[16][64];
     const int c = threadIdx.x & 63, g = threadIdx.x >> 6;
     const int i = blockIdx.x * 64 + c;
     float s = 0.0f;
     if (i < np) {
 #pragma unroll 8
-        for (int r = g; r < rows; r += 16) s += part[(long)r * np + i];
+        for (int r = g; r < rows; r += 16) s += part.row(r, np)[i];
     }
     red[g][c] = s;
     __syncthreads();
@@ -822,13 +829,14 @@ __global__ void __launch_bounds__(1024) k_wgrad_reduce(const float* part, int ro
     }
 }
 
-// part: room for `room` floats of partial sums (at least one row).
+// a, b: two arrays of `room` floats each for partial sums (a of at least one row; b null: one array).
 template <int C, bool FIRST>
-static hipError_t run_wgrad(const uint16_t* dz, const uint16_t* x, float* dw, float* db, int n, float* part, long room,
-                            hipStream_t st) {
+static hipError_t run_wgrad(const uint16_t* dz, const uint16_t* x, float* dw, float* db, int n, uint16_t* a, uint16_t* b,
+                            long room, hipStream_t st) {
     using S = WgradShape<C, FIRST>;
+    const WgradRows part{reinterpret_cast<float*>(a), reinterpret_cast<float*>(b), (int)(room / S::NP)};
     const long tiles = conv_tiles(n);
-    const int blocks = (int)std::min(std::min(tiles, 512L), room / S::NP);  // two blocks per CU
+    const int blocks = (int)std::min(std::min(tiles, 512L), (long)part.na * (b ? 2 : 1));  // two blocks per CU
     auto kern = k_conv3_wgrad<C, FIRST>;
     if (hipError_t e = allow_lds_lc(kern, S::kLds); e != hipSuccess) return e;
     ProfScope ps(PROF_LC_WGRAD, st);
@@ -1198,13 +1206,12 @@ static hipError_t backward_c(const LcParams& P, const LcActs& A, LcGrads& G, int
                            st, ddf, A.z2, P.w3, out_scale, n, A.dz2, G.w3, G.b3);
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
-    // A2 is not read by the backward pass: its space takes the partial sums of the weight gradients
-    float* const part = reinterpret_cast<float*>(A.a2);
+    // A2 is not read by the backward pass, and dZ1 not yet written: they take partial sums of the weight gradients
     const long room = V * C / 2;
-    if (hipError_t e = run_wgrad<C, false>(A.dz2, A.a1, G.w2, G.b2, n, part, room, st); e != hipSuccess) return e;
+    if (hipError_t e = run_wgrad<C, false>(A.dz2, A.a1, G.w2, G.b2, n, A.a2, A.dz1, room, st); e != hipSuccess) return e;
     if (hipError_t e = run_conv<C, NB, EPI_DSILU>(A.dz2, P.wt2, nullptr, A.dz1, nullptr, A.z1, n, st); e != hipSuccess)
         return e;
-    return run_wgrad<C, true>(A.dz1, A.x0, G.w1, G.b1, n, part, room, st);
+    return run_wgrad<C, true>(A.dz1, A.x0, G.w1, G.b1, n, A.a2, nullptr, room, st);
 }
 
 hipError_t lc_backward(const LcParams& P, const LcActs& A, LcGrads& G, int n, float out_scale, float band,
