@@ -197,6 +197,8 @@ __device__ __forceinline__ AbsCells abs_cells(const float* px, const float* py, 
     return a;
 }
 
+constexpr int kOddRecord = (int)0x80000000;
+
 // Whether all fractions are those of a finite position near enough for its float32 cell coordinate to hold them:
 // within a quarter of [0, 1], which up to 2^22 cells from the origin they are.
 __device__ __forceinline__ bool regular(const AbsCells& a) {
@@ -218,43 +220,19 @@ __global__ void __launch_bounds__(256) k_abs_count(const float* px, const float*
     if (valid) __builtin_nontemporal_store(r, rank + p);
 }
 
-// odd (null: all points go the same way): set where a point is not regular; its record then has no weight, and
-// k_abs_odd adds it.
+// MARK: the cell of a point that is not regular has its sign set.
+template <bool MARK>
 __global__ void __launch_bounds__(256) k_abs_scatter(const float* px, const float* py, const float* pz, long n,
                                                      int n_mesh, float inv_h, TileGeom tg, const uint32_t* start,
-                                                     const uint32_t* rank, float4* sorted, uint32_t* odd) {
+                                                     const uint32_t* rank, float4* sorted) {
     const long p = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n) return;
     const uint32_t r = __builtin_nontemporal_load(rank + p);
-    AbsCells a = abs_cells(px, py, pz, p, n_mesh, inv_h);
+    const AbsCells a = abs_cells(px, py, pz, p, n_mesh, inv_h);
     int local;
     const uint32_t key = tile_key(tg, a.c[0].m, a.c[1].m, a.c[2].m, local);
-    if (odd && !regular(a)) {
-        *odd = 1u;
-        a.c[0].f = __int_as_float(0x7fc00000);
-    }
+    if (MARK && !regular(a)) local |= kOddRecord;
     sorted[start[key] + r] = make_float4(__int_as_float(local), a.c[0].f, a.c[1].f, a.c[2].f);
-}
-
-// The points that are not regular, added to the finished mesh with float atomics: NaN and infinite weights reach
-// the cells that they have there, as in a mesh of float sums.
-__global__ void __launch_bounds__(256) k_abs_odd(const float* px, const float* py, const float* pz, long n, int n_mesh,
-                                                 float inv_h, const uint32_t* odd, float* mesh, long row, float scale) {
-    if (!*odd) return;
-    for (long p = (long)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += (long)gridDim.x * blockDim.x) {
-        const AbsCells a = abs_cells(px, py, pz, p, n_mesh, inv_h);
-        if (regular(a)) continue;
-        for (int c = 0; c < 8; ++c) {
-            const int o[3] = {c >> 2, (c >> 1) & 1, c & 1};
-            float w = 1.0f;
-            long i[3];
-            for (int d = 0; d < 3; ++d) {
-                w *= o[d] ? a.c[d].f : 1.0f - a.c[d].f;
-                i[d] = o[d] && a.c[d].m + 1 == n_mesh ? 0 : a.c[d].m + o[d];
-            }
-            atomicAdd(mesh + (i[0] * n_mesh + i[1]) * row + i[2], w * scale);
-        }
-    }
 }
 
 // Exclusive scan of the key counts in at most two launches (three for more than 4096 blocks of keys).  At a
@@ -402,7 +380,6 @@ __device__ __forceinline__ unsigned long long fixed_weight(float w) {
 // A CIC weight of either sign, below 2 in magnitude, in fixed point with `frac` bits after the point (rounded to even).
 __device__ __forceinline__ unsigned long long signed_weight(float w, int frac) {
     const uint32_t b = __float_as_uint(w), e = (b >> 23) & 255u;
-    if (e == 255u) return 0ull;  // not finite: k_abs_odd adds it
     const uint32_t m = (b & 0x7fffffu) | (e ? 0x800000u : 0u);  // w = m 2^(max(e, 1) - 150)
     const int s = (int)max(e, 1u) - 150 + frac;
     unsigned long long v = 0ull;
@@ -439,6 +416,8 @@ __device__ __forceinline__ float signed_mass_of(unsigned long long v) {
 // of any size and its sign.  So theirs (FRAC = 1) are signed, with `frac` = 61 - ceil(log2 particles) bits after the
 // point where cells are more than three to two particles (rounded to cells 2^-61 a term, in units of the mean
 // density), and 32 otherwise (rounded to 2^-32; the contrast itself is rounded to 2^-25; the bits of cic_density).
+// Points that are not regular are left out of the sums and added to the finished tile with float atomics:
+// NaN and infinite weights reach the cells that they have there, as in a mesh of float sums.
 template <bool FRAC>
 __global__ void __launch_bounds__(256) k_dep_tile(TileGeom tg, SortBufs sb, long npr, float* mesh, long row,
                                                   long mesh_bstride, float scale, float offset, int frac) {
@@ -467,6 +446,7 @@ __global__ void __launch_bounds__(256) k_dep_tile(TileGeom tg, SortBufs sb, long
     const uint32_t i0 = threadIdx.x * chunk;
     const uint32_t i1 = min(total, i0 + chunk);
     int dx = 0, dy = 0, dz = 0;
+    bool odd = false;
     float4 next = make_float4(0.f, 0.f, 0.f, 0.f);
     if (i0 < i1) next = recs[pulled_record(pr, ps, i0, dx, dy, dz)];
     for (uint32_t i = i0; i < i1; ++i) {
@@ -474,6 +454,10 @@ __global__ void __launch_bounds__(256) k_dep_tile(TileGeom tg, SortBufs sb, long
         int hx, hy, hz;
         pulled_cell(tg, __float_as_int(rec.x), dx, dy, dz, hx, hy, hz);
         if (i + 1 < i1) next = recs[pulled_record(pr, ps, i + 1, dx, dy, dz)];
+        if (FRAC && (__float_as_int(rec.x) & kOddRecord)) {
+            odd = true;
+            continue;
+        }
         const float wx[2] = {1.0f - rec.y, rec.y}, wy[2] = {1.0f - rec.z, rec.z}, wz[2] = {1.0f - rec.w, rec.w};
         const bool okx[2] = {hx >= 0, hx + 1 < tb.nx}, oky[2] = {hy >= 0, hy + 1 < tb.ny}, okz[2] = {hz >= 0, hz + 1 < tb.nz};
         const int cell0 = ((hx << tg.ly) + hy) * (1 << tg.lz) + hz;  // of the lower corner (an index, not yet a cell)
@@ -488,7 +472,8 @@ __global__ void __launch_bounds__(256) k_dep_tile(TileGeom tg, SortBufs sb, long
                 if (okz[1]) atomicAdd(&acc[c + 1], fixed(wxy * wz[1]));
             }
     }
-    __syncthreads();
+    if (FRAC) odd = __syncthreads_or(odd);
+    else __syncthreads();
     float* out = mesh + (long)r * mesh_bstride + ((long)tb.x0 * tg.n + tb.y0) * row + tb.z0;
     const uint32_t row32 = (uint32_t)row;  // offsets within a tile: below 8 1536 rows of 1568 floats
     if (((tg.tz | tg.n | (int)row) & 3) == 0) {  // rows of the tile are whole, aligned float4s
@@ -507,6 +492,23 @@ __global__ void __launch_bounds__(256) k_dep_tile(TileGeom tg, SortBufs sb, long
             const int uz = i & (tg.tz - 1), uy = (i >> tg.lz) & (tg.ty - 1), ux = i >> (tg.lz + tg.ly);
             if (ux >= tb.nx || uy >= tb.ny || uz >= tb.nz) continue;
             out[__umul24(__umul24(ux, tg.n) + uy, row32) + uz] = cell(acc[i]);
+        }
+    }
+    if (!FRAC || !odd) return;
+    __syncthreads();
+    const float back = ldexpf(scale, frac - 32);  // the scale of a weight
+    for (uint32_t i = threadIdx.x; i < total; i += 256) {
+        const float4 rec = recs[pulled_record(pr, ps, i, dx, dy, dz)];
+        const int local = __float_as_int(rec.x);
+        if (!(local & kOddRecord)) continue;
+        int h[3];
+        pulled_cell(tg, local & ~kOddRecord, dx, dy, dz, h[0], h[1], h[2]);
+        const float f[3] = {rec.y, rec.z, rec.w};
+        for (int c = 0; c < 8; ++c) {
+            const int ux = h[0] + (c >> 2), uy = h[1] + (c >> 1 & 1), uz = h[2] + (c & 1);
+            if (ux < 0 || uy < 0 || uz < 0 || ux >= tb.nx || uy >= tb.ny || uz >= tb.nz) continue;
+            const float w = (c >> 2 ? f[0] : 1.0f - f[0]) * (c >> 1 & 1 ? f[1] : 1.0f - f[1]) * (c & 1 ? f[2] : 1.0f - f[2]);
+            atomicAdd(out + __umul24(__umul24(ux, tg.n) + uy, row32) + uz, w * back);
         }
     }
 }
@@ -613,7 +615,6 @@ hipError_t sorted_deposit_absolute(const float* const pos[3], long n, int n_mesh
     sb.block_sums = reinterpret_cast<uint32_t*>(take((size_t)(tg.nkeys + 1023) / 1024 * 4));
     hipError_t e = launch_fill(reinterpret_cast<float*>(sb.count), sb.kstride, 0.0f, st);
     if (e != hipSuccess) return e;
-    uint32_t* const odd = full_weights ? sb.count + tg.nkeys : nullptr;  // the entry that no key counts in
     const dim3 grid((unsigned)((n + 255) / 256));
     {
         ProfScope ps(PROF_DEPOSIT, st);
@@ -625,19 +626,15 @@ hipError_t sorted_deposit_absolute(const float* const pos[3], long n, int n_mesh
         if ((e = scan_counts(sb.count, sb.start, nullptr, sb.block_sums, tg.nkeys, 0, 1, (uint32_t)n, false, st)) !=
             hipSuccess)
             return e;
-        hipLaunchKernelGGL(k_abs_scatter, grid, dim3(256), 0, st, pos[0], pos[1], pos[2], n, n_mesh, inv_h, tg,
-                           sb.start, rank, sb.sorted, odd);
+        hipLaunchKernelGGL(full_weights ? k_abs_scatter<true> : k_abs_scatter<false>, grid, dim3(256), 0, st, pos[0],
+                           pos[1], pos[2], n, n_mesh, inv_h, tg, sb.start, rank, sb.sorted);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     int lg = 0;
     while ((1L << lg) < n) ++lg;
     const bool sparse = (double)n_mesh * n_mesh * n_mesh > 1.5 * (double)n;
     const int frac = full_weights ? (sparse ? 61 - lg : std::min(32, 61 - lg)) : 0;
-    e = run_tiles(n, 1, tg, sb, mesh, row, 0, scale, offset, frac, st);
-    if (e != hipSuccess || !odd) return e;
-    hipLaunchKernelGGL(k_abs_odd, dim3(std::min(grid.x, 1024u)), dim3(256), 0, st, pos[0], pos[1], pos[2], n, n_mesh, inv_h,
-                       odd, mesh, row, scale);
-    return hipGetLastError();
+    return run_tiles(n, 1, tg, sb, mesh, row, 0, scale, offset, frac, st);
 }
 
 hipError_t sorted_deposit(const ParticlePtrs& P, long npr, int n_real, const LatticeGeom& dg, bool drift,
