@@ -31,7 +31,8 @@ namespace cola {
 // 8 x 8 x 64 made the tile pass and the sort counters (many waves on one key) slower: 0.19 + 0.25 ms
 // against 0.13 + 0.16 ms for 8 x 8 x 16.  Meshes of several particles per cell take smaller tiles, until
 // one holds about 4096 particles, so that there are keys and blocks enough (uniform points in no
-// order, 2.1e6 on 28^3: 485 -> 354 us, 1.7e6 on 64^3: 487 -> 285 us).
+// order, 2.1e6 on 28^3: 485 -> 354 us, 1.7e6 on 64^3: 487 -> 285 us; 3e6 on 7^3 with tiles of 2 x 2 x 4 cells
+// 2600, of single cells 530).
 // Tiles that divide the side, as before, fell to 2 x 2 x 2 and to single cells for sides of 2 b and odd
 // sides: 1e6 points on 250^3 took 2389 us, and past 256^3 single-cell tiles are more blocks than a
 // grid holds.
@@ -43,8 +44,8 @@ TileGeom make_tiles(int n, long n_particles) {
     t.tz = 16;
     for (int c : {64, 32})
         if ((n + c - 1) / c * c - n <= n / 8 && (double)t.tx * t.tx * c * per_cell <= 1024.0) { t.tz = c; break; }
-    while ((double)t.tx * t.tx * t.tz * per_cell > 4096.0 && t.tx * t.tz > 8) {
-        if (t.tx > 4 || t.tz <= 4) t.tx /= 2;
+    while ((double)t.tx * t.tx * t.tz * per_cell > 4096.0 && t.tx * t.tz > 1) {
+        if (t.tx > 4 || (t.tz <= 4 && t.tx > 1)) t.tx /= 2;
         else t.tz /= 2;
     }
     t.ty = t.tx;
