@@ -378,17 +378,6 @@ __device__ __forceinline__ unsigned long long fixed_weight(float w) {
     return (unsigned long long)(whole ? 1u : 0u) << 32 | (whole ? 0u : (uint32_t)t);
 }
 
-// A CIC weight of either sign, below 2 in magnitude, in fixed point with `frac` bits after the point (rounded to even).
-__device__ __forceinline__ unsigned long long signed_weight(float w, int frac) {
-    const uint32_t b = __float_as_uint(w), e = (b >> 23) & 255u;
-    const uint32_t m = (b & 0x7fffffu) | (e ? 0x800000u : 0u);  // w = m 2^(max(e, 1) - 150)
-    const int s = (int)max(e, 1u) - 150 + frac;
-    unsigned long long v = 0ull;
-    if (s >= 0) v = (unsigned long long)m << min(s, 63);
-    else if (s > -25) v = (m + (1u << (-s - 1)) - 1u + ((m >> -s) & 1u)) >> -s;
-    return (int)b < 0 ? 0ull - v : v;
-}
-
 // A 32.32 fixed-point sum as float, rounded once: its 32 leading bits, the last of them also set for any
 // bit below (round to nearest even of the conversion then sees them).
 __device__ __forceinline__ float mass_of(unsigned long long v) {
@@ -396,9 +385,6 @@ __device__ __forceinline__ float mass_of(unsigned long long v) {
     const int s = hi ? __clz((int)hi) : 32;
     const unsigned long long t = v << s;
     return ldexpf((float)((uint32_t)(t >> 32) | min((uint32_t)t, 1u)), -s);
-}
-__device__ __forceinline__ float signed_mass_of(unsigned long long v) {
-    return (long long)v < 0 ? -mass_of(0ull - v) : mass_of(v);
 }
 
 // One block per tile: pull the records whose corners reach into the tile, accumulate in LDS,
@@ -437,8 +423,9 @@ __global__ void __launch_bounds__(256) k_dep_tile(TileGeom tg, SortBufs sb, long
     __syncthreads();
     const uint32_t total = pr.len[14];
     const PullStarts ps = pull_starts(pr);
-    auto fixed = [&](float w) { return FRAC ? signed_weight(w, frac) : fixed_weight(w); };
-    auto cell = [&](unsigned long long v) { return fmaf(FRAC ? signed_mass_of(v) : mass_of(v), scale, offset); };
+    const float units = ldexpf(1.0f, frac);  // of a weight of 1
+    auto fixed = [&](float w) { return FRAC ? (unsigned long long)__float2ll_rn(w * units) : fixed_weight(w); };
+    auto cell = [&](unsigned long long v) { return fmaf(FRAC ? (float)(long long)v : mass_of(v), scale, offset); };
     // Each thread sweeps a contiguous chunk of the concatenated records, so that the lanes of a
     // wave work on records far apart in the sorted order: records of one key range are in
     // Lagrangian order, and neighbouring particles hit the same cells -- consecutive records on
@@ -497,7 +484,7 @@ __global__ void __launch_bounds__(256) k_dep_tile(TileGeom tg, SortBufs sb, long
     }
     if (!FRAC || !odd) return;
     __syncthreads();
-    const float back = ldexpf(scale, frac - 32);  // the scale of a weight
+    const float back = scale * units;  // the scale of a weight
     for (uint32_t i = threadIdx.x; i < total; i += 256) {
         const float4 rec = recs[pulled_record(pr, ps, i, dx, dy, dz)];
         const int local = __float_as_int(rec.x);
@@ -563,7 +550,7 @@ hipError_t run_tiles(long npr, int n_real, const TileGeom& tg, const SortBufs& s
     const dim3 grid((unsigned)tg.ntiles, n_real);
     if (frac)
         hipLaunchKernelGGL(k_dep_tile<true>, grid, dim3(256), lds, st, tg, sb, npr, mesh, row, mesh_bstride,
-                           ldexpf(scale, 32 - frac), offset, frac);
+                           ldexpf(scale, -frac), offset, frac);
     else
         hipLaunchKernelGGL(k_dep_tile<false>, grid, dim3(256), lds, st, tg, sb, npr, mesh, row, mesh_bstride, scale,
                            offset, 0);
