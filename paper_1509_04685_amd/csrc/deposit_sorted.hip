@@ -217,7 +217,7 @@ __global__ void __launch_bounds__(256) k_abs_count(const float* px, const float*
         int local;
         key = tile_key(tg, a.c[0].m, a.c[1].m, a.c[2].m, local);
     }
-    const uint32_t r = wave_increment(count, key, valid);
+    const uint32_t r = wave_increment<true>(count, key, valid);
     if (valid) __builtin_nontemporal_store(r, rank + p);
 }
 
