@@ -104,6 +104,17 @@ __device__ __forceinline__ void store_stream(float2* p, float2 v) {
     __builtin_nontemporal_store(v.y, &p->y);
 }
 
+// The fused z pass, PART: a block of fewer than 16 lines takes a part of a 128-byte line per kz plane, and the block
+// that takes the rest finds it in L2 only if the load was not non-temporal (768^3, 8 lines: 6.4 GB read,
+// 5.45 so, the size of the spectra; the step 0.7 % shorter).  With 16 lines nothing is left, and non-temporal loads
+// spare the cache (corrected steps on 256^3 1.5 % longer without).  A compile-time choice: of two branches the
+// compiler makes one, without the hint.
+template <bool PART>
+__device__ __forceinline__ float2 load_z(const float2* p) {
+    if constexpr (PART) return *p;
+    else return load_stream(p);
+}
+
 // Column passes: streaming access only when a tile row fills whole 128-byte lines (16 columns).
 template <int TK>
 __device__ __forceinline__ float2 load_col(const float2* p) {
@@ -265,7 +276,7 @@ __global__ void __launch_bounds__(512) k_fft_z_c2r(const float2* in, long in_bst
 // which the whole block then writes with contiguous stores.  A CIC gather finds the three
 // components of a cell pair (z, z + 1) in 24 contiguous bytes instead of three lines of separate
 // meshes.
-template <class LE>
+template <class LE, bool PART>
 __global__ void __launch_bounds__(1024) k_fft_z_c2r3(const float2* in0, const float2* in1, const float2* in2,
                                                      long in_bstride, float* out, long out_row, long out_bstride,
                                                      int n, long plane, int lw, LE eng, const float2* tw, float kf,
@@ -293,9 +304,8 @@ __global__ void __launch_bounds__(1024) k_fft_z_c2r3(const float2* in0, const fl
         const uint32_t pl = (uint32_t)plane;
         float2 xv[R];
 #pragma unroll
-        for (int u = 0; u < R; ++u)  // k plane < (n/2 + 1) plane < 2^31
-            xv[u] = load_stream(src + (uint32_t)(k0 + u * T) * pl);
-        const float2 xm = lt < W ? load_stream(src + (long)M * plane) : make_float2(0.f, 0.f);
+        for (int u = 0; u < R; ++u) xv[u] = load_z<PART>(src + (uint32_t)(k0 + u * T) * pl);  // k plane < (n/2 + 1) plane < 2^31
+        const float2 xm = lt < W ? load_z<PART>(src + (long)M * plane) : make_float2(0.f, 0.f);
 #pragma unroll
         for (int u = 0; u < R; ++u) {
             const int k = k0 + u * T;
@@ -616,14 +626,21 @@ inline hipError_t go_z_c2r(const FftLaunch& L, LE e) {
     return hipGetLastError();
 }
 
-template <class LE>
-inline hipError_t go_z_c2r3(const FftLaunch& L, LE e) {
-    auto kern = k_fft_z_c2r3<LE>;
+template <class LE, bool PART>
+inline hipError_t go_z_c2r3_lines(const FftLaunch& L, LE e) {
+    auto kern = k_fft_z_c2r3<LE, PART>;
     const size_t lds = z_lds_bytes<LE>(L, e, 3);
     if (hipError_t ea = allow_lds_fft(kern, lds); ea != hipSuccess) return ea;
     hipLaunchKernelGGL(kern, L.grid, L.block, lds, L.st, L.cin, L.cin1, L.cin2, L.in_bstride, L.rout, L.out_row,
                        L.out_bstride, L.mesh_n, L.plane, L.lw, e, L.tw, L.kf, L.scale);
     return hipGetLastError();
+}
+
+// W: lines per block where they are known at compile time (the default of a side; a tuned number of lines keeps its hint).
+template <class LE, int W = 0>
+inline hipError_t go_z_c2r3(const FftLaunch& L, LE e) {
+    if constexpr (W > 0) return go_z_c2r3_lines<LE, (W < 16)>(L, e);
+    else return L.lw < 4 ? go_z_c2r3_lines<LE, true>(L, e) : go_z_c2r3_lines<LE, false>(L, e);
 }
 
 template <class LE, int OPR>
@@ -695,13 +712,13 @@ inline hipError_t static_rows_ops(const FftLaunch& L) {
     }
 }
 
-template <int M, int R, FftOp OP>
+template <int M, int R, FftOp OP, int W = 0>
 inline hipError_t static_z_op(const FftLaunch& L) {
     using E = StatLine<M, R, 1, 2, false>;
     if (L.probe) return hipSuccess;
     if constexpr (OP == OP_Z_R2C) return go_z_r2c<E>(L, E{});
     else if constexpr (OP == OP_Z_C2R) return go_z_c2r<E>(L, E{});
-    else return go_z_c2r3<E>(L, E{});
+    else return go_z_c2r3<E, W>(L, E{});
 }
 
 template <int M, int R>
@@ -797,7 +814,8 @@ inline hipError_t static_default(const FftLaunch& L) {
                         c = default_pass(PC_COLS, n);
     static_assert(z.R && z3.R && r.R && c.R, "a side without a compile-time plan");
     if (L.split) return hipErrorNotSupported;
-    if (L.op == OP_Z_C2R3) return L.R == z3.R ? static_z_op<n / 2, z3.R, OP_Z_C2R3>(L) : hipErrorNotSupported;
+    if (L.op == OP_Z_C2R3)
+        return L.R == z3.R ? static_z_op<n / 2, z3.R, OP_Z_C2R3, z3.width>(L) : hipErrorNotSupported;
     if (is_z_op(L.op)) {
         if (L.R != z.R) return hipErrorNotSupported;
         return L.op == OP_Z_R2C ? static_z_op<n / 2, z.R, OP_Z_R2C>(L) : static_z_op<n / 2, z.R, OP_Z_C2R>(L);
