@@ -123,13 +123,16 @@ def node_index(table, a_out):
     return max(0, min(j, len(a) - 1))
 
 
-KERNEL_SOURCES = {"fft": ("fft.hip", "fft_core.h", "fft_kernels.h", "fft_static_1536.hip", "fft_static_768.hip",
-                          "fft_static_512.hip", "fft_static_384.hip", "fft_static_288.hip", "fft_static_256.hip"), "cic": ("deposit_sorted.hip", "lattice.h", "tile_pull.h", "wave_ops.h"),
-                  "pk_deposit": ("deposit_sorted.hip", "force_gather.h", "lattice.h", "wave_ops.h"),
-                  "gather_kick_drift": ("deposit_sorted.hip", "pm_kernels.hip", "force_gather.h", "lattice.h",
-                                        "wave_ops.h"),
-                  "gather": ("pm_kernels.hip", "force_gather.h", "lattice.h"),
-                  "lc": ("lc_kernels.hip", "lc_loss.hip", "lc_cic.h"),
+# Source files of each kernel kind with the headers that they include, except cola_internal.h and lc_internal.h
+# (declarations for all).
+FFT_SOURCES = tuple(["fft.hip", "fft_core.h", "fft_kernels.h", "wave_ops.h"] +
+                    [f"fft_static_{n}.hip" for n in (1536, 768, 512, 384, 288, 256)] +
+                    [f"fft_static_sides_{i}.hip" for i in range(4)])
+DEPOSIT_SOURCES = ("deposit_sorted.hip", "force_gather.h", "lattice.h", "tile_pull.h", "wave_ops.h")
+GATHER_SOURCES = ("pm_kernels.hip", "force_gather.h", "lattice.h")
+KERNEL_SOURCES = {"fft": FFT_SOURCES, "cic": DEPOSIT_SOURCES, "pk_deposit": DEPOSIT_SOURCES,
+                  "gather_kick_drift": DEPOSIT_SOURCES + ("pm_kernels.hip",), "gather": GATHER_SOURCES,
+                  "lc": ("lc_kernels.hip", "lc_loss.hip", "lc_cic.h", "force_gather.h", "tile_pull.h", "wave_ops.h"),
                   "pk_alias": ("pk_kernels.hip",)}
 
 
