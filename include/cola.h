@@ -377,7 +377,10 @@ int cola_pm_force_noalloc(const cola_problem* prob, const cola_particles* in, fl
  * each, any real, wrapped into the box) onto n_mesh^3 cells, delta = rho / rho_bar - 1, the force
  * g_k = i k delta_k / k^2 as in cola_pm_force, and its CIC interpolation to the particles.  Each
  * output may be NULL: delta (dense n_mesh^3), g[3] (dense n_mesh^3 each), acc[3] (n each), all
- * device.  ws: cola_pm_fields_workspace_bytes(n_mesh) bytes. */
+ * device.  ws: cola_pm_fields_workspace_bytes(n_mesh) bytes.  A coordinate that is NaN or infinite makes the cells
+ * that it reaches so (NaN falls into cell 0), and with them the whole force.  Up to about one particle per cell the
+ * density is an integer sum and repeats to the bit; with more, whose sorting the workspace does not hold,
+ * float sums in any order round differently from call to call. */
 size_t cola_pm_fields_workspace_bytes(int32_t n_mesh);
 int cola_pm_fields(int32_t n_mesh, double box, const float* pos[3], int64_t n, float* delta, float* g[3],
                    float* acc[3], void* ws, size_t ws_bytes, void* stream);

@@ -11,9 +11,11 @@
 // into M.  It accumulates the corners that fall inside M in LDS and writes every cell of M once,
 // already converted to delta = rho * scale + offset.
 //
-// Passes: bin (key + cell record per particle, wave-aggregated counts), exclusive scan of the
-// counts, scatter of the records into key order, tile accumulation.  Records keep the CIC
-// fractions exactly as computed from the lattice index and displacement.
+// Passes: bin (wave-aggregated counts per key, which leave each particle its rank in its key), exclusive scan of the
+// counts, place (the record of every particle, formed again from its position, at its key's start plus its
+// rank), tile accumulation.  Particles drifted on the fly, whose positions are not kept, are binned with key and
+// record, which a scatter pass moves.  Records keep the CIC fractions exactly as computed from the lattice index and
+// displacement.
 
 #include <algorithm>
 

@@ -304,8 +304,8 @@ ShapeCache& shape_cache() {
 }  // namespace
 
 // same_digits: the transform of a power spectrum.  Its float64 sums carry the rounding of the plan (1e-8
-// between two plans of one side), and spectra are kept and compared between runs; so untuned spectra stay
-// on the plan that they always had, with the default lines per block where that plan has them.
+// between two plans of one side), so spectra of a side that the process has not tuned stay on the plan that they
+// always had, with the default lines per block where that plan has them; a tuned side has its tuned plan's digits.
 static FftShape shape_for(FftKind k, int n, bool same_digits = false) {
     ShapeCache& c = shape_cache();
     std::lock_guard<std::mutex> g(c.mu);

@@ -1,7 +1,7 @@
 // FFT pass kernels, written against a line engine (DynLine: host-built plan, any size;
 // StatLine: plan fixed at compile time), and their launch helpers.  Included by fft.hip (the
-// host logic and the dynamic instantiations) and by the fft_static_*.hip files (the static
-// instantiations for the mesh sizes of the workloads).
+// host logic and the dynamic instantiations), by fft_static_<n>.hip (the static instantiations of the workloads' mesh
+// sizes, several shapes each) and by fft_static_sides_<i>.hip (one default shape of every other smooth side).
 //
 // Layouts: real fields are [x][y][z] with rows of `row` floats (2 nzp in the workspace meshes, z
 // contiguous); the half spectrum is transposed, [kz][x][y] of float2 with y contiguous, so that no
@@ -758,7 +758,7 @@ inline hipError_t static_z_ops(const FftLaunch& L) {
 //    meshes (96^3 3.8 against 4.3).
 //  * powers of two take R >= 8, whose stages are those of the run-time plans with 16 values, so that their
 //    digits stay (R = 4 would gain 3 % on the z passes of 64^3 and 128^3).
-//  * never less than a wave per block.
+//  * never less than a wave per block while lines are left to add (up to 32: side 16 ends with 32 threads).
 // The run-time plans that most of these sides had before took, for x_green, 23.6 against 7.1 (96^3) and
 // 909 against 245 (432^3); for z c2r3 at 324^3 125 against 80.
 

@@ -14,9 +14,9 @@
 //   scatter  particle records {x, y, z, index} in cell order, at the cell's start plus the rank;
 //   local    the pairs of records of one block that follow each other in a row of cells, joined in
 //            LDS; every particle's first parent is the smallest index of its set so far;
-//   link     one thread per record: the other pairs with the records after it in its own cell and
-//            with every record of the 13 "forward" neighbour cells (each unordered pair of
-//            cells once); a friend pair joins its two trees in a lock-free union-find;
+//   link     one thread per record: the other pairs with the records after it in its own cell and with
+//            those of the 13 "forward" neighbour cells (each unordered pair of cells once) that lie within
+//            reach; a friend pair joins its two trees in a lock-free union-find;
 //   finish   every particle's root, written back as its label (full compression), and the
 //            group sizes at the roots (sizes start at 1: only members below a root count themselves).
 //
@@ -26,8 +26,8 @@
 // and the root of each tree is the smallest index in it.  Each failed compare-and-swap means
 // another thread completed a hook, and at most n - 1 hooks exist, so every thread exits.
 //
-// Cost: the link pass tests every pair in each cell and between forward neighbours, so its time
-// grows with the square of the particles per cell.  At the mean density there is about one
+// Cost: the link pass tests every pair in each cell and between the neighbours within a linking length of a
+// particle's own cell, so its time grows with the square of the particles per cell.  At the mean density there is about one
 // particle per cell; the densest cells of the z = 0 runs hold a few hundred.  Positions that
 // pile a large fraction of all particles into one cell (a degenerate input) make the pass
 // quadratic in n.

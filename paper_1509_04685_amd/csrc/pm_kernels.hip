@@ -92,9 +92,9 @@ __global__ void k_deposit_abs(const float* px, const float* py, const float* pz,
     const float* ps[3] = {px, py, pz};
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        float u = __fmul_rn(ps[d][gid], inv_h);  // rounded, so that u - floor(u) >= 0
-        float fl = floorf(u);
-        c[d].f = u - fl;
+        // as the tiled deposit of points: the cell of the rounded product, the fraction of the exact one
+        const float x = ps[d][gid], fl = floorf(x * inv_h);
+        c[d].f = fmaf(x, inv_h, -fl);
         int m = (int)fl % n_mesh;
         m = m < 0 ? m + n_mesh : m;
         c[d].m = min(max(m, 0), n_mesh - 1);
@@ -151,7 +151,7 @@ __device__ __forceinline__ float bracket(float g, float d1, float d2m, float s1,
 }
 
 // p += kick [g - D1 psi1 - (D2 - D1^2) psi2];  x += p Dr + dD1 psi1 + dD2 psi2.
-// Grid: (particle blocks, realizations).  Every particle array is read before the first store, so
+// Grid: lattice_grid (blocks of one lattice plane, planes, realizations).  Every particle array is read before the first store, so
 // the twelve streaming loads and the eight corner-column loads are in flight together (the arrays of one
 // particle set could alias as far as the compiler knows, which would otherwise order them).  The
 // particle streams are non-temporal, leaving L2 to the force-mesh lines that neighbouring
