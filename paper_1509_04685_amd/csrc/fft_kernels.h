@@ -106,9 +106,10 @@ __device__ __forceinline__ void store_stream(float2* p, float2 v) {
 
 // The fused z pass, PART: a block of fewer than 16 lines takes a part of a 128-byte line per kz plane, and the block
 // that takes the rest finds it in L2 only if the load was not non-temporal (768^3, 8 lines: 6.4 GB read,
-// 5.45 so, the size of the spectra; the step 0.7 % shorter).  With 16 lines nothing is left, and non-temporal loads
-// spare the cache (corrected steps on 256^3 1.5 % longer without).  A compile-time choice: of two branches the
-// compiler makes one, without the hint.
+// 5.45 so, the size of the spectra; the step 0.7 % shorter).  With 16 lines nothing is left, and three spectra that
+// fit the 256 MB cache are found there: non-temporal loads then spare the cache for what follows (corrected steps
+// on 256^3 1.3 % longer without).  A compile-time choice: of two branches the compiler makes one, without the hint.
+constexpr bool z_part_lines(int n, int lines) { return lines < 16 && 12L * n * n * n > (256L << 20); }
 template <bool PART>
 __device__ __forceinline__ float2 load_z(const float2* p) {
     if constexpr (PART) return *p;
@@ -639,8 +640,8 @@ inline hipError_t go_z_c2r3_lines(const FftLaunch& L, LE e) {
 // W: lines per block where they are known at compile time (the default of a side; a tuned number of lines keeps its hint).
 template <class LE, int W = 0>
 inline hipError_t go_z_c2r3(const FftLaunch& L, LE e) {
-    if constexpr (W > 0) return go_z_c2r3_lines<LE, (W < 16)>(L, e);
-    else return L.lw < 4 ? go_z_c2r3_lines<LE, true>(L, e) : go_z_c2r3_lines<LE, false>(L, e);
+    if constexpr (W > 0) return go_z_c2r3_lines<LE, z_part_lines(2 * LE::kN, W)>(L, e);
+    else return z_part_lines(L.mesh_n, 1 << L.lw) ? go_z_c2r3_lines<LE, true>(L, e) : go_z_c2r3_lines<LE, false>(L, e);
 }
 
 template <class LE, int OPR>
