@@ -11,6 +11,7 @@
 //   scan     of the counts
 //   scatter  32-byte records {cell, fractions, r} in key order
 //   tile     accumulation, d_dF written (no clear before)
+// 128^3 particles on 128^3 cells in a training step: 111 + 5 + 22 + 62 us.
 //
 // The LDS sums are 64-bit fixed point: LDS integer atomics run at tens of times the rate of float ones.  The unit is
 // 2^-b of the power of two above the tile's largest term, b = min(52, 62 - ceil(log2 records)), so that no sum
