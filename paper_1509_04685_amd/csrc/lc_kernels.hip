@@ -836,7 +836,10 @@ static hipError_t run_wgrad(const uint16_t* dz, const uint16_t* x, float* dw, fl
     using S = WgradShape<C, FIRST>;
     const WgradRows part{reinterpret_cast<float*>(a), reinterpret_cast<float*>(b), (int)(room / S::NP)};
     const long tiles = conv_tiles(n);
-    const int blocks = (int)std::min(std::min(tiles, 512L), (long)part.na * (b ? 2 : 1));  // two blocks per CU
+    // two blocks per CU where the first array has the rows; the second one only up to 128, since a row costs its scattered
+    // stores (32 channels, whole backward pass: 48^3 163 -> 136 us with 126 for 63 blocks, 64^3 225 -> 264 with 302 for 151)
+    const long rows = std::max((long)part.na, b ? std::min(2L * part.na, 128L) : 0L);
+    const int blocks = (int)std::min(std::min(tiles, 512L), rows);
     auto kern = k_conv3_wgrad<C, FIRST>;
     if (hipError_t e = allow_lds_lc(kern, S::kLds); e != hipSuccess) return e;
     ProfScope ps(PROF_LC_WGRAD, st);
