@@ -24,8 +24,9 @@ def cola():
     return c
 
 
-def density(pos, n, box):
-    """(density contrast, sum of weights in its units, number of terms) per cell in float64."""
+def density(pos, n, box, least=0.0):
+    """(density contrast, sum of weights in its units, number of terms) per cell in float64; weights below `least`
+    (a point that rounds up to a node has a fraction of about -1e-7 of its cell coordinate) are raised to it."""
     inv = np.float32(n / box)
     fl = np.floor(pos * inv)
     assert fl.dtype == np.float32
@@ -38,7 +39,7 @@ def density(pos, n, box):
         w = np.ones(pos.shape[1])
         for d in range(3):
             w = w * (f[d] if o[d] else 1.0 - f[d])
-        rho += np.bincount(i, weights=np.maximum(w, 0.0), minlength=n ** 3)
+        rho += np.bincount(i, weights=np.maximum(w, least), minlength=n ** 3)
         number += np.bincount(i, minlength=n ** 3)
     scale = n ** 3 / pos.shape[1]
     return rho * scale - 1.0, rho * scale, number * scale
@@ -63,3 +64,22 @@ def test_density(cola, n, count, width):
     worst = float((err / (4e-7 * rho + 2e-7 + 2.4e-10 * terms)).max())
     assert worst <= 1.0, worst
     assert torch.equal(cola.cic_density(pos, n, box), got)
+
+
+# one block sorts up to 4096 points on up to 8192 keys (8 per tile: 6912 on 96^3, 9464 on 104^3), the general path more
+@pytest.mark.parametrize("n,count", [(2, 1), (2, 4096), (3, 4097), (16, 4096), (16, 4097), (96, 4096), (96, 4097),
+                                     (104, 4096), (33, 1), (64, 1023), (64, 1025)])
+def test_few_points(cola, n, count):
+    print(f"few points: {count} on {n}^3", file=sys.stderr, flush=True)
+    box = 50.0
+    gen = torch.Generator(device="cuda").manual_seed(n + count)
+    pos = torch.rand((3, count), generator=gen, device="cuda") * box
+    got = cola.cic_density(pos, n, box)
+    want, rho, terms = density(pos.cpu().numpy(), n, box)
+    err = np.abs(got.cpu().numpy().astype(np.float64).reshape(-1) - want)
+    assert np.all(err <= 4e-7 * rho + 2e-7 + 2.4e-10 * terms)
+    if n in (16, 64, 96):  # pm_fields keeps the sign of a weight
+        want, rho, terms = density(pos.cpu().numpy(), n, box, least=-1.0)
+        rho = np.abs(rho)
+        fields = cola.pm_fields(pos, n, box, g=False, acc=False)["delta"].cpu().numpy().astype(np.float64).reshape(-1)
+        assert np.all(np.abs(fields - want) <= 4e-7 * rho + 2e-7 + 2.4e-10 * terms)
